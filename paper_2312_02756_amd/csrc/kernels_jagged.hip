@@ -35,8 +35,10 @@ __device__ __forceinline__ int64_t npairs(int64_t c) { return c * (c - 1) / 2; }
 
 // ------------------------------------------------------------ pair offsets
 
-// Multi-workgroup exclusive scan of n_e (n_e - 1)/2 in three launches, with
-// pair_offsets itself holding the per-tile totals between them (no scratch):
+// Exclusive scan of n_e (n_e - 1)/2.  Up to kScanOnce events in one launch:
+// workgroup b sums the pair counts before its tile itself (k_po_once).  More
+// events in three launches, with pair_offsets itself holding the per-tile
+// totals between them (no scratch):
 //   1. workgroup b sums the pair counts of its kScanTile events and writes the
 //      total to pair_offsets[end_b], end_b = min((b + 1) kScanTile, ne);
 //   2. one workgroup turns those totals into running totals in place and sets
@@ -45,9 +47,15 @@ __device__ __forceinline__ int64_t npairs(int64_t c) { return c * (c - 1) / 2; }
 //      writes pair_offsets[e + 1] for its events except the last one, whose
 //      value step 2 left in place -- so no entry one workgroup reads is
 //      written by another.
-constexpr int kScanThreads = 256;
-constexpr int kScanPer = 16;
+// Tiles of 2048 events (512 workgroups of 8 wavefronts on 2^20 events) keep
+// enough loads in flight: 12.9 us for the three launches on 2^20 events against
+// 17.6 with 4096 events by four wavefronts.  One launch takes 2.8 us on 1,000
+// events (three: 7.6), 9.0 on 32,000 (10.1) and 12.8 on 64,000 (10.0, but two
+// launches and the gaps between them more).
+constexpr int kScanThreads = 512;
+constexpr int kScanPer = 4;
 constexpr int kScanTile = kScanThreads * kScanPer;
+constexpr int64_t kScanOnce = 1 << 16;
 
 // Exclusive prefix over the workgroup of one int64 per thread; *total gets
 // the workgroup's sum.  ws holds one int64 per wavefront.
@@ -101,13 +109,11 @@ __global__ __launch_bounds__(1024) void k_po_scan_totals(int64_t* __restrict__ p
   }
 }
 
-__global__ __launch_bounds__(kScanThreads) void k_po_tile_scan(const int64_t* __restrict__ off,
-                                                               int64_t* __restrict__ po, int64_t ne) {
-  __shared__ int64_t c[kScanTile];
-  __shared__ int64_t ws[kScanThreads / 64];
-  const int64_t b0 = (int64_t)blockIdx.x * kScanTile;
+// pair_offsets[e + 1] for the events [b0, end) of a tile whose first pair is
+// `base` (the last event's left out unless `last`).
+__device__ __forceinline__ void scan_tile(const int64_t* __restrict__ off, int64_t* __restrict__ po, int64_t b0,
+                                          int64_t ne, int64_t base, bool last, int64_t* c, int64_t* ws) {
   const int64_t end = min(b0 + kScanTile, ne);
-  const int64_t base = (blockIdx.x == 0) ? 0 : po[b0];
 #pragma unroll
   for (int j = 0; j < kScanPer; ++j) {
     const int idx = j * kScanThreads + threadIdx.x;
@@ -130,8 +136,32 @@ __global__ __launch_bounds__(kScanThreads) void k_po_tile_scan(const int64_t* __
   for (int j = 0; j < kScanPer; ++j) {
     const int idx = j * kScanThreads + threadIdx.x;
     const int64_t e = b0 + idx;
-    if (e + 1 < end) po[e + 1] = c[idx];
+    if (e + (last ? 0 : 1) < end) po[e + 1] = c[idx];
   }
+}
+
+__global__ __launch_bounds__(kScanThreads) void k_po_tile_scan(const int64_t* __restrict__ off,
+                                                               int64_t* __restrict__ po, int64_t ne) {
+  __shared__ int64_t c[kScanTile];
+  __shared__ int64_t ws[kScanThreads / 64];
+  const int64_t b0 = (int64_t)blockIdx.x * kScanTile;
+  scan_tile(off, po, b0, ne, (blockIdx.x == 0) ? 0 : po[b0], false, c, ws);
+}
+
+// One launch: the workgroup first sums the pair counts of all earlier events
+// (at most kScanOnce, 128 per thread, read from L2), then scans its tile.
+__global__ __launch_bounds__(kScanThreads) void k_po_once(const int64_t* __restrict__ off, int64_t* __restrict__ po,
+                                                          int64_t ne) {
+  __shared__ int64_t c[kScanTile];
+  __shared__ int64_t ws[kScanThreads / 64];
+  const int64_t b0 = (int64_t)blockIdx.x * kScanTile;
+  int64_t before = 0;
+#pragma unroll 16
+  for (int64_t e = threadIdx.x; e < b0; e += kScanThreads) before += npairs(off[e + 1] - off[e]);
+  int64_t base = 0;
+  if (b0) block_excl_scan(before, ws, &base);
+  if (b0 == 0 && threadIdx.x == 0) po[0] = 0;
+  scan_tile(off, po, b0, ne, base, true, c, ws);
 }
 
 __global__ __launch_bounds__(256) void k_validate_offsets(const int64_t* __restrict__ off, int64_t ne,
@@ -1774,8 +1804,8 @@ size_t event_reduce_bwd_lds_bytes(glv_dtype dt, const Tiling& t) {
 
 hipError_t launch_pair_offsets(int64_t ne, const int64_t* off, int64_t* po, hipStream_t s) {
   const int64_t ntiles = (ne + kScanTile - 1) / kScanTile;
-  if (ntiles == 0) {  // no events: pair_offsets = {0}
-    hipLaunchKernelGGL(k_po_scan_totals, dim3(1), dim3(1024), 0, s, po, ne, (int64_t)0);
+  if (ne <= kScanOnce) {  // also no events: pair_offsets = {0}
+    hipLaunchKernelGGL(k_po_once, dim3((unsigned)std::max<int64_t>(ntiles, 1)), dim3(kScanThreads), 0, s, off, po, ne);
     return hipGetLastError();
   }
   hipLaunchKernelGGL(k_po_tile_totals, dim3((unsigned)ntiles), dim3(kScanThreads), 0, s, off, po, ne);
