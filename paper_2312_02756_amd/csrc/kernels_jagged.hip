@@ -21,10 +21,10 @@
 // event, combined by the same scheme under a total order) instead of storing
 // pair masses.
 // The reverse mode stages one particle per thread of a workgroup (below).
-// An event with more particles than fit in LDS is left to a second, small
-// launch (k_event_reduce_big), where a whole workgroup takes it straight from
-// global memory (correct for any size, slower); on collider-sized events that
-// launch only reads the offsets.
+// Events of many particles, whose pairs are too many for one wavefront or
+// one workgroup's staging, are left to a second launch in either direction,
+// which shares all their pairs out evenly (k_event_dense, k_event_bwd_dense);
+// on collider-sized events it only reads the pair offsets.
 #include "glv_device.h"
 #include "glv_launch.h"
 
@@ -302,7 +302,7 @@ __device__ __forceinline__ T comp_pair(const LegC<T>& a, const LegC<T>& b, T ma,
 
 // Marks an event of the tiled FP32 compensated reduction that holds a pair
 // needing the FP64 redo: written to the event's mass (or, without event
-// masses, to its first pair mass) for k_event_reduce_big to find.  A quiet NaN
+// masses, to its first pair mass) for k_event_dense to find.  A quiet NaN
 // with a payload that arithmetic does not produce; should an input NaN carry
 // it, the event is merely recomputed.
 constexpr unsigned kRedoMarkBits = 0x7fd2e6b1u;
@@ -441,124 +441,10 @@ struct FwdArgs {
   int64_t ne;
   int epb;         // events per wavefront tile
   int cap;         // particles staged per chunk (per wavefront)
+  int small;       // events of more particles are left to the second launch (small <= cap)
   int qcap;        // pairs evaluated per round (per wavefront)
   int wave_bytes;  // LDS bytes per wavefront
 };
-
-// Lexicographic minimum of (distance bits, rank) over the workgroup, the mass
-// travelling with it; every thread receives the result.  `red` holds 48
-// bytes per wavefront, for at most four wavefronts (the 256-thread workgroups
-// of k_event_reduce_big; it is the 16-double scratch of block_sum, reused).
-template <typename T>
-__device__ __forceinline__ void block_best(unsigned long long* bd, int64_t* br, T* bm, double* red) {
-  auto take = [&](unsigned long long od, int64_t orr, T om) {
-    if (od < *bd || (od == *bd && orr < *br)) {
-      *bd = od;
-      *br = orr;
-      *bm = om;
-    }
-  };
-#pragma unroll
-  for (int d = 32; d > 0; d >>= 1)
-    take(__shfl_xor(*bd, d), __shfl_xor(*br, d), __shfl_xor(*bm, d));
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  unsigned long long* sd = reinterpret_cast<unsigned long long*>(red);
-  int64_t* sr = reinterpret_cast<int64_t*>(sd + 4);
-  double* sm = reinterpret_cast<double*>(sr + 4);
-  __syncthreads();
-  if (lane == 0) {
-    sd[wid] = *bd;
-    sr[wid] = *br;
-    sm[wid] = (double)*bm;
-  }
-  __syncthreads();
-  for (int w = 0; w < nw; ++w) take(sd[w], sr[w], (T)sm[w]);
-  __syncthreads();
-}
-
-// One event too large for LDS: the whole workgroup, from global memory.
-template <typename T, int COORDS, int MODE>
-__device__ void big_event(const FwdArgs<T, COORDS, MODE>& A, int64_t e, int64_t lo, int64_t hi, double* red,
-                          unsigned* fb, bool totals = true) {
-  const int64_t n = hi - lo;
-  double acc[4] = {0, 0, 0, 0};
-  double msum = 0.0;
-  for (int64_t i = lo + threadIdx.x; i < hi; i += blockDim.x) {
-    if (totals) {
-      T v[4];
-      to_cart<COORDS>(A.p.c[0][i], A.p.c[1][i], A.p.c[2][i], A.p.c[3][i], v);
-#pragma unroll
-      for (int k = 0; k < 4; ++k) acc[k] += (double)v[k];
-    }
-    if constexpr (MODE == GLV_COMPENSATED) msum += (double)A.p.c[3][i] * (double)A.p.c[3][i];
-  }
-  T tot[4] = {0, 0, 0, 0};
-  if (totals) {
-#pragma unroll
-    for (int k = 0; k < 4; ++k) tot[k] = (T)block_sum(acc[k], red);
-  }
-  if constexpr (MODE == GLV_COMPENSATED) msum = block_sum(msum, red);
-  double ksum = 0.0;
-  const bool want_k = (MODE == GLV_COMPENSATED) && A.event_m;
-  const bool want_best = A.best_rank != nullptr;
-  unsigned long long bd = ~0ull;  // this thread's best: distance bits, rank, mass
-  int64_t br = -1;
-  T bmass = T(0);
-  if (A.pair_m || want_k || want_best) {
-    const int64_t q = npairs(n);
-    const int64_t base = A.poff ? A.poff[e] : 0;
-    for (int64_t r = threadIdx.x; r < q; r += blockDim.x) {
-      int64_t i, j;
-      decode_pair(r, n, &i, &j);
-      i += lo;
-      j += lo;
-      T m;
-      if constexpr (MODE == GLV_COMPENSATED) {
-        T va[4], vb[4];  // the conversions are not needed here
-        LegC<T> a = comp_leg_cart<T>(A.p.c[0][i], A.p.c[1][i], A.p.c[2][i], A.p.c[3][i], va);
-        LegC<T> b = comp_leg_cart<T>(A.p.c[0][j], A.p.c[1][j], A.p.c[2][j], A.p.c[3][j], vb);
-        double kd;
-        m = comp_pair<T>(a, b, A.p.c[3][i], A.p.c[3][j], &kd, fb);
-        ksum += kd;
-      } else {
-        T va[4], vb[4], w[4];
-        to_cart<COORDS>(A.p.c[0][i], A.p.c[1][i], A.p.c[2][i], A.p.c[3][i], va);
-        to_cart<COORDS>(A.p.c[0][j], A.p.c[1][j], A.p.c[2][j], A.p.c[3][j], vb);
-        add4<T>(va, vb, w);
-        m = mass_of(w);
-      }
-      if (A.pair_m) store_out(A.pair_m, base + r, m);
-      if (want_best) {  // a thread's ranks only grow: a tie keeps the earlier one
-        const double d = fabs((double)m - A.target);
-        const unsigned long long b = (unsigned long long)__double_as_longlong(d);
-        if (d == d && b < bd) {
-          bd = b;
-          br = r;
-          bmass = m;
-        }
-      }
-    }
-    if (want_k) ksum = block_sum(ksum, red);
-    if (want_best) block_best<T>(&bd, &br, &bmass, red);
-  }
-  if (threadIdx.x == 0) {
-    if (want_best) {
-      A.best_rank[e] = bd != ~0ull ? br : -1;
-      A.best_m[e] = bd != ~0ull ? bmass : (T)__builtin_nan("");
-    }
-    if (totals && A.total[0]) {
-#pragma unroll
-      for (int k = 0; k < 4; ++k) A.total[k][e] = tot[k];
-    }
-    if (A.event_m) {
-      if constexpr (MODE == GLV_COMPENSATED)
-        A.event_m[e] = (T)sqrt(msum + 2.0 * ksum);
-      else
-        A.event_m[e] = mass_of(tot);
-    }
-  }
-  __syncthreads();
-}
 
 // Orders the LDS accesses of the lanes of one wavefront.  The waves of a
 // workgroup work independently, so the forward reduction needs no workgroup
@@ -713,19 +599,21 @@ __device__ __forceinline__ LegC<T> staged_leg(const typename V4<T>::type* q, T* 
 }
 
 // The chunk of a wavefront's tile that starts at the first event at or after
-// `from` small enough to stage (n <= cap): [*ca, *cb), the longest run of
-// consecutive events whose particles fit in cap slots and whose pairs number
-// at most pcap (the first event always belongs to it).  *ca = nev: none left.
+// `from` that belongs to this launch (n <= small): [*ca, *cb), the longest run
+// of consecutive such events whose particles fit in cap slots (small <= cap)
+// and whose pairs number at most pcap (the first event always belongs to it).
+// *ca = nev: none left.
 __device__ __forceinline__ void next_chunk(int from, int nev, uint64_t valid, bool mine, int64_t olo, int64_t ohi,
-                                           int cap, int64_t plo, int64_t phi, int64_t pcap, int* ca, int* cb) {
+                                           int cap, int small, int64_t plo, int64_t phi, int64_t pcap, int* ca,
+                                           int* cb) {
   const uint64_t after = from >= 64 ? 0ull : (valid & (~0ull << from));
-  const uint64_t small = __ballot(mine && (ohi - olo) <= (int64_t)cap) & after;
-  const int a = small ? (int)__builtin_ctzll(small) : nev;
+  const uint64_t ours = __ballot(mine && (ohi - olo) <= (int64_t)small);
+  const int a = (ours & after) ? (int)__builtin_ctzll(ours & after) : nev;
   int b = a;
   if (a < nev) {
     const int64_t base = readlane64(olo, a), pbase = readlane64(plo, a);
     const uint64_t ge = valid & (~0ull << a);
-    const uint64_t fits = __ballot(mine && (ohi - base <= (int64_t)cap) && (phi - pbase <= pcap)) & ge;
+    const uint64_t fits = __ballot(mine && (ohi - base <= (int64_t)cap) && (phi - pbase <= pcap)) & ours & ge;
     // the first event always opens the chunk (its pairs then take several rounds)
     const uint64_t stop = ge & ~fits & ~(1ull << a);
     b = stop ? (int)__builtin_ctzll(stop) : nev;
@@ -774,11 +662,11 @@ constexpr int fwd_waves() {
 //      scan of their tails (keyed by event over the lanes) plus the head of
 //      the run where it ends; the event's lane adds its K per round:
 //      deterministic for a tiling.
-// Events with more than cap particles are left to k_event_reduce_big.  In
+// Events with more than `small` particles are left to k_event_dense.  In
 // the FP32 compensated mode a pair whose error bound asks for FP64 makes its
 // K a NaN; the event's lane then writes a marker -- a quiet NaN with a fixed
 // payload -- into the event mass (or, without event masses, into the event's
-// first pair mass), and k_event_reduce_big recomputes the event.
+// first pair mass), and k_event_dense recomputes the event.
 template <typename T, int COORDS, int MODE, bool BEST>
 __global__ __launch_bounds__(kMaxBlock, (fwd_waves<T, MODE, BEST>())) void k_event_reduce(FwdArgs<T, COORDS, MODE> A) {
   extern __shared__ __align__(32) unsigned char lds[];
@@ -822,7 +710,7 @@ __global__ __launch_bounds__(kMaxBlock, (fwd_waves<T, MODE, BEST>())) void k_eve
   unsigned fb = 0;
 
   int ca, cb;
-  next_chunk(0, nev, valid, mine, olo, ohi, cap, plo, phi, pcap, &ca, &cb);
+  next_chunk(0, nev, valid, mine, olo, ohi, cap, A.small, plo, phi, pcap, &ca, &cb);
   Prefetch<T> pre;
   if (ca < nev) {
     const int64_t b0 = readlane64(olo, ca);
@@ -870,7 +758,7 @@ __global__ __launch_bounds__(kMaxBlock, (fwd_waves<T, MODE, BEST>())) void k_eve
 
     // the next chunk's particles into registers, in flight from here on
     int na, nb;
-    next_chunk(cb, nev, valid, mine, olo, ohi, cap, plo, phi, pcap, &na, &nb);
+    next_chunk(cb, nev, valid, mine, olo, ohi, cap, A.small, plo, phi, pcap, &na, &nb);
     if (na < nev) {
       const int64_t b1 = readlane64(olo, na);
       prefetch_chunk(A.p, b1, (int)(readlane64(ohi, nb - 1) - b1), lane, &pre);
@@ -1183,20 +1071,664 @@ __global__ __launch_bounds__(kMaxBlock, (fwd_waves<T, MODE, BEST>())) void k_eve
   }
 }
 
-// Events of more than cap particles, which k_event_reduce leaves out: the
-// workgroup scans the offsets for them and takes each one whole, from global
-// memory.  A separate launch, so that this rare path does not set the main
-// kernel's register budget; on collider-sized events it only reads the offsets.
-// In the FP32 compensated mode the same scan finds the events k_event_reduce
-// marked for the FP64 redo (a mark in the event mass, or in the first pair
-// mass without event masses) and recomputes their pair masses and event mass
-// with the redo, counting the redone pairs; their totals stay as computed.
+// ------------------------------------- forward, events of many particles
+//
+// Events of more than `small` particles, which k_event_reduce leaves out.
+// Two launches share the work by events' pairs, so that neither a few large
+// events nor a few events in all leave the chip idle:
+//   * plain pair masses: the pairs of all events (pair_offsets is their scan)
+//     are cut into equal runs, one per workgroup, an event's pairs falling
+//     to as many workgroups as its size asks for;
+//   * K sums (compensated event mass) and the best pair need one result per
+//     event: a workgroup takes every event whose first pair lies in its run.
+// A workgroup finds its first event by a 256-ary search of pair_offsets, reads
+// the sizes of blockDim events at a time and lists the ones that are its
+// business.  It stages runs of listed events (kDenseCap particles) in LDS,
+// converted once per workgroup, and deals the staged events' pairs to its
+// wavefronts as equal contiguous runs; a wavefront walks its run 64
+// consecutive pairs per step, so that the masses go out as whole cache lines
+// straight from registers, and a lane's step is j += 64 followed by one
+// subtraction per row end it passes.  What bounds it: the stores of the pair
+// masses in FP32 and FP64, and VALU issue in the compensated mode.
+// An event that does not fit kDenseCap slots is walked in tiles of
+// kDenseCap / 2 rows by kDenseCap / 2 columns, one row per wavefront.
+
+// Particles staged per chunk (LDS: 16 KB of records in FP64, 48 KB with the
+// legs of the FP32 ... compensated mode).
+template <typename T, int MODE>
+constexpr int dense_cap() {
+  return (MODE == GLV_COMPENSATED && sizeof(T) == 8) ? 256 : 512;
+}
+constexpr int kDenseEvents = 64;  // events per chunk (one lane each)
+constexpr int kDenseMinPairs = 2048;  // pairs a workgroup takes at least
+// Events of more particles take this path where pairs are evaluated.
+constexpr int kDenseFrom = 48;
+
+template <int MODE, bool BEST>
+constexpr bool dense_owned() {  // events stay with one workgroup
+  return MODE == GLV_COMPENSATED || BEST;
+}
+template <int MODE, bool BEST>
+constexpr int dense_block() {
+  return dense_owned<MODE, BEST>() ? 512 : 256;
+}
+
+// Workgroups of the large-event launches: what the GPU holds at once (four of
+// 256 threads or two of 512 per CU), so that on small events, where they only
+// read the offsets, they take one round.
+template <int MODE, bool BEST>
+constexpr int dense_grid() {
+  return dense_owned<MODE, BEST>() ? 512 : 1024;
+}
+
+// The events a workgroup of the large-event launches has to do among B
+// consecutive ones: first particle, size, first pair, and 2 (index in the
+// slice) + flag.
+template <int B>
+struct EventList {
+  int64_t lo[B], po[B];
+  int n[B], e[B];
+  int cnt[B / 64];
+};
+
+// Lists the threads' events with `mine`, in order; returns their number.
+template <int B>
+__device__ __forceinline__ int list_events(EventList<B>& L, bool mine, int64_t lo, int n, int64_t po, bool flag) {
+  const int lane = (int)threadIdx.x & 63, wid = (int)threadIdx.x >> 6;
+  const uint64_t mk = __ballot(mine);
+  __syncthreads();  // the previous list is no longer read
+  if (lane == 0) L.cnt[wid] = __builtin_popcountll(mk);
+  __syncthreads();
+  int at = 0, all = 0;
+#pragma unroll
+  for (int w = 0; w < B / 64; ++w) {
+    const int c = L.cnt[w];
+    at += w < wid ? c : 0;
+    all += c;
+  }
+  if (mine) {
+    at += __builtin_popcountll(mk & ((1ull << lane) - 1));
+    L.lo[at] = lo;
+    L.n[at] = n;
+    L.po[at] = po;
+    L.e[at] = ((int)threadIdx.x << 1) | (flag ? 1 : 0);
+  }
+  __syncthreads();
+  return __builtin_amdgcn_readfirstlane(all);
+}
+
+// The share of the calling workgroup in the large-event launches: the pairs of
+// all events, whose scan is pair_offsets, cut into one equal run [q0, q1) per
+// workgroup, of at least min_pairs.  Neighbouring runs go to workgroups of the
+// same XCD (dispatched round-robin over the eight), whose L2 then serves the
+// pair offsets both read.  From kShareByEvents events on, hundreds per
+// workgroup, equal numbers of events are equal work enough, and every pair
+// offset is read once (7.0 us against 4.6 on 2^20 small events).
+struct Share {
+  int64_t q0, q1;
+};
+__device__ __forceinline__ int share_index() {  // the grid is a multiple of 8
+  return (int)((blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3));
+}
+__device__ __forceinline__ Share my_share(int64_t nq, int64_t min_pairs) {
+  const int64_t grid = gridDim.x, b = share_index();
+  const int64_t per = max((nq + grid - 1) / grid, min_pairs);
+  return {min(b * per, nq), min((b + 1) * per, nq)};
+}
+
+constexpr int64_t kShareByEvents = 1 << 18;
+
+// An event e with poff[e] <= q at most `within` events before the last such
+// one, by probing 1024 evenly spread pair offsets per round.
+template <int B>
+__device__ __forceinline__ int64_t search_share(const int64_t* __restrict__ poff, int64_t ne, int64_t q,
+                                                int64_t within, int* cnt) {
+  constexpr int kProbes = 1024 / B;
+  const int tid = (int)threadIdx.x;
+  int64_t lo = 0, hi = ne;
+  while (hi - lo > within) {
+    const int64_t step = (hi - lo + 1023) >> 10;
+    int c = 0;
+#pragma unroll
+    for (int k = 0; k < kProbes; ++k) {
+      const int64_t at = lo + step * (tid + B * k);
+      c += __builtin_popcountll(__ballot(at < hi && poff[min(at, ne)] <= q));
+    }
+    __syncthreads();
+    if ((tid & 63) == 0) cnt[tid >> 6] = c;
+    __syncthreads();
+    c = 0;
+#pragma unroll
+    for (int w = 0; w < B / 64; ++w) c += cnt[w];
+    const int64_t top = lo + step * __builtin_amdgcn_readfirstlane(c);  // c >= 1: poff[lo] <= q
+    lo = top - step;
+    hi = min(hi, top);
+  }
+  return lo;
+}
+
+// Calls body(win, listed) with the whole workgroup for every slice of B events
+// from event win on that has events e with pick(peek(e), po, d) in its share
+// (first pair po, d pairs; peek reads what else tells), listed in L in order
+// with flag(d).  The pair offsets of kSlices slices are read at once, first
+// around the place where the share would begin if all events had the same
+// number of pairs (sizes drawn alike stay within the slack of about 1000
+// events either way for a million events), so that where no event is the
+// workgroup's business, as on small events, the scan costs one memory
+// latency; a share that begins outside is searched for.
+template <int B, typename Peek, typename Pick, typename Flag, typename Body>
+__device__ __forceinline__ void scan_share(const int64_t* __restrict__ off, const int64_t* __restrict__ poff,
+                                           int64_t ne, int64_t min_pairs, EventList<B>& L, Share* share, Peek peek,
+                                           Pick pick, Flag flag, Body body) {
+  constexpr int kSlices = B == 256 ? 12 : 8;
+  constexpr int64_t kWin = (int64_t)kSlices * B;
+  const int tid = (int)threadIdx.x;
+  int64_t wins, stop;  // events still to look at
+  bool placed, more = true;
+  if (ne >= kShareByEvents) {
+    const int64_t per = (ne + gridDim.x - 1) / (int64_t)gridDim.x;
+    wins = share_index() * per;
+    stop = min(wins + per, ne);
+    if (wins >= stop) return;
+    *share = {0, INT64_MAX};
+    placed = true;
+  } else {
+    // where equal events would put the share, if it is no smaller than the rest
+    wins = (int64_t)((double)ne * share_index() / (double)gridDim.x) - (kWin - ne / (int64_t)gridDim.x) / 2;
+    wins = max((int64_t)0, min(wins, ne - kWin));
+    stop = ne;
+    placed = false;
+  }
+  while (more) {
+    const int64_t wend = min(wins + kWin, stop);
+    const int64_t at0 = poff[wins], at1 = poff[wend], nq = poff[ne];
+    unsigned some = 0;  // bit s: this thread's event of slice s
+    {
+      // the low words do where the slices hold fewer than 2^32 pairs (half
+      // the registers); the list below looks at the whole offsets
+      const unsigned* const low = reinterpret_cast<const unsigned*>(poff + wins);
+      const int last = (int)(wend - wins) - 1;
+      unsigned po[kSlices], pe[kSlices];
+      decltype(peek(wins)) seen[kSlices];
+#pragma unroll
+      for (int sl = 0; sl < kSlices; ++sl) {
+        const int t = min(sl * B + tid, last);
+        po[sl] = low[2 * t];
+        pe[sl] = low[2 * t + 2];
+        seen[sl] = peek(wins + t);
+      }
+      if (!placed) {
+        placed = true;
+        *share = my_share(nq, min_pairs);
+        if (share->q0 >= share->q1) return;
+        if (at0 > share->q0 || at1 <= share->q0) {
+          wins = search_share<B>(poff, ne, share->q0, kWin / 4, L.cnt);
+          continue;
+        }
+      }
+      more = wend < stop && at1 < share->q1;
+      const bool wide = at1 - at0 >= ((int64_t)1 << 32);
+#pragma unroll
+      for (int sl = 0; sl < kSlices; ++sl) {
+        const int t = sl * B + tid;
+        const int64_t at = at0 + (unsigned)(po[sl] - (unsigned)at0);
+        if (t <= last && (wide || (at < share->q1 && pick(seen[sl], at, (int64_t)(unsigned)(pe[sl] - po[sl])))))
+          some |= 1u << sl;
+      }
+    }
+    if (__syncthreads_or(some != 0)) {
+#pragma unroll 1
+      for (int sl = 0; sl < kSlices; ++sl) {
+        bool mine = (some >> sl) & 1u;
+        if (!__syncthreads_or(mine)) continue;
+        const int64_t e = wins + sl * B + tid;
+        int64_t first = 0, n = 0, po = 0, d = 0;
+        if (mine) {
+          first = off[e];
+          n = off[e + 1] - first;
+          po = poff[e];
+          d = npairs(n);
+          mine = po < share->q1 && pick(peek(e), po, d);
+        }
+        const int listed = list_events<B>(L, mine, first, (int)n, po, mine && flag(d));
+        body(wins + sl * B, listed);
+      }
+    }
+    wins += kWin;
+  }
+}
+
+// Inclusive sum over the lanes at or below this one.
+__device__ __forceinline__ int wave_incl_sum(int x, int lane) {
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const int y = __shfl_up(x, d);
+    if (lane >= d) x += y;
+  }
+  return x;
+}
+
+__device__ __forceinline__ double wave_sum(double v) {
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d);
+  return v;
+}
+
+// Sum over the wavefront by lane moves: rows of 16 lanes, then across rows.
+__device__ __forceinline__ double wave_total(double v) {
+  v += dpp_f64<kDppRowShr + 1, 0xf>(v);
+  v += dpp_f64<kDppRowShr + 2, 0xf>(v);
+  v += dpp_f64<kDppRowShr + 4, 0xf>(v);
+  v += dpp_f64<kDppRowShr + 8, 0xf>(v);
+  v += dpp_f64<kDppRowBcast15, 0xa>(v);
+  v += dpp_f64<kDppRowBcast31, 0xc>(v);
+  return __builtin_bit_cast(double, readlane64(__builtin_bit_cast(int64_t, v), 63));
+}
+
+// A best-pair candidate by the bits of its distance (which order as unsigned
+// integers; ~0: none), then its rank.
+template <typename T, typename R>
+struct Cand {
+  unsigned long long d;
+  R r;
+  T m;
+  __device__ __forceinline__ void offer(unsigned long long od, R orr, T om) {
+    if (od < d || (od == d && orr < r)) {
+      d = od;
+      r = orr;
+      m = om;
+    }
+  }
+};
+
+template <typename T, typename R>
+__device__ __forceinline__ void wave_best(Cand<T, R>& c) {
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) {
+    const unsigned long long od = __shfl_xor(c.d, d);
+    const R orr = __shfl_xor(c.r, d);
+    const T om = __shfl_xor(c.m, d);
+    c.offer(od, orr, om);
+  }
+}
+
+// Total (and sum of M^2) of a staged event of more than kQuadMax particles,
+// by one wavefront: 256 strided partial sums, a butterfly per 64 of them, the
+// four results added in order.
+constexpr int kQuadMax = 128;
+template <typename V>
+__device__ __forceinline__ void tree_sum(const V* rec, int n, int lane, double tot[4], const V* legs, double* m2) {
+#pragma unroll 1
+  for (int w = 0; w < 4; ++w) {
+    double acc[4] = {0, 0, 0, 0}, ms = 0.0;
+    for (int t = w * 64 + lane; t < n; t += 256) {
+      const V r = rec[t];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) acc[k] += (double)r[k];
+      if (legs) {
+        const double m = (double)legs[2 * t][3];
+        ms += m * m;
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) tot[k] += wave_sum(acc[k]);
+    if (legs) *m2 += wave_sum(ms);
+  }
+}
+
+template <typename T, int COORDS, int MODE, bool BEST>
+__global__ __launch_bounds__((dense_block<MODE, BEST>()), 4) void k_event_dense(FwdArgs<T, COORDS, MODE> A) {
+  constexpr bool kComp = MODE == GLV_COMPENSATED;
+  constexpr bool kDefer = kComp && sizeof(T) == 4;
+  constexpr bool kOwn = dense_owned<MODE, BEST>();
+  constexpr int B = dense_block<MODE, BEST>();
+  constexpr int NW = B / 64;
+  constexpr int kCap = dense_cap<T, MODE>();
+  constexpr int kHalf = kCap / 2;
+  using R4 = typename V4<T>::type;
+  __shared__ R4 cart[kCap];
+  __shared__ R4 leg[kComp ? 2 * kCap : 1];
+  __shared__ EventList<B> L;                               // flag: redo only
+  __shared__ double kpart[kComp ? NW * kDenseEvents : 1];  // K of an event from each wavefront
+  __shared__ double kmsum[kComp ? kDenseEvents : 1];       // an event's sum of M^2
+  __shared__ unsigned long long bd[BEST ? NW * kDenseEvents : 1];  // best pair from each wavefront
+  __shared__ int64_t br[BEST ? NW * kDenseEvents : 1];
+  __shared__ T bm[BEST ? NW * kDenseEvents : 1];
+  __shared__ double red[16];
+  const int tid = (int)threadIdx.x, lane = tid & 63;
+  const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+  const bool want_pairs = !BEST && A.pair_m != nullptr;
+  const bool want_k = kComp && A.event_m != nullptr;
+  const bool want_sums = A.total[0] != nullptr || A.event_m != nullptr;
+  unsigned fb = 0;
+
+  // mass of the pair of staged particles i, j
+  auto pair_of = [&](int i, int j, double* kd) -> T {
+    if constexpr (kComp) {
+      T ma, mb;
+      const LegC<T> la = staged_leg<T>(leg + 2 * i, &ma), lb = staged_leg<T>(leg + 2 * j, &mb);
+      return comp_pair<T>(la, lb, ma, mb, kd, &fb);
+    } else {
+      const R4 a = cart[i], b = cart[j];
+      T w[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) w[k] = a[k] + b[k];
+      return mass_of(w);
+    }
+  };
+  auto stage = [&](int slot, int64_t gi) {
+    T v[4];
+    const T c0 = A.p.c[0][gi], c1 = A.p.c[1][gi], c2 = A.p.c[2][gi], c3 = A.p.c[3][gi];
+    if constexpr (kComp) {
+      const LegC<T> L = comp_leg_cart<T>(c0, c1, c2, c3, v);
+      leg[2 * slot] = R4{c0, c1, c2, c3};
+      leg[2 * slot + 1] = R4{L.mt, L.delta, L.dmt, L.m2};
+    } else {
+      to_cart<COORDS, T, true>(c0, c1, c2, c3, v);
+    }
+    cart[slot] = R4{v[0], v[1], v[2], v[3]};
+  };
+  auto finish_total = [&](int64_t e, const double* tot) {
+    T tt[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) tt[k] = (T)tot[k];
+    if (A.total[0]) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) A.total[k][e] = tt[k];
+    }
+    if constexpr (!kComp) {
+      if (A.event_m) A.event_m[e] = mass_of(tt);
+    }
+  };
+  auto offer = [&](auto& c, T m, auto r) {
+    const double d = fabs((double)m - A.target);
+    if (d == d) c.offer((unsigned long long)__double_as_longlong(d), r, m);
+  };
+
+  Share sh;
+  const int64_t small_pairs = npairs(A.small);
+  // the event's place for a redo mark (without event masses or best pairs: its first pair mass)
+  auto peek = [&](int64_t e) -> float {
+    if constexpr (kDefer) {
+      if (A.event_m) return A.event_m[e];
+      if (BEST) return A.best_m[e];
+    }
+    return 0.0f;
+  };
+  // whether an event (first pair po, d pairs) is this workgroup's business
+  auto picked = [&](float seen, int64_t po, int64_t d) -> bool {
+    if (kOwn ? po < sh.q0 : po + d <= sh.q0) return false;
+    if constexpr (kDefer) {
+      if (d > 0 && d <= small_pairs) {
+        if (!A.event_m && !BEST) return is_redo_mark(A.pair_m[po]);
+        return is_redo_mark(seen);
+      }
+    }
+    return d > small_pairs;
+  };
+  auto redo_only = [&](int64_t d) { return d <= small_pairs; };
+
+  scan_share<B>(A.off, A.poff, A.ne, kDenseMinPairs, L, &sh, peek, picked, redo_only, [&](int64_t win, int total_listed) {
+    const int64_t q0 = sh.q0, q1 = sh.q1;
+    for (int li = 0; li < total_listed;) {
+      // chunk: one lane per event from li on (each wavefront forms it alike)
+      const bool have = li + lane < total_listed;
+      int64_t clo = 0, cpo = 0;
+      int cn = 0, ce = 0;
+      if (have) {
+        clo = L.lo[li + lane];
+        cn = L.n[li + lane];
+        cpo = L.po[li + lane];
+        ce = L.e[li + lane];
+      }
+      const int cn32 = min(cn, kCap + 1);
+      const int incl = wave_incl_sum(cn32, lane);
+      const int nc = __builtin_popcountll(__ballot(have && incl <= kCap));
+      if (nc == 0) {
+        // one event of more than kCap particles, in tiles
+        const int64_t hlo = L.lo[li], hn = L.n[li], hpo = L.po[li], he = win + (L.e[li] >> 1);
+        const int64_t hq = npairs(hn);
+        const int64_t r0 = kOwn ? 0 : max((int64_t)0, q0 - hpo), r1 = kOwn ? hq : min(hq, q1 - hpo);
+        double msum = 0.0;
+        if (r0 == 0 && want_sums) {  // 256 strided partial sums, as tree_sum
+          double acc[4] = {0, 0, 0, 0}, ms = 0.0;
+          if (tid < 256) {
+            for (int64_t i = hlo + tid; i < hlo + hn; i += 256) {
+              T v[4];
+              to_cart<COORDS, T, true>(A.p.c[0][i], A.p.c[1][i], A.p.c[2][i], A.p.c[3][i], v);
+#pragma unroll
+              for (int k = 0; k < 4; ++k) acc[k] += (double)v[k];
+              if constexpr (kComp) ms += (double)A.p.c[3][i] * (double)A.p.c[3][i];
+            }
+          }
+#pragma unroll
+          for (int k = 0; k < 4; ++k) acc[k] = block_sum(acc[k], red);
+          if constexpr (kComp) msum = block_sum(ms, red);
+          if (tid == 0) finish_total(he, acc);
+        }
+        int64_t i0, i1, jt;
+        decode_pair(r0, hn, &i0, &jt);
+        decode_pair(r1 - 1, hn, &i1, &jt);
+        double kacc = 0.0;
+        Cand<T, int64_t> best{~0ull, 0, T(0)};
+        T* const pout = want_pairs ? A.pair_m + hpo : nullptr;
+        for (int64_t ta = i0; ta <= i1; ta += kHalf) {
+          const int64_t tae = min(i1 + 1, ta + kHalf);  // rows [ta, tae)
+          for (int64_t tb = ta + 1; tb < hn; tb += kHalf) {
+            const int64_t tbe = min(hn, tb + kHalf);  // columns [tb, tbe)
+            __syncthreads();
+            for (int t = tid; t < kCap; t += B) {
+              const int64_t g = t < kHalf ? ta + t : tb + (t - kHalf);
+              if (g < (t < kHalf ? tae : tbe)) stage(t, hlo + g);
+            }
+            __syncthreads();
+            for (int64_t i = ta + wid; i < tae; i += NW) {
+              const int64_t rs = row_start(i, hn) - i - 1;  // rank of (i, j) is rs + j
+              const int64_t jb = max(max(tb, i + 1), r0 - rs), je = min(tbe, r1 - rs);
+              for (int64_t j = jb + lane; j < je; j += 64) {
+                double kd;
+                const T m = pair_of((int)(i - ta), kHalf + (int)(j - tb), &kd);
+                if constexpr (kComp) kacc += kd;
+                if (want_pairs) store_out(pout, rs + j, m);
+                if constexpr (BEST) offer(best, m, rs + j);
+              }
+            }
+          }
+        }
+        if constexpr (kComp) {
+          if (want_k) {
+            kacc = block_sum(kacc, red);
+            if (tid == 0) A.event_m[he] = (T)sqrt(msum + 2.0 * kacc);
+          }
+        }
+        if constexpr (BEST) {
+          wave_best(best);
+          __syncthreads();
+          if (lane == 0) {
+            bd[wid] = best.d;
+            br[wid] = best.r;
+            bm[wid] = best.m;
+          }
+          __syncthreads();
+          if (tid == 0) {
+            for (int w = 1; w < NW; ++w) best.offer(bd[w], br[w], bm[w]);
+            const bool found = best.d != ~0ull;
+            A.best_rank[he] = found ? best.r : -1;
+            A.best_m[he] = found ? best.m : (T)__builtin_nan("");
+          }
+        }
+        __syncthreads();
+        ++li;
+        continue;
+      }
+      const bool in = lane < nc;
+      const int slot0 = in ? incl - cn32 : kCap;  // first slot of this lane's event
+      const int np = __shfl(incl, nc - 1);
+      int r0 = 0, cq = 0;  // the event's first rank and number of pairs here
+      if (in) {
+        const int q = (int)npairs(cn);
+        const int64_t a = kOwn ? 0 : max((int64_t)0, q0 - cpo), b = kOwn ? q : min((int64_t)q, q1 - cpo);
+        r0 = (int)a;
+        cq = (int)(b - a);
+      }
+      const int qincl = wave_incl_sum(cq, lane);
+      const int p0 = in ? qincl - cq : 0x7fffffff;  // first pair of this lane's event in the chunk
+      const int ptot = __shfl(qincl, nc - 1);
+
+      // stage: each slot's event by a binary search over the lanes' first slots
+      for (int t0 = 0; t0 < np; t0 += B) {
+        const int t = t0 + tid;
+        int c = 0;
+#pragma unroll
+        for (int d = kDenseEvents / 2; d > 0; d >>= 1) {
+          const int s = __shfl(slot0, c + d);
+          c = s <= t ? c + d : c;
+        }
+        const int64_t plo = __shfl(clo, c);
+        const int ps = __shfl(slot0, c);
+        if (t < np) stage(t, plo + (t - ps));
+      }
+      if constexpr (kComp) {
+        for (int t = tid; t < NW * kDenseEvents; t += B) kpart[t] = 0.0;
+      }
+      if constexpr (BEST) {
+        for (int t = tid; t < NW * kDenseEvents; t += B) bd[t] = ~0ull;
+      }
+      __syncthreads();
+
+      // totals: events of at most kQuadMax particles by a quad of lanes, 16
+      // events per wavefront, the others by one wavefront each
+      if (want_sums) {
+        const R4* legs = nullptr;
+        if constexpr (kComp) legs = leg;
+        for (int c0 = wid * 16; c0 < nc; c0 += NW * 16) {
+          const int c = c0 + (lane >> 2), src = min(c, 63);
+          const int s0 = __shfl(slot0, src), n0 = __shfl(cn32, src), rr0 = __shfl(r0, src), e0 = __shfl(ce, src);
+          const bool act = c < nc && n0 <= kQuadMax && rr0 == 0;
+          double tot[4] = {0, 0, 0, 0}, ms = 0.0;
+          residue_sum(cart, act ? s0 : 0, act ? s0 + n0 : 0, lane & 3, tot, legs, &ms);
+#pragma unroll
+          for (int k = 0; k < 4; ++k) tot[k] = tot[k] + dpp_f64<kDppQuadXor1, 0xf>(tot[k]);
+#pragma unroll
+          for (int k = 0; k < 4; ++k) tot[k] = tot[k] + dpp_f64<kDppQuadXor2, 0xf>(tot[k]);
+          if constexpr (kComp) {
+            ms = ms + dpp_f64<kDppQuadXor1, 0xf>(ms);
+            ms = ms + dpp_f64<kDppQuadXor2, 0xf>(ms);
+          }
+          if (act && (lane & 3) == 0) {
+            if constexpr (kComp) kmsum[c] = ms;
+            if (!(e0 & 1)) finish_total(win + (e0 >> 1), tot);
+          }
+        }
+        uint64_t wide = __ballot(in && cn32 > kQuadMax && r0 == 0);
+        for (int turn = 0; wide; ++turn, wide &= wide - 1) {
+          if (turn % NW != wid) continue;
+          const int c = (int)__builtin_ctzll(wide);
+          const int s0 = __builtin_amdgcn_readlane(slot0, c), n0 = __builtin_amdgcn_readlane(cn32, c);
+          const int e0 = __builtin_amdgcn_readlane(ce, c);
+          double tot[4] = {0, 0, 0, 0}, ms = 0.0;
+          tree_sum(cart + s0, n0, lane, tot, legs ? legs + 2 * s0 : legs, &ms);
+          if (lane == 0) {
+            if constexpr (kComp) kmsum[c] = ms;
+            if (!(e0 & 1)) finish_total(win + (e0 >> 1), tot);
+          }
+        }
+      }
+
+      // pairs: each wavefront a contiguous run of the chunk's, whole steps of
+      // 64 but for the last
+      const int share = ((ptot + B - 1) / B) * 64;
+      const int ka = wid * share, kb = min(ka + share, ptot);
+      for (int c = (int)__builtin_popcountll(__ballot(p0 <= ka)) - 1, k = ka; k < kb; ++c) {
+        const int s0 = __builtin_amdgcn_readlane(slot0, c), n0 = __builtin_amdgcn_readlane(cn32, c);
+        const int pb = __builtin_amdgcn_readlane(p0, c);
+        const int rb = __builtin_amdgcn_readlane(r0, c);
+        const int ke = min(kb, pb + __builtin_amdgcn_readlane(cq, c));
+        T* const pout = want_pairs ? A.pair_m + readlane64(cpo, c) : nullptr;
+        double kacc = 0.0;
+        Cand<T, int> best{~0ull, 0, T(0)};
+        int r = rb + (k - pb) + lane;
+        const int re = rb + (ke - pb);
+        if (r < re) {
+          int i, j;
+          decode_pair_small(r, n0, &i, &j);
+          for (; r < re; r += 64) {
+            double kd;
+            const T m = pair_of(s0 + i, s0 + j, &kd);
+            if constexpr (kComp) kacc += kd;
+            if (want_pairs)  // a 32-bit offset: at most kCap particles
+              store_out(reinterpret_cast<T*>(reinterpret_cast<char*>(pout) + (unsigned)r * (unsigned)sizeof(T)), 0, m);
+            if constexpr (BEST) offer(best, m, r);
+            j += 64;
+            while (j >= n0) {  // past the row's end: the next row starts one column later
+              ++i;
+              j += i + 1 - n0;
+              if (i >= n0 - 1) break;  // past the last pair: the loop ends here
+            }
+          }
+        }
+        if constexpr (kComp) {
+          if (want_k) {
+            kacc = wave_sum(kacc);
+            if (lane == 0) kpart[wid * kDenseEvents + c] = kacc;
+          }
+        }
+        if constexpr (BEST) {
+          wave_best(best);
+          if (lane == 0) {
+            bd[wid * kDenseEvents + c] = best.d;
+            br[wid * kDenseEvents + c] = best.r;
+            bm[wid * kDenseEvents + c] = best.m;
+          }
+        }
+        k = ke;
+      }
+      __syncthreads();
+      if constexpr (kOwn) {
+        if (wid == 0 && in) {
+          const int64_t ev = win + (ce >> 1);
+          if constexpr (kComp) {
+            if (want_k) {
+              double ks = 0.0;
+              for (int w = 0; w < NW; ++w) ks += kpart[w * kDenseEvents + lane];
+              A.event_m[ev] = (T)sqrt(kmsum[lane] + 2.0 * ks);
+            }
+          }
+          if constexpr (BEST) {
+            Cand<T, int64_t> best{~0ull, 0, T(0)};
+            for (int w = 0; w < NW; ++w) {
+              const int t = w * kDenseEvents + lane;
+              if (bd[t] != ~0ull) best.offer(bd[t], br[t], bm[t]);
+            }
+            const bool found = best.d != ~0ull;
+            A.best_rank[ev] = found ? best.r : -1;
+            A.best_m[ev] = found ? best.m : (T)__builtin_nan("");
+          }
+        }
+        __syncthreads();  // kpart, kmsum and the candidates are free again
+      }
+      li += nc;
+    }
+  });
+  if constexpr (kDefer) {
+    if (A.fallback) {
+#pragma unroll
+      for (int d = 32; d > 0; d >>= 1) fb += __shfl_xor(fb, d);
+      if (lane == 0 && fb) atomicAdd(A.fallback, (unsigned long long)fb);
+    }
+  }
+}
+
+// Without pairs to evaluate (no pair offsets then), the events of more than
+// cap particles: the workgroup scans the offsets for them and sums each one
+// whole, from global memory; on collider-sized events it only reads the
+// offsets.
 constexpr int kBigBlock = 256;
-// Events each thread of the second launch sizes per pass (kBigScan coalesced
-// slices of kBigBlock events): all their offsets are read at once, so the
-// scan of 2^20 events takes one or two memory latencies per workgroup with a
-// grid that fits the GPU (it took several rounds at one event per thread;
-// four slices measured 1-2 % faster in the calls than eight or sixteen).
+// Events each thread sizes per pass (kBigScan coalesced slices of kBigBlock
+// events): all their offsets are read at once, so the scan of 2^20 events
+// takes one or two memory latencies per workgroup with a grid that fits the
+// GPU.
 constexpr int kBigScan = 4;
 
 // Sizes of events base + k kBigBlock + threadIdx.x, k < kBigScan, or -1 past
@@ -1217,60 +1749,57 @@ __device__ __forceinline__ void scan_sizes(const int64_t* off, int64_t ne, int64
   for (int k = 0; k < kBigScan; ++k) n[k] = hi[k] - lo[k];
 }
 
-template <typename T, int COORDS, int MODE>
-__global__ __launch_bounds__(kBigBlock) void k_event_reduce_big(FwdArgs<T, COORDS, MODE> A) {
-  constexpr bool kDefer = (MODE == GLV_COMPENSATED) && (sizeof(T) == 4);
-  __shared__ double red[16];
-  __shared__ int64_t list[kBigBlock];  // event << 1 | (1: redo only)
+// Calls event(e) with the whole workgroup for every event with picked(n).
+template <typename Pick, typename Event>
+__device__ __forceinline__ void scan_events(const int64_t* off, int64_t ne, Pick picked, Event event) {
+  __shared__ int64_t list[kBigBlock];
   __shared__ int count;
-  unsigned fb = 0;
   const int64_t step = (int64_t)gridDim.x * kBigBlock * kBigScan;
-  for (int64_t base = (int64_t)blockIdx.x * kBigBlock * kBigScan; base < A.ne; base += step) {
-    // kBigScan coalesced slices of kBigBlock events, all offsets in flight at once
+  for (int64_t base = (int64_t)blockIdx.x * kBigBlock * kBigScan; base < ne; base += step) {
     int64_t n[kBigScan];
-    scan_sizes(A.off, A.ne, base, n);
-    unsigned bigm = 0, redom = 0;  // bit k: event k of this thread
+    scan_sizes(off, ne, base, n);
+    unsigned bigm = 0;  // bit k: event k of this thread
 #pragma unroll
-    for (int k = 0; k < kBigScan; ++k) {
-      if (n[k] > A.cap) bigm |= 1u << k;
-      if constexpr (kDefer) {
-        const int64_t e = base + k * kBigBlock + threadIdx.x;
-        bool redo = false;
-        if (n[k] >= 2 && n[k] <= A.cap) {
-          if (A.event_m)
-            redo = is_redo_mark(A.event_m[e]);
-          else if (A.best_m)
-            redo = is_redo_mark(A.best_m[e]);
-          else if (A.pair_m)
-            redo = is_redo_mark(A.pair_m[A.poff[e]]);
-        }
-        if (redo) redom |= 1u << k;
-      }
-    }
+    for (int k = 0; k < kBigScan; ++k)
+      if (n[k] >= 0 && picked(n[k])) bigm |= 1u << k;
 #pragma unroll 1
     for (int k = 0; k < kBigScan; ++k) {
-      const int64_t e = base + k * kBigBlock + threadIdx.x;
-      const bool big = (bigm >> k) & 1u, redo = (redom >> k) & 1u;
-      if (!__syncthreads_or(big || redo)) continue;
+      const bool big = (bigm >> k) & 1u;
+      if (!__syncthreads_or(big)) continue;
       if (threadIdx.x == 0) count = 0;
       __syncthreads();
-      if (big || redo) list[atomicAdd(&count, 1)] = (e << 1) | (redo ? 1 : 0);
+      if (big) list[atomicAdd(&count, 1)] = base + k * kBigBlock + threadIdx.x;
       __syncthreads();
       const int nbig = count;
-      for (int b = 0; b < nbig; ++b) {
-        const int64_t eb = list[b] >> 1;
-        big_event<T, COORDS, MODE>(A, eb, A.off[eb], A.off[eb + 1], red, &fb, (list[b] & 1) == 0);
-      }
+      for (int b = 0; b < nbig; ++b) event(list[b]);
       __syncthreads();
     }
   }
-  if constexpr (MODE == GLV_COMPENSATED && sizeof(T) == 4) {
-    if (A.fallback) {
+}
+
+template <typename T, int COORDS, int MODE>
+__global__ __launch_bounds__(kBigBlock) void k_event_totals_big(FwdArgs<T, COORDS, MODE> A) {
+  __shared__ double red[16];
+  scan_events(A.off, A.ne, [&](int64_t n) { return n > A.cap; }, [&](int64_t e) {
+    const int64_t lo = A.off[e], hi = A.off[e + 1];
+    double acc[4] = {0, 0, 0, 0};
+    for (int64_t i = lo + threadIdx.x; i < hi; i += kBigBlock) {
+      T v[4];
+      to_cart<COORDS>(A.p.c[0][i], A.p.c[1][i], A.p.c[2][i], A.p.c[3][i], v);
 #pragma unroll
-      for (int d = 32; d > 0; d >>= 1) fb += __shfl_xor(fb, d);
-      if ((threadIdx.x & 63) == 0 && fb) atomicAdd(A.fallback, (unsigned long long)fb);
+      for (int k = 0; k < 4; ++k) acc[k] += (double)v[k];
     }
-  }
+    T tot[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) tot[k] = (T)block_sum(acc[k], red);
+    if (threadIdx.x == 0) {
+      if (A.total[0]) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) A.total[k][e] = tot[k];
+      }
+      if (MODE != GLV_COMPENSATED && A.event_m) A.event_m[e] = mass_of(tot);
+    }
+  });
 }
 
 // --------------------------------------------------------------- backward
@@ -1292,66 +1821,7 @@ struct BwdArgs {
   int wave_bytes;  // LDS bytes per wavefront
 };
 
-// Cartesian gradient of particle i from its partners (global memory path).
-template <typename T, int COORDS>
-__device__ __forceinline__ void partner_sum_global(const BwdArgs<T, COORDS>& A, int64_t lo, int64_t n,
-                                                   int64_t pbase, int64_t ai, const T vi[4], T u[4]) {
-  for (int64_t bj = 0; bj < n; ++bj) {
-    if (bj == ai) continue;
-    const int64_t r = ai < bj ? ai : bj, c = ai < bj ? bj : ai;
-    const T g = A.gpair[pbase + row_start(r, n) + (c - r - 1)];
-    T vj[4], w[4], uw[4];
-    const int64_t j = lo + bj;
-    to_cart<COORDS>(A.p.c[0][j], A.p.c[1][j], A.p.c[2][j], A.p.c[3][j], vj);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) w[k] = vi[k] + vj[k];
-    dmass<T>(w, g, uw);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) u[k] += uw[k];
-  }
-}
-
-template <typename T, int COORDS>
-__device__ void big_event_bwd(const BwdArgs<T, COORDS>& A, int64_t e, int64_t lo, int64_t hi, double* red) {
-  const int64_t n = hi - lo;
-  // total 4-vector for the event-mass term: the forward's, or summed here
-  T ut[4] = {0, 0, 0, 0};
-  if (A.gem) {
-    T tot[4];
-    if (A.tot[0]) {
-#pragma unroll
-      for (int k = 0; k < 4; ++k) tot[k] = A.tot[k][e];
-    } else {
-      double acc[4] = {0, 0, 0, 0};
-      for (int64_t i = lo + threadIdx.x; i < hi; i += blockDim.x) {
-        T v[4];
-        to_cart<COORDS>(A.p.c[0][i], A.p.c[1][i], A.p.c[2][i], A.p.c[3][i], v);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) acc[k] += (double)v[k];
-      }
-#pragma unroll
-      for (int k = 0; k < 4; ++k) tot[k] = (T)block_sum(acc[k], red);
-    }
-    dmass<T>(tot, A.gem[e], ut);
-  }
-  if (A.gt[0]) {
-#pragma unroll
-    for (int k = 0; k < 4; ++k) ut[k] += A.gt[k][e];
-  }
-  for (int64_t i = lo + threadIdx.x; i < hi; i += blockDim.x) {
-    T c0 = A.p.c[0][i], c3 = A.p.c[3][i];
-    LegJ<T> L = to_cart_j<COORDS, T>(c0, A.p.c[1][i], A.p.c[2][i], c3);
-    T u[4] = {ut[0], ut[1], ut[2], ut[3]};
-    if (A.gpair) partner_sum_global<T, COORDS>(A, lo, n, A.poff[e], i - lo, L.v, u);
-    T g[4];
-    chain_coords<COORDS, T>(L, c0, c3, u, g);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) store_out(A.gp[k], i, g[k]);
-  }
-  __syncthreads();
-}
-
-// An event the tiled backward leaves to k_event_reduce_bwd_big: more than
+// An event the tiled backward leaves to the second launch: more than
 // cap particles or, with pair upstreams, more than qcap pairs.
 __device__ __forceinline__ bool bwd_big(int64_t n, int cap, int qcap, bool pairs) {
   return n > cap || (pairs && npairs(n) > (int64_t)qcap);
@@ -1425,7 +1895,7 @@ __global__ __launch_bounds__(kMaxBlock, 6) void k_event_reduce_bwd(BwdArgs<T, CO
     __syncthreads();
     int ca = 0;
     while (ca < nev) {
-      if (bwd_big(s_off[ca + 1] - s_off[ca], cap, qcap, pairs)) {  // k_event_reduce_bwd_big's event
+      if (bwd_big(s_off[ca + 1] - s_off[ca], cap, qcap, pairs)) {  // the second launch's event
         ++ca;
         continue;
       }
@@ -1627,38 +2097,241 @@ __global__ __launch_bounds__(kMaxBlock, 6) void k_event_reduce_bwd(BwdArgs<T, CO
   }
 }
 
-// Backward of the events k_event_reduce_bwd leaves out (more than cap
-// particles), as k_event_reduce_big does for the forward.
+// Backward of the events k_event_reduce_bwd leaves out when there are no
+// pair upstreams (more than cap particles): every particle's share of the
+// event outputs.
 template <typename T, int COORDS>
 __global__ __launch_bounds__(kBigBlock) void k_event_reduce_bwd_big(BwdArgs<T, COORDS> A) {
   __shared__ double red[16];
-  __shared__ int64_t list[kBigBlock];
-  __shared__ int count;
-  const int64_t step = (int64_t)gridDim.x * kBigBlock * kBigScan;
-  for (int64_t base = (int64_t)blockIdx.x * kBigBlock * kBigScan; base < A.ne; base += step) {
-    int64_t n[kBigScan];
-    scan_sizes(A.off, A.ne, base, n);
-    unsigned bigm = 0;  // bit k: event k of this thread
+  scan_events(A.off, A.ne, [&](int64_t n) { return n > A.cap; }, [&](int64_t e) {
+    const int64_t lo = A.off[e], hi = A.off[e + 1];
+    T ut[4] = {0, 0, 0, 0};
+    if (A.gem) {
+      T tot[4];
+      if (A.tot[0]) {
 #pragma unroll
-    for (int k = 0; k < kBigScan; ++k)
-      if (n[k] >= 0 && bwd_big(n[k], A.cap, A.qcap, A.gpair != nullptr)) bigm |= 1u << k;
-#pragma unroll 1
-    for (int k = 0; k < kBigScan; ++k) {
-      const int64_t e = base + k * kBigBlock + threadIdx.x;
-      const bool big = (bigm >> k) & 1u;
-      if (!__syncthreads_or(big)) continue;
-      if (threadIdx.x == 0) count = 0;
-      __syncthreads();
-      if (big) list[atomicAdd(&count, 1)] = e;
-      __syncthreads();
-      const int nbig = count;
-      for (int b = 0; b < nbig; ++b) {
-        const int64_t eb = list[b];
-        big_event_bwd<T, COORDS>(A, eb, A.off[eb], A.off[eb + 1], red);
+        for (int k = 0; k < 4; ++k) tot[k] = A.tot[k][e];
+      } else {
+        double acc[4] = {0, 0, 0, 0};
+        for (int64_t i = lo + threadIdx.x; i < hi; i += kBigBlock) {
+          T v[4];
+          to_cart<COORDS>(A.p.c[0][i], A.p.c[1][i], A.p.c[2][i], A.p.c[3][i], v);
+#pragma unroll
+          for (int k = 0; k < 4; ++k) acc[k] += (double)v[k];
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) tot[k] = (T)block_sum(acc[k], red);
       }
-      __syncthreads();
+      dmass<T>(tot, A.gem[e], ut);
     }
-  }
+    if (A.gt[0]) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) ut[k] += A.gt[k][e];
+    }
+    for (int64_t i = lo + threadIdx.x; i < hi; i += kBigBlock) {
+      const T c0 = A.p.c[0][i], c3 = A.p.c[3][i];
+      const LegJ<T> L = to_cart_j<COORDS, T>(c0, A.p.c[1][i], A.p.c[2][i], c3);
+      T g[4];
+      chain_coords<COORDS, T>(L, c0, c3, ut, g);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) store_out(A.gp[k], i, g[k]);
+    }
+    __syncthreads();
+  });
+}
+
+// ------------------------------------ backward, events of many particles
+//
+// With pair upstreams, the events k_event_reduce_bwd leaves out.  Each event
+// is cut into blocks of 32 particles, which stand at equal distances in the
+// event's run of pairs, and a workgroup takes the blocks that stand in its
+// equal share of all pairs, its wavefronts in turn.  A block is summed by one
+// wavefront, without atomics or workgroup barriers, and a large event spreads
+// over many.
+//
+// A block: lane l of either half of the wavefront owns particle a0 + (l & 31)
+// and goes through the event's partners 64 at a time, the halves taking 32
+// partners each.  The partners' Cartesian vectors are converted by the lanes
+// and staged in the wavefront's LDS; their pair upstreams come in batches of
+// kBatch partners per half: rows (b, a0..a0+31) of partners before the block
+// lie over the lanes, those after it along the lanes' own rows and are read
+// as 64- or 128-byte pieces; both are laid out in LDS as one row per lane.
+// The next batch's upstreams and the next partners are in flight while a
+// batch is evaluated.  Every ordered pair's c = g/|m| is evaluated by the lane
+// that needs it: twice per pair, where a shared evaluation would need a second
+// pass over the batch and sums across wavefronts.  Bound by VALU issue (about
+// 35 instructions per 64 ordered pairs).
+constexpr int kBwdGrid = 1024;
+template <typename T>
+constexpr int batch_cols() {
+  return sizeof(T) == 4 ? 16 : 8;
+}
+
+// Pair (i, j) of an event of n sits at row_at(i) + j; rows_on(d, left) is
+// row_at(i + d) - row_at(i) for left = n - i.
+__device__ __forceinline__ int64_t row_at(int64_t i, int64_t n) { return row_start(i, n) - i - 1; }
+__device__ __forceinline__ unsigned rows_on(unsigned d, unsigned left) {
+  return __umul24(d, left) - d - (__umul24(d, d + 1) >> 1);
+}
+
+template <typename T, int COORDS>
+__global__ __launch_bounds__(256, (sizeof(T) == 4 ? 4 : 3)) void k_event_bwd_dense(BwdArgs<T, COORDS> A) {
+  using R4 = typename V4<T>::type;
+  constexpr int B = 256, NW = 4;
+  constexpr int kC = batch_cols<T>(), kPitch = kC + 1;
+  constexpr int kRows = 32 / kC;  // rows of a block a half reads per load after the block
+  __shared__ R4 carts[NW][64];
+  __shared__ T tiles[NW][64 * kPitch];
+  __shared__ EventList<B> L;
+  const int tid = (int)threadIdx.x, lane = tid & 63, half = lane >> 5, al = lane & 31;
+  const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+  R4* const cart = carts[wid];
+  T* const tile = tiles[wid];
+  const bool want_v = A.gem != nullptr;
+  const bool sum_v = want_v && A.tot[0] == nullptr;
+
+  // One block: particles [a0, a0 + 32) of the event at lo with n particles
+  // and upstreams g.
+  auto block = [&](int64_t ev, int64_t lo, int n, const T* g, int a0) {
+    const int a = min(a0 + al, n - 1);  // past the event: its last particle again, not stored
+    const int64_t ai = lo + a;
+    const T c0 = A.p.c[0][ai], c1 = A.p.c[1][ai], c2 = A.p.c[2][ai], c3 = A.p.c[3][ai];
+    LegJ<T> J;
+    T S[4] = {0, 0, 0, 0};  // sum of c (v_a + v_b)
+    T gt[4] = {0, 0, 0, 0}, gem = 0, tot[4] = {0, 0, 0, 0};  // the event's upstreams
+    double acc[4] = {0, 0, 0, 0};
+    // batch k: partners b = 64 (k / kPer) + 32 half + kC (k % kPer), ..., b + kC - 1
+    constexpr int kPer = 32 / kC;
+    const int nb = ((n + 63) / 64) * kPer;
+    T gv[kC];  // the upstreams on their way
+    T nx[4];   // the partner on its way
+#pragma unroll 1
+    for (int k = 0; k <= nb; ++k) {
+      const int t0 = (k - 1) / kPer * 64, b = t0 + 32 * half + (k - 1) % kPer * kC;
+      if (k > 0) {  // batch k - 1 (and its partners) into LDS
+        const bool before = b < a0;
+        wave_sync();  // what is overwritten has been read
+        if ((k - 1) % kPer == 0) {
+          T v[4];
+          to_cart<COORDS, T, true>(nx[0], nx[1], nx[2], nx[3], v);
+          cart[lane] = R4{v[0], v[1], v[2], v[3]};
+          if (sum_v && t0 + lane < n) {
+#pragma unroll
+            for (int d = 0; d < 4; ++d) acc[d] += (double)v[d];
+          }
+        }
+        T* w = tile + (half * 32 + (before ? al : al / kC)) * kPitch + (before ? 0 : al % kC);
+        const int ws = before ? 1 : kRows * kPitch;
+#pragma unroll
+        for (int u = 0; u < kC; ++u) w[u * ws] = gv[u];
+        wave_sync();
+      }
+      if (k < nb) {  // batch k on its way
+        if (k % kPer == 0) {
+          const int64_t i = lo + min(k / kPer * 64 + lane, n - 1);
+#pragma unroll
+          for (int d = 0; d < 4; ++d) nx[d] = A.p.c[d][i];
+        }
+        const int bk0 = k / kPer * 64 + k % kPer * kC, bk = bk0 + 32 * half;
+        const bool before = bk < a0;
+        const int r0 = a0 + al / kC, col = bk + al % kC;
+        // rows are addressed from row ub (its last pair is there: `spare`)
+        const int ub = min(bk0, a0);
+        const unsigned left = (unsigned)(n - ub), spare = (unsigned)(n - 1) * sizeof(T);
+        const char* const base = reinterpret_cast<const char*>(g + row_at(ub, n));
+        if (__ballot(bk >= a0 && bk < a0 + 32)) {  // a half inside the block: either order of the pair
+#pragma unroll
+          for (int u = 0; u < kC; ++u) {
+            const int r = r0 + u * kRows, i = before ? bk + u : min(r, col), j = before ? a : max(r, col);
+            const unsigned at = (rows_on((unsigned)(i - ub), left) + (unsigned)j) * sizeof(T);
+            gv[u] = *reinterpret_cast<const T*>(base + (i != j && j < n ? at : spare));
+          }
+        } else {
+          // before: rows bk + u at column a; after: rows r0 + kRows u at column col
+          const int row = before ? bk : r0, by = before ? 1 : kRows;
+          const int rows = before ? kC : col < n ? (n - r0 + kRows - 1) / kRows : 0;  // of them in the event
+          unsigned at = (rows_on((unsigned)(row - ub), left) + (unsigned)(before ? a : col)) * sizeof(T);
+          unsigned step = ((unsigned)(n - 1 - row) * by - (before ? 1u : kRows * (kRows + 1) / 2)) * sizeof(T);
+          const unsigned dec = (before ? 1 : kRows * kRows) * sizeof(T);
+#pragma unroll
+          for (int u = 0; u < kC; ++u) {
+            gv[u] = *reinterpret_cast<const T*>(base + (u < rows ? at : spare));
+            at += step;
+            step -= dec;
+          }
+        }
+      }
+      if (k == 0) J = to_cart_j<COORDS, T, true>(c0, c1, c2, c3);
+      if (k == nb) {  // on their way during the last batch
+        if (want_v) gem = A.gem[ev];
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+          if (A.gt[0]) gt[d] = A.gt[d][ev];
+          if (want_v && !sum_v) tot[d] = A.tot[d][ev];
+        }
+      }
+      if (k > 0) {  // batch k - 1
+        const T* const mine = tile + lane * kPitch;
+        const R4* const vb = cart + (b - t0);
+        // partners this lane has here: none past the event
+        const int have = min(kC, n - b), self = a0 + al - b;
+#pragma unroll 4
+        for (int u = 0; u < kC; ++u) {
+          const R4 pb = vb[u];
+          T w[4];
+#pragma unroll
+          for (int d = 0; d < 4; ++d) w[d] = J.v[d] + pb[d];
+          T cf = pair_coef<T>(w, mine[u]);
+          cf = (u < have && u != self) ? cf : T(0);
+#pragma unroll
+          for (int d = 0; d < 4; ++d) S[d] += cf * w[d];
+        }
+      }
+    }
+    // the halves' sums, then the event's upstream
+#pragma unroll
+    for (int k = 0; k < 4; ++k) S[k] += __shfl_xor(S[k], 32);
+    T ut[4] = {0, 0, 0, 0};
+    if (want_v) {
+      if (sum_v) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) tot[k] = (T)wave_total(acc[k]);
+      }
+      dmass<T>(tot, gem, ut);
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) ut[k] += gt[k];
+    if (half == 0 && a0 + al < n) {
+      T u[4], gr[4];
+#pragma unroll
+      for (int k = 0; k < 3; ++k) u[k] = ut[k] - S[k];
+      u[3] = ut[3] + S[3];
+      chain_coords<COORDS, T>(J, c0, c3, u, gr);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) store_out(A.gp[k], ai, gr[k]);
+    }
+  };
+
+  Share sh;
+  int turn = 0;  // the workgroup's blocks so far: its wavefronts take them in turn
+  const int64_t cap_pairs = npairs(A.cap);
+  scan_share<B>(
+      A.off, A.poff, A.ne, kDenseMinPairs, L, &sh,
+      [](int64_t) { return 0; },
+      [&](int, int64_t po, int64_t d) { return po + d > sh.q0 && (d > A.qcap || d > cap_pairs); },
+      [](int64_t) { return false; },
+      [&](int64_t win, int listed) {
+        for (int li = 0; li < listed; ++li) {
+          const int64_t lo = readlane64(L.lo[li], 0), po = readlane64(L.po[li], 0);
+          const int n = __builtin_amdgcn_readfirstlane(L.n[li]);
+          const int64_t ev = win + (__builtin_amdgcn_readfirstlane(L.e[li]) >> 1);
+          const int64_t nblk = (n + 31) / 32, unit = npairs(n) / nblk;
+          const int64_t k0 = sh.q0 > po ? (sh.q0 - po + unit - 1) / unit : 0;
+          const int64_t k1 = min(nblk, (sh.q1 - po + unit - 1) / unit);
+          for (int64_t k = k0; k < k1; ++k, ++turn)
+            if (turn % NW == wid) block(ev, lo, n, A.gpair + po, (int)(32 * k));
+        }
+      });
 }
 
 int big_grid(int64_t ne) {
@@ -1694,6 +2367,8 @@ hipError_t fwd_typed(int64_t ne, const int64_t* off, const int64_t* poff, const 
   A.ne = ne;
   A.epb = t.events_per_tile;
   A.cap = t.lds_particles;
+  const bool pairs = best || pm || (MODE == GLV_COMPENSATED && em);  // evaluated: pair offsets are given
+  A.small = pairs ? std::min(A.cap, kDenseFrom) : A.cap;
   A.qcap = t.pairs_per_round;
   const int waves = t.block / 64;
   const int64_t tiles = (ne + t.events_per_tile - 1) / t.events_per_tile;
@@ -1708,7 +2383,14 @@ hipError_t fwd_typed(int64_t ne, const int64_t* off, const int64_t* poff, const 
   }
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;
-  hipLaunchKernelGGL((k_event_reduce_big<T, COORDS, MODE>), dim3(big_grid(ne)), dim3(kBigBlock), 0, s, A);
+  if (!pairs)
+    hipLaunchKernelGGL((k_event_totals_big<T, COORDS, MODE>), dim3(big_grid(ne)), dim3(kBigBlock), 0, s, A);
+  else if (best)
+    hipLaunchKernelGGL((k_event_dense<T, COORDS, MODE, true>), dim3(dense_grid<MODE, true>()), dim3(dense_block<MODE, true>()), 0, s,
+                       A);
+  else
+    hipLaunchKernelGGL((k_event_dense<T, COORDS, MODE, false>), dim3(dense_grid<MODE, false>()), dim3(dense_block<MODE, false>()), 0,
+                       s, A);
   return hipGetLastError();
 }
 
@@ -1739,7 +2421,10 @@ hipError_t bwd_typed(int64_t ne, const int64_t* off, const int64_t* poff, const 
                      s, A);
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;
-  hipLaunchKernelGGL((k_event_reduce_bwd_big<T, COORDS>), dim3(big_grid(ne)), dim3(kBigBlock), 0, s, A);
+  if (gpair)
+    hipLaunchKernelGGL((k_event_bwd_dense<T, COORDS>), dim3(kBwdGrid), dim3(256), 0, s, A);
+  else
+    hipLaunchKernelGGL((k_event_reduce_bwd_big<T, COORDS>), dim3(big_grid(ne)), dim3(kBigBlock), 0, s, A);
   return hipGetLastError();
 }
 
