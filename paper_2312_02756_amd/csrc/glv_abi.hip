@@ -177,6 +177,19 @@ glv::Tiling default_tiling_bwd(glv_dtype dt) {
   return t;
 }
 
+// Events per tile of the default tilings: a tile's events are done one chunk
+// after the other by one wavefront (one workgroup in the backward), so with
+// few events smaller tiles spread them over more of the GPU.  On Poisson(8)
+// events, FP64, forward / backward: 1,000 events 16.3 / 32.7 us at the default
+// of 32 / 64, 6.2 / 8.3 us at 4; 16,000 events 17.0 / 32.8 us against 9.0 /
+// 13.2 us at 8; 64,000 events 20.5 / 42.6 us against 18.5 / 32.8 us at 16.
+int tile_events(int dflt, int64_t ne) {
+  if (ne <= 8192) return std::min(dflt, 4);
+  if (ne <= 32768) return std::min(dflt, 8);
+  if (ne <= 131072) return std::min(dflt, 16);
+  return dflt;
+}
+
 constexpr size_t kMaxLds = 64 * 1024;
 
 bool block_ok(int b) { return (b == 64 || b == 128 || b == 256 || b == 512) && b <= glv::kMaxBlock; }
@@ -191,10 +204,12 @@ bool tiling_valid(glv_dtype dt, glv_mode mode, bool bwd, const glv::Tiling& t, b
   return lds <= kMaxLds;
 }
 
-// Resolve a user tiling (fields 0 = current choice) and validate it.
-glv_status resolve_tiling(glv_dtype dt, glv_coords co, glv_mode mode, const glv_tiling* user, bool bwd,
+// Resolve a user tiling (fields 0 = current choice) for ne events and validate
+// it.
+glv_status resolve_tiling(glv_dtype dt, glv_coords co, glv_mode mode, const glv_tiling* user, bool bwd, int64_t ne,
                           glv::Tiling* out, bool best = false) {
   glv::Tiling base = bwd ? default_tiling_bwd(dt) : best ? default_tiling_best() : default_tiling(dt, mode);
+  base.events_per_tile = tile_events(base.events_per_tile, ne);
   if (!best) {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) dev = 0;
@@ -696,7 +711,7 @@ glv_status glv_event_reduce(glv_dtype dt, glv_coords co, glv_mode mode, int64_t 
   glv_status st = validate_event_reduce(dt, co, mode, ne, off, poff, p, total, em, pm);
   if (st != GLV_OK) return st;
   glv::Tiling t;
-  st = resolve_tiling(dt, co, mode, tiling, false, &t);
+  st = resolve_tiling(dt, co, mode, tiling, false, ne, &t);
   if (st != GLV_OK) return st;
   if (ne == 0 || (!total && !em && !pm)) return GLV_OK;
   return hip_status(
@@ -721,7 +736,7 @@ glv_status glv_event_reduce_best_pair(glv_dtype dt, glv_coords co, glv_mode mode
       if (a >= r.lo && a < r.hi) return GLV_EINVAL_ALIAS;
   }
   glv::Tiling t;
-  st = resolve_tiling(dt, co, mode, tiling, false, &t, true);
+  st = resolve_tiling(dt, co, mode, tiling, false, ne, &t, true);
   if (st != GLV_OK) return st;
   const glv::BestOut b{best_rank, best_m, target};
   return hip_status(glv::launch_event_reduce(dt, co, mode, ne, off, poff, p, nullptr, nullptr, nullptr, fallback, t,
@@ -777,7 +792,7 @@ glv_status glv_event_reduce_bwd(glv_dtype dt, glv_coords co, int64_t ne, const i
   glv_status st = validate_event_reduce_bwd(dt, co, ne, off, poff, p, gt, gem, gpair, gp);
   if (st != GLV_OK || ne == 0) return st;
   glv::Tiling t;
-  st = resolve_tiling(dt, co, GLV_PLAIN, tiling, true, &t);
+  st = resolve_tiling(dt, co, GLV_PLAIN, tiling, true, ne, &t);
   if (st != GLV_OK) return st;
   if (ne == 0) return GLV_OK;
   return hip_status(
@@ -795,7 +810,7 @@ glv_status glv_event_reduce_bwd_totals(glv_dtype dt, glv_coords co, int64_t ne, 
     for (int j = 0; j < 4; ++j)
       if (overlap(rng(tot[j], ne, elem(dt)), rng(gp[k], 1, elem(dt)))) return GLV_EINVAL_ALIAS;
   glv::Tiling t;
-  st = resolve_tiling(dt, co, GLV_PLAIN, tiling, true, &t);
+  st = resolve_tiling(dt, co, GLV_PLAIN, tiling, true, ne, &t);
   if (st != GLV_OK) return st;
   return hip_status(glv::launch_event_reduce_bwd(dt, co, ne, off, poff, p, gt, gem, gpair, gp, t,
                                                  (hipStream_t)stream, gem ? tot : nullptr));
@@ -808,7 +823,7 @@ glv_status glv_current_tiling(glv_dtype dt, glv_coords co, glv_mode mode, glv_ti
   if (ms != GLV_OK) return ms;
   if (!out) return GLV_EINVAL_NULL;
   glv::Tiling t;
-  glv_status st = resolve_tiling(dt, co, mode, nullptr, false, &t);
+  glv_status st = resolve_tiling(dt, co, mode, nullptr, false, INT64_MAX, &t);
   if (st != GLV_OK) return st;
   write_tiling(t, out);
   return GLV_OK;
@@ -819,7 +834,7 @@ glv_status glv_current_tiling_bwd(glv_dtype dt, glv_coords co, glv_tiling* out) 
   if (!coords_ok(co)) return GLV_EINVAL_COORDS;
   if (!out) return GLV_EINVAL_NULL;
   glv::Tiling t;
-  glv_status st = resolve_tiling(dt, co, GLV_PLAIN, nullptr, true, &t);
+  glv_status st = resolve_tiling(dt, co, GLV_PLAIN, nullptr, true, INT64_MAX, &t);
   if (st != GLV_OK) return st;
   write_tiling(t, out);
   return GLV_OK;
