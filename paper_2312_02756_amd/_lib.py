@@ -111,6 +111,24 @@ def load():
     return _lib
 
 
+_native = None
+
+
+def native():
+    """The native part of the binding (_native.so, built with the library): its
+    functions return None for a call they leave to the Python path."""
+    global _native
+    if _native is None:
+        load()
+        try:
+            from . import _native as mod
+        except ImportError as e:
+            raise RuntimeError("the native binding is missing or does not fit this torch: build it with "
+                               "`python -m paper_2312_02756_amd.build`; there is no fallback path") from e
+        _native = mod
+    return _native
+
+
 class GlvError(RuntimeError):
     def __init__(self, fn, code):
         lib = load()

@@ -1,11 +1,16 @@
 """torch.autograd wrappers: forward and backward both run the library's
 hand-written kernels (the backward calls the "_bwd" entry points, which
 recompute the forward pass from the saved inputs instead of storing
-intermediates)."""
+intermediates).
+
+invariant_mass, boost and event_reduce run as native autograd nodes, whose
+backward needs no interpreter (a forward and backward of small columns: 186 us
+of host time in the Python classes); the classes below serve what the native
+ones decline and define what they do."""
 
 import torch
 
-from . import glv
+from . import _lib, glv
 
 
 class InvariantMass(torch.autograd.Function):
@@ -69,6 +74,9 @@ class EventReduce(torch.autograd.Function):
 
 def invariant_mass(a, b, coords="PtEtaPhiM", mode="plain"):
     """Differentiable pair mass of two 4-column legs."""
+    m = _lib.native().autograd_mass(a, b, coords, mode)
+    if m is not None:
+        return m
     return InvariantMass.apply(coords, mode, *a, *b)
 
 
@@ -82,10 +90,16 @@ def boost(x, beta):
     if beta[0].numel() != x[0].numel() and any(b.requires_grad for b in beta):
         raise ValueError("boost: a broadcast beta (one velocity for all vectors) has no gradient; "
                          "pass one velocity per vector or detach beta")
+    y = _lib.native().autograd_boost(x, beta)
+    if y is not None:
+        return y
     return Boost.apply(*x, *beta)
 
 
 def event_reduce(p, offsets, pair_offsets=None, coords="PtEtaPhiM"):
+    out = _lib.native().autograd_event_reduce(p, offsets, pair_offsets, coords)
+    if out is not None:
+        return tuple(out[:4]), out[4], out[5]
     if pair_offsets is None:
         pair_offsets = glv.glv_pair_offsets(offsets)
     out = EventReduce.apply(offsets, pair_offsets, coords, *p)

@@ -3,7 +3,9 @@ with the same name.  Argument marshalling only: tensors are checked (same GPU,
 dtype, contiguous) and their device pointers handed to the library together
 with torch's current HIP stream; every step of the computation runs in the
 library's gfx950 kernels.  Outputs are allocated here with torch (the
-library itself never allocates).
+library itself never allocates).  The calls a program makes in a loop are
+first offered to the native binding, which does the same checks and
+allocations for plain tensors and declines everything else.
 
 Coordinates are given as "PxPyPzE", "PtEtaPhiM", "PtEtaPhiE" or "PxPyPzM"; modes as
 "plain" or "compensated".
@@ -69,6 +71,10 @@ def glv_invariant_mass(a, b, coords="PtEtaPhiM", mode="plain", out=None, fallbac
     """m[i] = mass(conv(a_i) + conv(b_i)).  ``fallback_count``: optional int64
     GPU tensor of one element, incremented by the number of FP32 items the
     compensated mode recomputed in FP64."""
+    if out is None:
+        m = _lib.native().mass(a, b, coords, mode, fallback_count)
+        if m is not None:
+            return m
     dev, dt = a[0].device, a[0].dtype
     _check_device(a[0])
     n = a[0].numel()
@@ -131,6 +137,10 @@ def glv_boost(x, beta, out=None):
     """Active boost of Cartesian (px, py, pz, E) columns by beta (3 columns of
     n items, or of 1 element = one velocity for all).  ``out`` may be ``x``
     itself (in place)."""
+    if out is None:
+        y = _lib.native().boost(x, beta)
+        if y is not None:
+            return y
     dev, dt = x[0].device, x[0].dtype
     _check_device(x[0])
     n = x[0].numel()
@@ -177,6 +187,10 @@ def _params(m, n, k, dt, dev, name):
 
 
 def _transform(kind, x, m, out):
+    if out is None and len(m) == _TF[kind][1]:
+        y = _lib.native().transform(x, m)
+        if y is not None:
+            return y
     fn, k, _ = _TF[kind]
     dev, dt = x[0].device, x[0].dtype
     _check_device(x[0])
@@ -253,6 +267,10 @@ def glv_rotate_axis_angle_bwd(axis_angle, grad_y):
 def glv_convert(cols, from_coords, to_coords, out=None):
     """The ``to_coords`` coordinates of vectors given in ``from_coords`` (4
     columns each).  ``out`` may be ``cols`` itself (in place)."""
+    if out is None:
+        y = _lib.native().convert(cols, from_coords, to_coords)
+        if y is not None:
+            return y
     dev, dt = cols[0].device, cols[0].dtype
     _check_device(cols[0])
     n = cols[0].numel()
@@ -314,6 +332,9 @@ def glv_invariant_mass_histogram(a, b, lo, hi, n_bins, coords="PtEtaPhiM", mode=
     """The pair masses of glv_invariant_mass(a, b, coords, mode) counted into
     n_bins equal bins of [lo, hi) plus under- and overflow (n_bins + 2 int64)
     without being stored; ``counts``, if given, is added to."""
+    c = _lib.native().mass_histogram(a, b, lo, hi, n_bins, coords, mode, counts, fallback_count)
+    if c is not None:
+        return c
     dev, dt = a[0].device, a[0].dtype
     _check_device(a[0])
     n = a[0].numel()
@@ -336,6 +357,10 @@ def glv_event_reduce_best_pair(p, offsets, target, pair_offsets=None, coords="Pt
     """(rank, mass) per event of its pair closest to ``target``, chosen inside
     the jagged reduction without writing pair masses (rank -1 and NaN for an
     event without one)."""
+    if tiling is None:
+        r = _lib.native().event_reduce_best_pair(p, offsets, target, pair_offsets, coords, mode, fallback_count)
+        if r is not None:
+            return r
     dev, dt = p[0].device, p[0].dtype
     _check_device(p[0])
     offsets = _offsets(offsets, dev)
@@ -361,6 +386,9 @@ def _offsets(offsets, dev):
 
 
 def glv_pair_offsets(offsets):
+    po = _lib.native().pair_offsets(offsets)
+    if po is not None:
+        return po
     _check_device(offsets)
     offsets = _offsets(offsets, offsets.device)
     ne = offsets.numel() - 1
@@ -399,6 +427,11 @@ def glv_event_reduce(p, offsets, pair_offsets=None, coords="PtEtaPhiM", mode="pl
                      want_event_m=True, want_pair_m=True, tiling=None, fallback_count=None, n_pairs=None):
     """Returns (total (4 tensors) or None, event_m or None, pair_m or None).
     ``n_pairs`` (the last pair offset) avoids a device-to-host read when given."""
+    if tiling is None:
+        r = _lib.native().event_reduce(p, offsets, pair_offsets, coords, mode, want_total, want_event_m, want_pair_m,
+                                       fallback_count, n_pairs)
+        if r is not None:
+            return r
     dev, dt = p[0].device, p[0].dtype
     _check_device(p[0])
     offsets = _offsets(offsets, dev)
