@@ -30,17 +30,21 @@ struct OutCols3 {
   T* c[3];
 };
 
-// 16 bytes per lane per column: 2 doubles or 4 floats.
+// 16 bytes per lane per column: 2 doubles or 4 floats.  The type asks for the
+// alignment of its elements only: gfx950's global loads and stores of 16 bytes
+// take any such address, so that the rows of a block with an odd length go the
+// same way as aligned columns (one element per lane before: 10,000,019 FP32
+// boosts forward and backward, rows of that length, 215 us -> 204 us).
 template <typename T>
 struct Vec16;
 template <>
 struct Vec16<double> {
-  typedef double type __attribute__((ext_vector_type(2)));
+  typedef double type __attribute__((ext_vector_type(2), aligned(8)));
   static constexpr int N = 2;
 };
 template <>
 struct Vec16<float> {
-  typedef float type __attribute__((ext_vector_type(4)));
+  typedef float type __attribute__((ext_vector_type(4), aligned(4)));
   static constexpr int N = 4;
 };
 

@@ -94,14 +94,9 @@ hipError_t hist_typed(int64_t n, const void* m, double lo, double hi, int64_t nb
   const T* v = (const T*)m;
   if (nb + 2 <= kHistLdsSlots) {
     constexpr int V = Vec16<T>::N;
-    const bool al = (reinterpret_cast<uintptr_t>(m) & 15) == 0;
-    const int64_t packs = al ? n / V : n;
-    int64_t blocks = (packs + kHistBlock - 1) / kHistBlock;
+    int64_t blocks = (n / V + kHistBlock - 1) / kHistBlock;
     blocks = blocks < 1 ? 1 : (blocks > kHistGrid ? kHistGrid : blocks);
-    if (al)
-      hipLaunchKernelGGL((k_hist_lds<T, V>), dim3((unsigned)blocks), dim3(kHistBlock), 0, s, v, n, h, counts);
-    else
-      hipLaunchKernelGGL((k_hist_lds<T, 1>), dim3((unsigned)blocks), dim3(kHistBlock), 0, s, v, n, h, counts);
+    hipLaunchKernelGGL((k_hist_lds<T, V>), dim3((unsigned)blocks), dim3(kHistBlock), 0, s, v, n, h, counts);
   } else {
     int64_t blocks = (n + kHistBlock - 1) / kHistBlock;
     blocks = blocks < 1 ? 1 : (blocks > 65536 ? 65536 : blocks);

@@ -8,8 +8,7 @@
 // HBM bandwidth: each lane moves 16 bytes per column per step (2 doubles or
 // 4 floats) with non-temporal loads and stores, one wavefront covers a
 // contiguous 1 KiB of every column, and the grid has one lane per pack (a
-// grid-stride loop only takes over beyond 2^31 workgroups).  Columns not
-// aligned to 16 bytes take the same code with one element per lane.
+// grid-stride loop only takes over beyond 2^31 workgroups).
 #include "glv_device.h"
 #include "glv_launch.h"
 
@@ -59,13 +58,9 @@ hipError_t run_stream(const Op& op, int64_t n, unsigned long long* counter, hipS
   return hipGetLastError();
 }
 
-inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
-
 template <typename T, typename Op>
-hipError_t dispatch_width(const Op& op, bool all_aligned, int64_t n, unsigned long long* counter,
-                          hipStream_t s) {
-  if (all_aligned) return run_stream<Op, Vec16<T>::N>(op, n, counter, s);
-  return run_stream<Op, 1>(op, n, counter, s);
+hipError_t run_packs(const Op& op, int64_t n, unsigned long long* counter, hipStream_t s) {
+  return run_stream<Op, Vec16<T>::N>(op, n, counter, s);
 }
 
 // ------------------------------------------------ mass -> histogram, fused
@@ -670,99 +665,81 @@ OutCols3<T> out3(void* const p[3]) {
   return {{(T*)p[0], (T*)p[1], (T*)p[2]}};
 }
 
-template <int N>
-bool all16(const void* const* p) {
-  for (int k = 0; k < N; ++k)
-    if (!aligned16(p[k])) return false;
-  return true;
-}
-
 template <typename T>
 hipError_t mass_typed(glv_coords co, glv_mode mode, int64_t n, const void* const a[4],
                       const void* const b[4], void* m, unsigned long long* fb, hipStream_t s) {
-  bool al = all16<4>(a) && all16<4>(b) && aligned16(m);
   Cols4<T> ca = cols4<T>(a), cb = cols4<T>(b);
-  if (mode == GLV_COMPENSATED) return dispatch_width<T>(MassComp<T>{ca, cb, (T*)m}, al, n, fb, s);
+  if (mode == GLV_COMPENSATED) return run_packs<T>(MassComp<T>{ca, cb, (T*)m}, n, fb, s);
   switch (co) {
     case GLV_PXPYPZE:
-      return dispatch_width<T>(MassPlain<T, GLV_PXPYPZE>{ca, cb, (T*)m}, al, n, nullptr, s);
+      return run_packs<T>(MassPlain<T, GLV_PXPYPZE>{ca, cb, (T*)m}, n, nullptr, s);
     case GLV_PTETAPHIM:
-      return dispatch_width<T>(MassPlain<T, GLV_PTETAPHIM>{ca, cb, (T*)m}, al, n, nullptr, s);
+      return run_packs<T>(MassPlain<T, GLV_PTETAPHIM>{ca, cb, (T*)m}, n, nullptr, s);
     case GLV_PXPYPZM:
-      return dispatch_width<T>(MassPlain<T, GLV_PXPYPZM>{ca, cb, (T*)m}, al, n, nullptr, s);
+      return run_packs<T>(MassPlain<T, GLV_PXPYPZM>{ca, cb, (T*)m}, n, nullptr, s);
     default:
-      return dispatch_width<T>(MassPlain<T, GLV_PTETAPHIE>{ca, cb, (T*)m}, al, n, nullptr, s);
+      return run_packs<T>(MassPlain<T, GLV_PTETAPHIE>{ca, cb, (T*)m}, n, nullptr, s);
   }
 }
 
 template <typename Op>
-hipError_t run_mass_hist(const Op& op, bool al, int64_t n, const HistSpec& h, unsigned long long* counts,
+hipError_t run_mass_hist(const Op& op, int64_t n, const HistSpec& h, unsigned long long* counts,
                          unsigned long long* fb, hipStream_t s) {
-  using T = typename Op::Scalar;
-  constexpr int V = Vec16<T>::N;
+  constexpr int V = Vec16<typename Op::Scalar>::N;
   const bool lds = h.nb + 2 <= kHistLdsSlots;
-  const int64_t packs = al ? n / V : n;
-  int64_t blocks = (packs + kFusedHistBlock - 1) / kFusedHistBlock;
+  int64_t blocks = (n / V + kFusedHistBlock - 1) / kFusedHistBlock;
   // the LDS path merges once per workgroup: 1024 workgroups (32 wavefronts
   // per CU) keep the streams busy without multiplying the merges
   const int64_t cap = lds ? 1024 : 65536;
   blocks = blocks < 1 ? 1 : (blocks > cap ? cap : blocks);
   const dim3 g((unsigned)blocks), b(kFusedHistBlock);
-  if (al && lds)
+  if (lds)
     hipLaunchKernelGGL((k_mass_hist<Op, V, true>), g, b, 0, s, op, n, h, counts, fb);
-  else if (al)
-    hipLaunchKernelGGL((k_mass_hist<Op, V, false>), g, b, 0, s, op, n, h, counts, fb);
-  else if (lds)
-    hipLaunchKernelGGL((k_mass_hist<Op, 1, true>), g, b, 0, s, op, n, h, counts, fb);
   else
-    hipLaunchKernelGGL((k_mass_hist<Op, 1, false>), g, b, 0, s, op, n, h, counts, fb);
+    hipLaunchKernelGGL((k_mass_hist<Op, V, false>), g, b, 0, s, op, n, h, counts, fb);
   return hipGetLastError();
 }
 
 template <typename T>
 hipError_t mass_hist_typed(glv_coords co, glv_mode mode, int64_t n, const void* const a[4], const void* const b[4],
                            const HistSpec& h, unsigned long long* counts, unsigned long long* fb, hipStream_t s) {
-  const bool al = all16<4>(a) && all16<4>(b);
   Cols4<T> ca = cols4<T>(a), cb = cols4<T>(b);
-  if (mode == GLV_COMPENSATED) return run_mass_hist(MassComp<T>{ca, cb, nullptr}, al, n, h, counts, fb, s);
+  if (mode == GLV_COMPENSATED) return run_mass_hist(MassComp<T>{ca, cb, nullptr}, n, h, counts, fb, s);
   switch (co) {
     case GLV_PXPYPZE:
-      return run_mass_hist(MassPlain<T, GLV_PXPYPZE>{ca, cb, nullptr}, al, n, h, counts, nullptr, s);
+      return run_mass_hist(MassPlain<T, GLV_PXPYPZE>{ca, cb, nullptr}, n, h, counts, nullptr, s);
     case GLV_PTETAPHIM:
-      return run_mass_hist(MassPlain<T, GLV_PTETAPHIM>{ca, cb, nullptr}, al, n, h, counts, nullptr, s);
+      return run_mass_hist(MassPlain<T, GLV_PTETAPHIM>{ca, cb, nullptr}, n, h, counts, nullptr, s);
     case GLV_PXPYPZM:
-      return run_mass_hist(MassPlain<T, GLV_PXPYPZM>{ca, cb, nullptr}, al, n, h, counts, nullptr, s);
+      return run_mass_hist(MassPlain<T, GLV_PXPYPZM>{ca, cb, nullptr}, n, h, counts, nullptr, s);
     default:
-      return run_mass_hist(MassPlain<T, GLV_PTETAPHIE>{ca, cb, nullptr}, al, n, h, counts, nullptr, s);
+      return run_mass_hist(MassPlain<T, GLV_PTETAPHIE>{ca, cb, nullptr}, n, h, counts, nullptr, s);
   }
 }
 
 template <typename T>
 hipError_t mass_bwd_typed(glv_coords co, int64_t n, const void* const a[4], const void* const b[4],
                           const void* gm, void* const ga[4], void* const gb[4], hipStream_t s) {
-  bool al = all16<4>(a) && all16<4>(b) && aligned16(gm) && all16<4>((const void* const*)ga) &&
-            all16<4>((const void* const*)gb);
   Cols4<T> ca = cols4<T>(a), cb = cols4<T>(b);
   OutCols4<T> oa = out4<T>(ga), ob = out4<T>(gb);
   const T* g = (const T*)gm;
   switch (co) {
     case GLV_PXPYPZE:
-      return dispatch_width<T>(MassBwd<T, GLV_PXPYPZE>{ca, cb, g, oa, ob}, al, n, nullptr, s);
+      return run_packs<T>(MassBwd<T, GLV_PXPYPZE>{ca, cb, g, oa, ob}, n, nullptr, s);
     case GLV_PTETAPHIM:
-      return dispatch_width<T>(MassBwd<T, GLV_PTETAPHIM>{ca, cb, g, oa, ob}, al, n, nullptr, s);
+      return run_packs<T>(MassBwd<T, GLV_PTETAPHIM>{ca, cb, g, oa, ob}, n, nullptr, s);
     case GLV_PXPYPZM:
-      return dispatch_width<T>(MassBwd<T, GLV_PXPYPZM>{ca, cb, g, oa, ob}, al, n, nullptr, s);
+      return run_packs<T>(MassBwd<T, GLV_PXPYPZM>{ca, cb, g, oa, ob}, n, nullptr, s);
     default:
-      return dispatch_width<T>(MassBwd<T, GLV_PTETAPHIE>{ca, cb, g, oa, ob}, al, n, nullptr, s);
+      return run_packs<T>(MassBwd<T, GLV_PTETAPHIE>{ca, cb, g, oa, ob}, n, nullptr, s);
   }
 }
 
 template <typename T>
 hipError_t boost_typed(int64_t n, const void* const x[4], const void* const beta[3], int64_t bs,
                        void* const y[4], hipStream_t s) {
-  bool al = all16<4>(x) && all16<4>((const void* const*)y) && (bs == 0 || all16<3>(beta));
-  if (bs == 1) return dispatch_width<T>(BoostFwd<T, 1>{cols4<T>(x), cols3<T>(beta), out4<T>(y)}, al, n, nullptr, s);
-  return dispatch_width<T>(BoostFwd<T, 0>{cols4<T>(x), cols3<T>(beta), out4<T>(y)}, al, n, nullptr, s);
+  if (bs == 1) return run_packs<T>(BoostFwd<T, 1>{cols4<T>(x), cols3<T>(beta), out4<T>(y)}, n, nullptr, s);
+  return run_packs<T>(BoostFwd<T, 0>{cols4<T>(x), cols3<T>(beta), out4<T>(y)}, n, nullptr, s);
 }
 
 template <typename T>
@@ -770,20 +747,16 @@ hipError_t boost_bwd_typed(int64_t n, const void* const x[4], const void* const 
                            const void* const gy[4], void* const gx[4], void* const gb[3],
                            hipStream_t s) {
   bool want = gb != nullptr;
-  bool al = all16<4>(gy) && all16<4>((const void* const*)gx) && (bs == 0 || all16<3>(beta)) &&
-            (!want || (all16<4>(x) && all16<3>((const void* const*)gb)));
   Cols4<T> cx = want ? cols4<T>(x) : Cols4<T>{{nullptr, nullptr, nullptr, nullptr}};
   Cols3<T> cbeta = cols3<T>(beta);
   if (want) {
     // grad_beta is per item: beta_stride 1 only (checked by the caller)
-    return dispatch_width<T>(BoostBwd<T, 1, true>{cx, cbeta, cols4<T>(gy), out4<T>(gx), out3<T>(gb)}, al, n,
-                             nullptr, s);
+    return run_packs<T>(BoostBwd<T, 1, true>{cx, cbeta, cols4<T>(gy), out4<T>(gx), out3<T>(gb)}, n, nullptr, s);
   }
   if (bs == 1)
-    return dispatch_width<T>(BoostBwd<T, 1, false>{cx, cbeta, cols4<T>(gy), out4<T>(gx), out3<T>(nullptr)}, al,
-                             n, nullptr, s);
-  return dispatch_width<T>(BoostBwd<T, 0, false>{cx, cbeta, cols4<T>(gy), out4<T>(gx), out3<T>(nullptr)}, al, n,
-                           nullptr, s);
+    return run_packs<T>(BoostBwd<T, 1, false>{cx, cbeta, cols4<T>(gy), out4<T>(gx), out3<T>(nullptr)}, n,
+                        nullptr, s);
+  return run_packs<T>(BoostBwd<T, 0, false>{cx, cbeta, cols4<T>(gy), out4<T>(gx), out3<T>(nullptr)}, n, nullptr, s);
 }
 
 template <typename T, int K>
@@ -805,10 +778,9 @@ template <typename T, int KIND>
 hipError_t transform_typed(int64_t n, const void* const x[4], const void* const* m, int64_t ms, void* const y[4],
                            hipStream_t s) {
   constexpr int K = TfParams<KIND>::K;
-  const bool al = all16<4>(x) && all16<4>((const void* const*)y) && (ms == 0 || all16<K>(m));
   const ColsK<T, K> cm = colsk<T, K>(m);
-  if (ms == 1) return dispatch_width<T>(TransformFwd<T, KIND, 1>{cols4<T>(x), cm, out4<T>(y)}, al, n, nullptr, s);
-  return dispatch_width<T>(TransformFwd<T, KIND, 0>{cols4<T>(x), cm, out4<T>(y)}, al, n, nullptr, s);
+  if (ms == 1) return run_packs<T>(TransformFwd<T, KIND, 1>{cols4<T>(x), cm, out4<T>(y)}, n, nullptr, s);
+  return run_packs<T>(TransformFwd<T, KIND, 0>{cols4<T>(x), cm, out4<T>(y)}, n, nullptr, s);
 }
 
 template <typename T, int KIND>
@@ -816,36 +788,33 @@ hipError_t transform_bwd_typed(int64_t n, const void* const x[4], const void* co
                                const void* const gy[4], void* const gx[4], void* const* gm, hipStream_t s) {
   constexpr int K = TfParams<KIND>::K, NN = TfParams<KIND>::N * TfParams<KIND>::N;
   const bool want = gm != nullptr;
-  const bool al = all16<4>(gy) && all16<4>((const void* const*)gx) && (ms == 0 || all16<K>(m)) &&
-                  (!want || (all16<4>(x) && all16<NN>((const void* const*)gm)));
   const Cols4<T> cx = want ? cols4<T>(x) : Cols4<T>{{nullptr, nullptr, nullptr, nullptr}};
   const ColsK<T, K> cm = colsk<T, K>(m);
   if constexpr (KIND != kTfAxisAngle) {
     if (want)  // per-item matrix gradients: stride 1 only (checked by the caller)
-      return dispatch_width<T>(TransformBwd<T, KIND, 1, true>{cx, cols4<T>(gy), cm, out4<T>(gx), outk<T, NN>(gm)},
-                               al, n, nullptr, s);
+      return run_packs<T>(TransformBwd<T, KIND, 1, true>{cx, cols4<T>(gy), cm, out4<T>(gx), outk<T, NN>(gm)}, n,
+                          nullptr, s);
   }
   if (ms == 1)
-    return dispatch_width<T>(TransformBwd<T, KIND, 1, false>{cx, cols4<T>(gy), cm, out4<T>(gx), outk<T, NN>(nullptr)},
-                             al, n, nullptr, s);
-  return dispatch_width<T>(TransformBwd<T, KIND, 0, false>{cx, cols4<T>(gy), cm, out4<T>(gx), outk<T, NN>(nullptr)},
-                           al, n, nullptr, s);
+    return run_packs<T>(TransformBwd<T, KIND, 1, false>{cx, cols4<T>(gy), cm, out4<T>(gx), outk<T, NN>(nullptr)}, n,
+                        nullptr, s);
+  return run_packs<T>(TransformBwd<T, KIND, 0, false>{cx, cols4<T>(gy), cm, out4<T>(gx), outk<T, NN>(nullptr)}, n,
+                      nullptr, s);
 }
 
 template <typename T, int FROM>
 hipError_t convert_to(glv_coords to, int64_t n, const void* const in[4], void* const out[4], hipStream_t s) {
-  const bool al = all16<4>(in) && all16<4>((const void* const*)out);
   const Cols4<T> ci = cols4<T>(in);
   const OutCols4<T> co = out4<T>(out);
   switch (to) {
     case GLV_PXPYPZE:
-      return dispatch_width<T>(Convert<T, FROM, GLV_PXPYPZE>{ci, co}, al, n, nullptr, s);
+      return run_packs<T>(Convert<T, FROM, GLV_PXPYPZE>{ci, co}, n, nullptr, s);
     case GLV_PTETAPHIM:
-      return dispatch_width<T>(Convert<T, FROM, GLV_PTETAPHIM>{ci, co}, al, n, nullptr, s);
+      return run_packs<T>(Convert<T, FROM, GLV_PTETAPHIM>{ci, co}, n, nullptr, s);
     case GLV_PXPYPZM:
-      return dispatch_width<T>(Convert<T, FROM, GLV_PXPYPZM>{ci, co}, al, n, nullptr, s);
+      return run_packs<T>(Convert<T, FROM, GLV_PXPYPZM>{ci, co}, n, nullptr, s);
     default:
-      return dispatch_width<T>(Convert<T, FROM, GLV_PTETAPHIE>{ci, co}, al, n, nullptr, s);
+      return run_packs<T>(Convert<T, FROM, GLV_PTETAPHIE>{ci, co}, n, nullptr, s);
   }
 }
 
@@ -867,18 +836,17 @@ hipError_t convert_typed(glv_coords from, glv_coords to, int64_t n, const void* 
 template <typename T, int FROM>
 hipError_t convert_bwd_to(glv_coords to, int64_t n, const void* const in[4], const void* const gout[4],
                           void* const gin[4], hipStream_t s) {
-  const bool al = all16<4>(in) && all16<4>(gout) && all16<4>((const void* const*)gin);
   const Cols4<T> ci = cols4<T>(in), cg = cols4<T>(gout);
   const OutCols4<T> co = out4<T>(gin);
   switch (to) {
     case GLV_PXPYPZE:
-      return dispatch_width<T>(ConvertBwd<T, FROM, GLV_PXPYPZE>{ci, cg, co}, al, n, nullptr, s);
+      return run_packs<T>(ConvertBwd<T, FROM, GLV_PXPYPZE>{ci, cg, co}, n, nullptr, s);
     case GLV_PTETAPHIM:
-      return dispatch_width<T>(ConvertBwd<T, FROM, GLV_PTETAPHIM>{ci, cg, co}, al, n, nullptr, s);
+      return run_packs<T>(ConvertBwd<T, FROM, GLV_PTETAPHIM>{ci, cg, co}, n, nullptr, s);
     case GLV_PXPYPZM:
-      return dispatch_width<T>(ConvertBwd<T, FROM, GLV_PXPYPZM>{ci, cg, co}, al, n, nullptr, s);
+      return run_packs<T>(ConvertBwd<T, FROM, GLV_PXPYPZM>{ci, cg, co}, n, nullptr, s);
     default:
-      return dispatch_width<T>(ConvertBwd<T, FROM, GLV_PTETAPHIE>{ci, cg, co}, al, n, nullptr, s);
+      return run_packs<T>(ConvertBwd<T, FROM, GLV_PTETAPHIE>{ci, cg, co}, n, nullptr, s);
   }
 }
 
@@ -928,15 +896,13 @@ hipError_t launch_mass_histogram(glv_dtype dt, glv_coords co, glv_mode mode, int
 
 hipError_t launch_mass_comp_bwd(glv_dtype dt, int64_t n, const void* const a[4], const void* const b[4],
                                 const void* gm, void* const ga[4], void* const gb[4], hipStream_t s) {
-  const bool al = all16<4>(a) && all16<4>(b) && aligned16(gm) && all16<4>((const void* const*)ga) &&
-                  all16<4>((const void* const*)gb);
   if (dt == GLV_F64)
-    return dispatch_width<double>(MassCompBwd<double>{cols4<double>(a), cols4<double>(b), (const double*)gm,
-                                                      out4<double>(ga), out4<double>(gb)},
-                                  al, n, nullptr, s);
-  return dispatch_width<float>(MassCompBwd<float>{cols4<float>(a), cols4<float>(b), (const float*)gm,
-                                                  out4<float>(ga), out4<float>(gb)},
-                               al, n, nullptr, s);
+    return run_packs<double>(MassCompBwd<double>{cols4<double>(a), cols4<double>(b), (const double*)gm,
+                                                 out4<double>(ga), out4<double>(gb)},
+                             n, nullptr, s);
+  return run_packs<float>(MassCompBwd<float>{cols4<float>(a), cols4<float>(b), (const float*)gm,
+                                             out4<float>(ga), out4<float>(gb)},
+                            n, nullptr, s);
 }
 
 hipError_t launch_mass_bwd(glv_dtype dt, glv_coords co, int64_t n, const void* const a[4],
