@@ -463,6 +463,13 @@ __device__ __forceinline__ int64_t readlane64(int64_t x, int lane) {
   return (int64_t)(((uint64_t)hi << 32) | lo);
 }
 
+__device__ __forceinline__ double lane_value(double x, int lane) {
+  return __builtin_bit_cast(double, readlane64(__builtin_bit_cast(int64_t, x), lane));
+}
+__device__ __forceinline__ float lane_value(float x, int lane) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), lane));
+}
+
 // Last c in [lo, hi) with a[c] <= key (a non-decreasing, a[lo] <= key).
 __device__ __forceinline__ int search_le32(const int* a, int lo, int hi, int key) {
   while (hi - lo > 1) {
@@ -1110,15 +1117,17 @@ constexpr bool dense_owned() {  // events stay with one workgroup
 }
 template <int MODE, bool BEST>
 constexpr int dense_block() {
-  return dense_owned<MODE, BEST>() ? 512 : 256;
+  return MODE != GLV_COMPENSATED && BEST ? 512 : 256;
 }
 
 // Workgroups of the large-event launches: what the GPU holds at once (four of
-// 256 threads or two of 512 per CU), so that on small events, where they only
-// read the offsets, they take one round.
+// 256 threads per CU, three with the registers of the compensated mode, or two
+// of 512), so that on small events, where they only read the pair offsets,
+// they take one round.  No variant uses scratch memory where that can be
+// helped: it made the same scan take 14 us instead of 6 on 2^19 events.
 template <int MODE, bool BEST>
 constexpr int dense_grid() {
-  return dense_owned<MODE, BEST>() ? 512 : 1024;
+  return MODE == GLV_COMPENSATED ? 768 : BEST ? 512 : 1024;
 }
 
 // The events a workgroup of the large-event launches has to do among B
@@ -1224,20 +1233,21 @@ __device__ __forceinline__ void scan_share(const int64_t* __restrict__ off, cons
   constexpr int64_t kWin = (int64_t)kSlices * B;
   const int tid = (int)threadIdx.x;
   int64_t wins, stop;  // events still to look at
-  bool placed, more = true;
+  int tries;
+  bool more = true;
   if (ne >= kShareByEvents) {
     const int64_t per = (ne + gridDim.x - 1) / (int64_t)gridDim.x;
     wins = share_index() * per;
     stop = min(wins + per, ne);
     if (wins >= stop) return;
     *share = {0, INT64_MAX};
-    placed = true;
+    tries = 0;
   } else {
     // where equal events would put the share, if it is no smaller than the rest
     wins = (int64_t)((double)ne * share_index() / (double)gridDim.x) - (kWin - ne / (int64_t)gridDim.x) / 2;
     wins = max((int64_t)0, min(wins, ne - kWin));
     stop = ne;
-    placed = false;
+    tries = 2;
   }
   while (more) {
     const int64_t wend = min(wins + kWin, stop);
@@ -1257,14 +1267,20 @@ __device__ __forceinline__ void scan_share(const int64_t* __restrict__ off, cons
         pe[sl] = low[2 * t + 2];
         seen[sl] = peek(wins + t);
       }
-      if (!placed) {
-        placed = true;
+      if (tries) {
         *share = my_share(nq, min_pairs);
         if (share->q0 >= share->q1) return;
-        if (at0 > share->q0 || at1 <= share->q0) {
-          wins = search_share<B>(poff, ne, share->q0, kWin / 4, L.cnt);
+        if (at0 > share->q0 || at1 <= share->q0) {  // begins elsewhere
+          if (--tries && share->q1 - share->q0 == min_pairs) {  // few pairs: shares larger than the grid's equal ones
+            wins = (int64_t)((double)ne * (double)share->q0 / (double)nq) - kWin / 2;
+            wins = max((int64_t)0, min(wins, ne - kWin));
+          } else {
+            wins = search_share<B>(poff, ne, share->q0, kWin / 4, L.cnt);
+            tries = 0;
+          }
           continue;
         }
+        tries = 0;
       }
       more = wend < stop && at1 < share->q1;
       const bool wide = at1 - at0 >= ((int64_t)1 << 32);
@@ -1322,7 +1338,7 @@ __device__ __forceinline__ double wave_total(double v) {
   v += dpp_f64<kDppRowShr + 8, 0xf>(v);
   v += dpp_f64<kDppRowBcast15, 0xa>(v);
   v += dpp_f64<kDppRowBcast31, 0xc>(v);
-  return __builtin_bit_cast(double, readlane64(__builtin_bit_cast(int64_t, v), 63));
+  return lane_value(v, 63);
 }
 
 // A best-pair candidate by the bits of its distance (which order as unsigned
@@ -1377,7 +1393,7 @@ __device__ __forceinline__ void tree_sum(const V* rec, int n, int lane, double t
 }
 
 template <typename T, int COORDS, int MODE, bool BEST>
-__global__ __launch_bounds__((dense_block<MODE, BEST>()), 4) void k_event_dense(FwdArgs<T, COORDS, MODE> A) {
+__global__ __launch_bounds__((dense_block<MODE, BEST>()), (MODE == GLV_COMPENSATED ? 3 : 4)) void k_event_dense(FwdArgs<T, COORDS, MODE> A) {
   constexpr bool kComp = MODE == GLV_COMPENSATED;
   constexpr bool kDefer = kComp && sizeof(T) == 4;
   constexpr bool kOwn = dense_owned<MODE, BEST>();
@@ -2181,6 +2197,7 @@ __global__ __launch_bounds__(256, (sizeof(T) == 4 ? 4 : 3)) void k_event_bwd_den
   constexpr int kC = batch_cols<T>(), kPitch = kC + 1;
   constexpr int kRows = 32 / kC;  // rows of a block a half reads per load after the block
   __shared__ R4 carts[NW][64];
+  __shared__ R4 owns[NW][64];  // a block's particles: Jacobian pieces, (c0, c3), until the end
   __shared__ T tiles[NW][64 * kPitch];
   __shared__ EventList<B> L;
   const int tid = (int)threadIdx.x, lane = tid & 63, half = lane >> 5, al = lane & 31;
@@ -2195,29 +2212,33 @@ __global__ __launch_bounds__(256, (sizeof(T) == 4 ? 4 : 3)) void k_event_bwd_den
   auto block = [&](int64_t ev, int64_t lo, int n, const T* g, int a0) {
     const int a = min(a0 + al, n - 1);  // past the event: its last particle again, not stored
     const int64_t ai = lo + a;
-    const T c0 = A.p.c[0][ai], c1 = A.p.c[1][ai], c2 = A.p.c[2][ai], c3 = A.p.c[3][ai];
-    LegJ<T> J;
+    R4* const own = owns[wid] + 2 * al;
+    T v[4] = {A.p.c[0][ai], A.p.c[1][ai], A.p.c[2][ai], A.p.c[3][ai]};  // its coordinates, then its vector
     T S[4] = {0, 0, 0, 0};  // sum of c (v_a + v_b)
-    T gt[4] = {0, 0, 0, 0}, gem = 0, tot[4] = {0, 0, 0, 0};  // the event's upstreams
+    T up = 0;  // the event's upstreams: g_total in lanes 0-3, g_m in 4, the given totals in 5-8
     double acc[4] = {0, 0, 0, 0};
-    // batch k: partners b = 64 (k / kPer) + 32 half + kC (k % kPer), ..., b + kC - 1
-    constexpr int kPer = 32 / kC;
-    const int nb = ((n + 63) / 64) * kPer;
+    // Tile t0: partners [t0, t0 + 64), split evenly between the halves in
+    // whole batches; batch c of a tile: partners b = t0 + hw half + kC c, ...
     T gv[kC];  // the upstreams on their way
     T nx[4];   // the partner on its way
+    auto half_width = [&](int t0) { return min(32, ((n - t0 + 2 * kC - 1) / (2 * kC)) * kC); };
+    int t0 = 0, c = 0, hw = half_width(0);    // the batch to load next
+    int pt0 = 0, pc = 0, phw = 0;             // the batch loaded before
+    bool last = false;
 #pragma unroll 1
-    for (int k = 0; k <= nb; ++k) {
-      const int t0 = (k - 1) / kPer * 64, b = t0 + 32 * half + (k - 1) % kPer * kC;
-      if (k > 0) {  // batch k - 1 (and its partners) into LDS
-        const bool before = b < a0;
+    for (bool loaded = false; !last; loaded = true) {
+      last = t0 >= n;  // nothing left to load
+      const int pb = pt0 + phw * half + pc * kC;
+      if (loaded) {  // the last batch (and its partners) into LDS
+        const bool before = pb < a0;
         wave_sync();  // what is overwritten has been read
-        if ((k - 1) % kPer == 0) {
-          T v[4];
-          to_cart<COORDS, T, true>(nx[0], nx[1], nx[2], nx[3], v);
-          cart[lane] = R4{v[0], v[1], v[2], v[3]};
-          if (sum_v && t0 + lane < n) {
+        if (pc == 0) {
+          T x[4];
+          to_cart<COORDS, T, true>(nx[0], nx[1], nx[2], nx[3], x);
+          cart[lane] = R4{x[0], x[1], x[2], x[3]};
+          if (sum_v && pt0 + lane < n) {
 #pragma unroll
-            for (int d = 0; d < 4; ++d) acc[d] += (double)v[d];
+            for (int d = 0; d < 4; ++d) acc[d] += (double)x[d];
           }
         }
         T* w = tile + (half * 32 + (before ? al : al / kC)) * kPitch + (before ? 0 : al % kC);
@@ -2226,13 +2247,13 @@ __global__ __launch_bounds__(256, (sizeof(T) == 4 ? 4 : 3)) void k_event_bwd_den
         for (int u = 0; u < kC; ++u) w[u * ws] = gv[u];
         wave_sync();
       }
-      if (k < nb) {  // batch k on its way
-        if (k % kPer == 0) {
-          const int64_t i = lo + min(k / kPer * 64 + lane, n - 1);
+      if (!last) {  // the next batch on its way
+        if (c == 0) {
+          const int64_t i = lo + min(t0 + lane, n - 1);
 #pragma unroll
           for (int d = 0; d < 4; ++d) nx[d] = A.p.c[d][i];
         }
-        const int bk0 = k / kPer * 64 + k % kPer * kC, bk = bk0 + 32 * half;
+        const int bk0 = t0 + c * kC, bk = bk0 + hw * half;
         const bool before = bk < a0;
         const int r0 = a0 + al / kC, col = bk + al % kC;
         // rows are addressed from row ub (its last pair is there: `spare`)
@@ -2253,39 +2274,79 @@ __global__ __launch_bounds__(256, (sizeof(T) == 4 ? 4 : 3)) void k_event_bwd_den
           unsigned at = (rows_on((unsigned)(row - ub), left) + (unsigned)(before ? a : col)) * sizeof(T);
           unsigned step = ((unsigned)(n - 1 - row) * by - (before ? 1u : kRows * (kRows + 1) / 2)) * sizeof(T);
           const unsigned dec = (before ? 1 : kRows * kRows) * sizeof(T);
+          if (__ballot(rows < kC)) {
 #pragma unroll
+            for (int u = 0; u < kC; ++u) {
+              gv[u] = *reinterpret_cast<const T*>(base + (u < rows ? at : spare));
+              at += step;
+              step -= dec;
+            }
+          } else {
+#pragma unroll
+            for (int u = 0; u < kC; ++u) {
+              gv[u] = *reinterpret_cast<const T*>(base + at);
+              at += step;
+              step -= dec;
+            }
+          }
+        }
+      } else {  // the event's upstreams on their way during the last batch
+        const T* at = nullptr;
+        if (want_v) at = lane == 4 ? A.gem : at;
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+          at = lane == d ? A.gt[d] : at;
+          if (want_v && !sum_v) at = lane == 5 + d ? A.tot[d] : at;
+        }
+        if (at) up = at[ev];
+      }
+      if (!loaded) {
+        const LegJ<T> J = to_cart_j<COORDS, T, true>(v[0], v[1], v[2], v[3]);
+        if (half == 0) {
+          own[0] = R4{J.cp, J.sp, J.sh, J.ch};
+          own[1] = R4{v[0], v[3], 0, 0};
+        }
+#pragma unroll
+        for (int d = 0; d < 4; ++d) v[d] = J.v[d];
+      }
+      if (loaded) {  // the batch in LDS
+        const T* const mine = tile + lane * kPitch;
+        const R4* const vb = cart + (pb - pt0);
+        // partners this lane has here: none past the event, not itself
+        const int have = min(kC, n - pb), self = a0 + al - pb;
+        if (__ballot(have < kC || (self >= 0 && self < kC))) {
+#pragma unroll 2
           for (int u = 0; u < kC; ++u) {
-            gv[u] = *reinterpret_cast<const T*>(base + (u < rows ? at : spare));
-            at += step;
-            step -= dec;
+            const R4 q = vb[u];
+            T w[4];
+#pragma unroll
+            for (int d = 0; d < 4; ++d) w[d] = v[d] + q[d];
+            T cf = pair_coef<T>(w, mine[u]);
+            cf = (u < have && u != self) ? cf : T(0);
+#pragma unroll
+            for (int d = 0; d < 4; ++d) S[d] += cf * w[d];
+          }
+        } else {
+#pragma unroll (sizeof(T) == 4 ? 4 : 2)
+          for (int u = 0; u < kC; ++u) {
+            const R4 q = vb[u];
+            T w[4];
+#pragma unroll
+            for (int d = 0; d < 4; ++d) w[d] = v[d] + q[d];
+            const T cf = pair_coef<T>(w, mine[u]);
+#pragma unroll
+            for (int d = 0; d < 4; ++d) S[d] += cf * w[d];
           }
         }
       }
-      if (k == 0) J = to_cart_j<COORDS, T, true>(c0, c1, c2, c3);
-      if (k == nb) {  // on their way during the last batch
-        if (want_v) gem = A.gem[ev];
-#pragma unroll
-        for (int d = 0; d < 4; ++d) {
-          if (A.gt[0]) gt[d] = A.gt[d][ev];
-          if (want_v && !sum_v) tot[d] = A.tot[d][ev];
-        }
-      }
-      if (k > 0) {  // batch k - 1
-        const T* const mine = tile + lane * kPitch;
-        const R4* const vb = cart + (b - t0);
-        // partners this lane has here: none past the event
-        const int have = min(kC, n - b), self = a0 + al - b;
-#pragma unroll 4
-        for (int u = 0; u < kC; ++u) {
-          const R4 pb = vb[u];
-          T w[4];
-#pragma unroll
-          for (int d = 0; d < 4; ++d) w[d] = J.v[d] + pb[d];
-          T cf = pair_coef<T>(w, mine[u]);
-          cf = (u < have && u != self) ? cf : T(0);
-#pragma unroll
-          for (int d = 0; d < 4; ++d) S[d] += cf * w[d];
-        }
+      pt0 = t0;
+      pc = c;
+      phw = hw;
+      c += 1;
+      if (c * kC >= hw) {
+        t0 += 64;
+        c = 0;
+        hw = half_width(t0);
       }
     }
     // the halves' sums, then the event's upstream
@@ -2293,20 +2354,21 @@ __global__ __launch_bounds__(256, (sizeof(T) == 4 ? 4 : 3)) void k_event_bwd_den
     for (int k = 0; k < 4; ++k) S[k] += __shfl_xor(S[k], 32);
     T ut[4] = {0, 0, 0, 0};
     if (want_v) {
-      if (sum_v) {
+      T tot[4];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) tot[k] = (T)wave_total(acc[k]);
-      }
-      dmass<T>(tot, gem, ut);
+      for (int k = 0; k < 4; ++k) tot[k] = sum_v ? (T)wave_total(acc[k]) : lane_value(up, 5 + k);
+      dmass<T>(tot, lane_value(up, 4), ut);
     }
 #pragma unroll
-    for (int k = 0; k < 4; ++k) ut[k] += gt[k];
+    for (int k = 0; k < 4; ++k) ut[k] += lane_value(up, k);
     if (half == 0 && a0 + al < n) {
       T u[4], gr[4];
 #pragma unroll
       for (int k = 0; k < 3; ++k) u[k] = ut[k] - S[k];
       u[3] = ut[3] + S[3];
-      chain_coords<COORDS, T>(J, c0, c3, u, gr);
+      const R4 o0 = own[0], o1 = own[1];
+      const LegJ<T> J{{v[0], v[1], v[2], v[3]}, o0[0], o0[1], o0[2], o0[3]};
+      chain_coords<COORDS, T>(J, o1[0], o1[1], u, gr);
 #pragma unroll
       for (int k = 0; k < 4; ++k) store_out(A.gp[k], ai, gr[k]);
     }
