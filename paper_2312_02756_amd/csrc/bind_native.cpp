@@ -475,6 +475,61 @@ PyObject* py_best_pair(PyObject*, PyObject* const* args, Py_ssize_t na) {
   END_HANDLE_TH_ERRORS
 }
 
+// The tiling of the reverse mode for ne events of n_pairs pairs where none is
+// given or tuned (the library knows the mean size of the events only on the
+// device).  The default, 128 particles and 512 pairs per chunk, suits events
+// of up to about 9 particles; larger ones fill the particles of a chunk only
+// with more pairs.  FP64, 100,000 events of 14 / 24 particles: 104.6 / 303 us
+// at the default, 66.7 / 187 at 256 particles and 2048 pairs, 88.6 / 209 at
+// 4096 (fewer workgroups per CU); 2^19 events of 8: 162.5 / 177 / 231.  FP32:
+// 74.2 / 212 at the default, 46.5 / 96 at 4096; of 8: 104.3 / 101.2.  From
+// about 50 particles on most events are left to the large-event launch.
+std::optional<glv_tiling> bwd_tiling(glv_dtype dt, glv_coords co, int64_t ne, int64_t n_pairs) {
+  constexpr glv_tiling dflt{128, 64, 128, 512};
+  glv_tiling cur;
+  if (ne < 1 || glv_current_tiling_bwd(dt, co, &cur) != GLV_OK) return std::nullopt;
+  if (cur.block != dflt.block || cur.events_per_tile != dflt.events_per_tile ||
+      cur.lds_particles != dflt.lds_particles || cur.pairs_per_round != dflt.pairs_per_round)
+    return std::nullopt;  // tuned
+  const double mean = (double)n_pairs / (double)ne;
+  if (mean < 45.0 || mean > 1250.0) return std::nullopt;
+  if (ne <= 32768 && mean < 150.0) return glv_tiling{0, 0, 0, 1024};
+  return glv_tiling{256, 0, 256, dt == GLV_F32 || mean > 350.0 ? 4096 : 2048};
+}
+
+// event_reduce_bwd(p, offsets, pair_offsets, grad_total, grad_event_m, grad_pair_m, coords)
+PyObject* py_event_reduce_bwd(PyObject*, PyObject* const* args, Py_ssize_t na) {
+  HANDLE_TH_ERRORS
+  Events e;
+  glv_coords co;
+  if (na != 7 || !plain_context() || !e.parse(args[0], args[1], args[2]) || !coords_arg(args[6], &co))
+    Py_RETURN_NONE;
+  Cols gt;
+  Tensor gem, gpm;
+  if (args[3] != Py_None && !columns(args[3], 4, &e.k, false, e.ne(), &gt)) Py_RETURN_NONE;
+  for (int i : {4, 5}) {
+    if (args[i] == Py_None) continue;
+    const Tensor* t = plain_tensor(args[i]);
+    if (!t || !column(*t, e.k, i == 4 ? e.ne() : -1)) Py_RETURN_NONE;
+    (i == 4 ? gem : gpm) = *t;
+  }
+  Cols g;
+  if (!unlocked([&] {
+        if (gpm.defined() && !e.need_pairs()) return false;
+        g = empties(e.k, e.k.n, 4);
+        std::array<void*, 4> tp{};
+        for (size_t i = 0; i < gt.size(); ++i) tp[i] = gt[i].data_ptr();
+        const auto t = gpm.defined() ? bwd_tiling(e.k.dt(), co, e.ne(), gpm.numel()) : std::nullopt;
+        return glv_event_reduce_bwd(e.k.dt(), co, e.ne(), e.offs(), e.pos(), Ptrs<4>(e.p).in(),
+                                    gt.empty() ? nullptr : tp.data(), gem.defined() ? gem.data_ptr() : nullptr,
+                                    gpm.defined() ? gpm.data_ptr() : nullptr, Ptrs<4>(g).out(), t ? &*t : nullptr,
+                                    stream_of(e.k.device)) == GLV_OK;
+      }))
+    Py_RETURN_NONE;
+  return wrap_tuple(g, 0, 4);
+  END_HANDLE_TH_ERRORS
+}
+
 // --------------------------------------------------------------- autograd
 
 // The status of a library call inside an autograd node.
@@ -575,11 +630,13 @@ struct EventReduce : torch::autograd::Function<EventReduce> {
     const Kind k = kind_of(c[2]);
     for (Tensor& t : gy) t = t.contiguous();
     Cols g = empties(k, k.n, 4);
+    const glv_coords co = (glv_coords)ctx->saved_data["coords"].toInt();
+    const int64_t ne = c[0].numel() - 1;
+    const auto t = bwd_tiling(k.dt(), co, ne, gy[5].numel());
     check("glv_event_reduce_bwd",
-          glv_event_reduce_bwd(k.dt(), (glv_coords)ctx->saved_data["coords"].toInt(), c[0].numel() - 1,
-                               c[0].data_ptr<int64_t>(), c[1].data_ptr<int64_t>(), Ptrs<4>(c, 2).in(),
-                               Ptrs<4>(gy).in(), gy[4].data_ptr(), gy[5].data_ptr(), Ptrs<4>(g).out(), nullptr,
-                               stream_of(k.device)));
+          glv_event_reduce_bwd(k.dt(), co, ne, c[0].data_ptr<int64_t>(), c[1].data_ptr<int64_t>(),
+                               Ptrs<4>(c, 2).in(), Ptrs<4>(gy).in(), gy[4].data_ptr(), gy[5].data_ptr(),
+                               Ptrs<4>(g).out(), t ? &*t : nullptr, stream_of(k.device)));
     return with_none(3, g);
   }
 };
@@ -660,6 +717,7 @@ PyMODINIT_FUNC PyInit__native() {
                                   method<py_transform>("transform"),
                                   method<py_pair_offsets>("pair_offsets"),
                                   method<py_event_reduce>("event_reduce"),
+                                  method<py_event_reduce_bwd>("event_reduce_bwd"),
                                   method<py_best_pair>("event_reduce_best_pair"),
                                   method<py_autograd_mass>("autograd_mass"),
                                   method<py_autograd_boost>("autograd_boost"),

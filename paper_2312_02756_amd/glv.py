@@ -463,6 +463,10 @@ def glv_event_reduce_bwd(p, offsets, pair_offsets=None, grad_total=None, grad_ev
     """Reverse mode of glv_event_reduce (plain).  `total`: the forward's event
     totals (4 columns), if at hand -- then glv_event_reduce_bwd_totals, which
     takes the event-mass term's V from them instead of summing it again."""
+    if tiling is None and total is None:
+        gp = _lib.native().event_reduce_bwd(p, offsets, pair_offsets, grad_total, grad_event_m, grad_pair_m, coords)
+        if gp is not None:
+            return gp
     dev, dt = p[0].device, p[0].dtype
     _check_device(p[0])
     offsets = _offsets(offsets, dev)
