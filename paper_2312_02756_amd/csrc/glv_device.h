@@ -128,6 +128,20 @@ __device__ __forceinline__ double d_sqrt(double x) {
   return (x == 0.0 || x == __builtin_huge_val()) ? x : g;
 }
 __device__ __forceinline__ float d_sqrt(float x) { return sqrtf(x); }
+// The same root where the instructions of a pair loop count (ten instead of
+// eighteen): x times the hardware's reciprocal square root, corrected once from
+// the residual.  It equals sqrtf for every x from 2^-102 up to the largest
+// float (all 1.9e9 of them compared on the GPU); the others, zero, infinity
+// and NaN take sqrtf.
+__device__ __forceinline__ float pair_sqrt(float x) {
+  const float y = __builtin_amdgcn_rsqf(x);
+  const float g = x * y;
+  const float r = fmaf(fmaf(-g, g, x), 0.5f * y, g);
+  const unsigned b = __builtin_bit_cast(unsigned, x);  // x >= 2^-96 and finite
+  if (__builtin_expect(b - 0x0f800000u < 0x7f800000u - 0x0f800000u, 1)) return r;
+  return sqrtf(x);
+}
+__device__ __forceinline__ double pair_sqrt(double x) { return d_sqrt(x); }
 __device__ __forceinline__ double d_abs(double x) { return fabs(x); }
 // a * b + c with one rounding, either precision: written out where a sum of
 // products must fuse the same way in every kernel that evaluates it.
@@ -321,6 +335,13 @@ __device__ __forceinline__ void dmass(const T w[4], T g, T u[4]) {
   u[1] = -w[1] * s;
   u[2] = -w[2] * s;
   u[3] = w[3] * s;
+}
+
+// mass_of, in a pair loop.
+template <typename T>
+__device__ __forceinline__ T pair_mass_of(const T w[4]) {
+  T q = w[3] * w[3] - w[0] * w[0] - w[1] * w[1] - w[2] * w[2];
+  return __builtin_copysign(pair_sqrt(d_abs(q)), q);
 }
 
 // ------------------------------------------------- conversion, either way

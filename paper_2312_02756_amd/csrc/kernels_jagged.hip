@@ -1092,11 +1092,10 @@ __global__ __launch_bounds__(kMaxBlock, (fwd_waves<T, MODE, BEST>())) void k_eve
 // the sizes of blockDim events at a time and lists the ones that are its
 // business.  It stages runs of listed events (kDenseCap particles) in LDS,
 // converted once per workgroup, and deals the staged events' pairs to its
-// wavefronts as equal contiguous runs; a wavefront walks its run 64
-// consecutive pairs per step, so that the masses go out as whole cache lines
-// straight from registers, and a lane's step is j += 64 followed by one
-// subtraction per row end it passes.  What bounds it: the stores of the pair
-// masses in FP32 and FP64, and VALU issue in the compensated mode.
+// wavefronts as equal runs of the folded pairs (Folded), 64 per step, so that
+// the masses go out as runs of consecutive addresses straight from registers
+// and a step's bookkeeping is the same for every lane.  What bounds it: VALU
+// issue (about 40 instructions per 64 FP32 pairs), then the stores.
 // An event that does not fit kDenseCap slots is walked in tiles of
 // kDenseCap / 2 rows by kDenseCap / 2 columns, one row per wavefront.
 
@@ -1392,6 +1391,40 @@ __device__ __forceinline__ void tree_sum(const V* rec, int n, int lane, double t
   }
 }
 
+// The pairs of an event of n particles (2 <= n <= 512) folded into a rectangle
+// of rows of equal length w: row i of the pairs followed by the row that
+// completes it, n - 1 - i (n even, w = n - 1) or n - 2 - i (n odd, w = n).
+// Position `at` goes through it 64 at a time with one comparison per step,
+// whatever the rows' lengths; (i, i + 1 + y) is the pair there.
+struct Folded {
+  int n, w, c;     // c - i: the completing row
+  int rows, rest;  // 64 positions: so many rows and the rest
+  int at, i0, x;
+  __device__ __forceinline__ Folded(int n_, int f) : n(n_), at(f) {
+    w = n - 1 + (n & 1);
+    c = n - 1 - (n & 1);
+    rows = 64 / w;
+    rest = 64 - rows * w;
+    // the row: exact, as (f + 1/2) / w stays 1 / (2 w) > 2^-10 from an integer
+    // and the quotient, at most 256, is off by less than 2^-13
+    i0 = (int)(((float)f + 0.5f) * __builtin_amdgcn_rcpf((float)w));
+    x = f - (int)__umul24(i0, w);
+  }
+  __device__ __forceinline__ void step() {
+    at += 64;
+    x += rest;
+    const bool over = x >= w;
+    x = over ? x - w : x;
+    i0 += rows + (over ? 1 : 0);
+  }
+  __device__ __forceinline__ void pair(int* i, int* y) const {
+    const int len = n - 1 - i0;
+    const bool first = x < len;
+    *i = first ? i0 : c - i0;
+    *y = first ? x : x - len;
+  }
+};
+
 template <typename T, int COORDS, int MODE, bool BEST>
 __global__ __launch_bounds__((dense_block<MODE, BEST>()), (MODE == GLV_COMPENSATED ? 3 : 4)) void k_event_dense(FwdArgs<T, COORDS, MODE> A) {
   constexpr bool kComp = MODE == GLV_COMPENSATED;
@@ -1414,7 +1447,7 @@ __global__ __launch_bounds__((dense_block<MODE, BEST>()), (MODE == GLV_COMPENSAT
   const int tid = (int)threadIdx.x, lane = tid & 63;
   const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-  const bool want_pairs = !BEST && A.pair_m != nullptr;
+  const bool want_pairs = !BEST && (!kComp || A.pair_m != nullptr);  // plain: pairs are all that brings it here
   const bool want_k = kComp && A.event_m != nullptr;
   const bool want_sums = A.total[0] != nullptr || A.event_m != nullptr;
   unsigned fb = 0;
@@ -1430,7 +1463,7 @@ __global__ __launch_bounds__((dense_block<MODE, BEST>()), (MODE == GLV_COMPENSAT
       T w[4];
 #pragma unroll
       for (int k = 0; k < 4; ++k) w[k] = a[k] + b[k];
-      return mass_of(w);
+      return pair_mass_of(w);
     }
   };
   auto stage = [&](int slot, int64_t gi) {
@@ -1664,25 +1697,18 @@ __global__ __launch_bounds__((dense_block<MODE, BEST>()), (MODE == GLV_COMPENSAT
         T* const pout = want_pairs ? A.pair_m + readlane64(cpo, c) : nullptr;
         double kacc = 0.0;
         Cand<T, int> best{~0ull, 0, T(0)};
-        int r = rb + (k - pb) + lane;
-        const int re = rb + (ke - pb);
-        if (r < re) {
-          int i, j;
-          decode_pair_small(r, n0, &i, &j);
-          for (; r < re; r += 64) {
-            double kd;
-            const T m = pair_of(s0 + i, s0 + j, &kd);
-            if constexpr (kComp) kacc += kd;
-            if (want_pairs)  // a 32-bit offset: at most kCap particles
-              store_out(reinterpret_cast<T*>(reinterpret_cast<char*>(pout) + (unsigned)r * (unsigned)sizeof(T)), 0, m);
-            if constexpr (BEST) offer(best, m, r);
-            j += 64;
-            while (j >= n0) {  // past the row's end: the next row starts one column later
-              ++i;
-              j += i + 1 - n0;
-              if (i >= n0 - 1) break;  // past the last pair: the loop ends here
-            }
-          }
+        const int fe = rb + (ke - pb);
+        Folded f(n0, rb + (k - pb) + lane);
+        for (; f.at < fe; f.step()) {
+          int i, y;
+          f.pair(&i, &y);
+          const unsigned r = (unsigned)row_start32(i, n0) + (unsigned)y;  // its rank
+          double kd;
+          const T m = pair_of(s0 + i, s0 + i + 1 + y, &kd);
+          if constexpr (kComp) kacc += kd;
+          if (want_pairs)  // a 32-bit offset: at most kCap particles
+            *reinterpret_cast<T*>(reinterpret_cast<char*>(pout) + r * (unsigned)sizeof(T)) = m;
+          if constexpr (BEST) offer(best, m, (int)r);
         }
         if constexpr (kComp) {
           if (want_k) {
