@@ -441,7 +441,7 @@ struct FwdArgs {
   int64_t ne;
   int epb;         // events per wavefront tile
   int cap;         // particles staged per chunk (per wavefront)
-  int small;       // events of more particles are left to the second launch (small <= cap)
+  int small;       // events of more particles are left to the second launch (see small_events)
   int qcap;        // pairs evaluated per round (per wavefront)
   int wave_bytes;  // LDS bytes per wavefront
 };
@@ -480,6 +480,27 @@ __device__ __forceinline__ int search_le32(const int* a, int lo, int hi, int key
       hi = mid;
   }
   return lo;
+}
+
+// The largest events of the first launch.  Where pairs are evaluated it
+// depends on their mean number per event, which both launches read: on
+// small events the tail of the sizes is better done beside its neighbours
+// (up to kDenseFrom particles) than by waking the second launch, and once most
+// events are large that launch takes all but the smallest (kDenseLow).  The
+// line lies where the two cross for Poisson sizes, by type; 40,000 events,
+// first launch / second launch: FP64 of 22 particles 52.2 / 56.4 us, of 26
+// 70.2 / 63.5, of 32 94.5 / 73.6; FP32 of 18 48.2 / 47.9, of 26 94.3 / 51.2;
+// FP32 compensated of 22 85.2 / 81.4, of 26 114.5 / 91.0; FP64 compensated of
+// 14 101 / 120, of 18 148 / 126; best pair of 22 67.5 / 79.6, of 26 90.8 / 86.8.
+constexpr int kDenseFrom = 48;
+constexpr int kDenseLow = 12;
+
+template <typename T, int MODE, bool BEST>
+__device__ __forceinline__ int small_events(const int64_t* poff, int64_t ne, int small) {
+  constexpr int64_t kMean = BEST                      ? 310
+                            : MODE == GLV_COMPENSATED ? (sizeof(T) == 8 ? 140 : 230)
+                                                      : (sizeof(T) == 8 ? 290 : 180);
+  return poff[ne] >= ne * kMean ? min(small, kDenseLow) : small;
 }
 
 // LDS of one wavefront of the forward reduction (cap particles, qcap pairs):
@@ -709,6 +730,7 @@ __global__ __launch_bounds__(kMaxBlock, (fwd_waves<T, MODE, BEST>())) void k_eve
     }
   }
   const uint64_t valid = (nev >= 64) ? ~0ull : ((1ull << nev) - 1);
+  const int small = need_po ? small_events<T, MODE, BEST>(A.poff, A.ne, A.small) : A.small;
   // where the rounds hold per-pair partials (compensated, best pair), a chunk
   // takes at most one round of pairs, so that no round runs nearly empty
   // (FP32 compensated 252 -> 241 us, best pair 254 -> 225 us on 2^20
@@ -717,7 +739,7 @@ __global__ __launch_bounds__(kMaxBlock, (fwd_waves<T, MODE, BEST>())) void k_eve
   unsigned fb = 0;
 
   int ca, cb;
-  next_chunk(0, nev, valid, mine, olo, ohi, cap, A.small, plo, phi, pcap, &ca, &cb);
+  next_chunk(0, nev, valid, mine, olo, ohi, cap, small, plo, phi, pcap, &ca, &cb);
   Prefetch<T> pre;
   if (ca < nev) {
     const int64_t b0 = readlane64(olo, ca);
@@ -765,7 +787,7 @@ __global__ __launch_bounds__(kMaxBlock, (fwd_waves<T, MODE, BEST>())) void k_eve
 
     // the next chunk's particles into registers, in flight from here on
     int na, nb;
-    next_chunk(cb, nev, valid, mine, olo, ohi, cap, A.small, plo, phi, pcap, &na, &nb);
+    next_chunk(cb, nev, valid, mine, olo, ohi, cap, small, plo, phi, pcap, &na, &nb);
     if (na < nev) {
       const int64_t b1 = readlane64(olo, na);
       prefetch_chunk(A.p, b1, (int)(readlane64(ohi, nb - 1) - b1), lane, &pre);
@@ -1107,8 +1129,6 @@ constexpr int dense_cap() {
 }
 constexpr int kDenseEvents = 64;  // events per chunk (one lane each)
 constexpr int kDenseMinPairs = 2048;  // pairs a workgroup takes at least
-// Events of more particles take this path where pairs are evaluated.
-constexpr int kDenseFrom = 48;
 
 template <int MODE, bool BEST>
 constexpr bool dense_owned() {  // events stay with one workgroup
@@ -1496,7 +1516,7 @@ __global__ __launch_bounds__((dense_block<MODE, BEST>()), (MODE == GLV_COMPENSAT
   };
 
   Share sh;
-  const int64_t small_pairs = npairs(A.small);
+  const int64_t small_pairs = npairs(small_events<T, MODE, BEST>(A.poff, A.ne, A.small));
   // the event's place for a redo mark (without event masses or best pairs: its first pair mass)
   auto peek = [&](int64_t e) -> float {
     if constexpr (kDefer) {
