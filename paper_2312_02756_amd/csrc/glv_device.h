@@ -54,17 +54,18 @@ struct Pack {
   T v[V];
 };
 
-// Streaming load of elements [V*i, V*i + V) of column p.  The data is read
-// once per launch, so it bypasses the caches' retention (non-temporal).
-template <typename T, int V>
+// Load of elements [V*i, V*i + V) of column p.  The data is read once per
+// launch; with STREAM it bypasses the caches' retention (non-temporal).
+template <typename T, int V, bool STREAM = true>
 __device__ __forceinline__ Pack<T, V> load_pack(const T* __restrict__ p, int64_t i) {
   Pack<T, V> r;
   if constexpr (V == 1) {
-    r.v[0] = __builtin_nontemporal_load(p + i);
+    r.v[0] = STREAM ? __builtin_nontemporal_load(p + i) : p[i];
   } else {
     static_assert(V == Vec16<T>::N, "vector width must be 16 bytes");
     typedef typename Vec16<T>::type VT;
-    VT x = __builtin_nontemporal_load(reinterpret_cast<const VT*>(p) + i);
+    const VT* const q = reinterpret_cast<const VT*>(p) + i;
+    const VT x = STREAM ? __builtin_nontemporal_load(q) : *q;
 #pragma unroll
     for (int k = 0; k < V; ++k) r.v[k] = x[k];
   }

@@ -1446,7 +1446,8 @@ struct Folded {
 };
 
 template <typename T, int COORDS, int MODE, bool BEST>
-__global__ __launch_bounds__((dense_block<MODE, BEST>()), (MODE == GLV_COMPENSATED ? 3 : 4)) void k_event_dense(FwdArgs<T, COORDS, MODE> A) {
+__global__ __launch_bounds__((dense_block<MODE, BEST>()),
+                             (MODE == GLV_COMPENSATED ? 3 : 4)) void k_event_dense(FwdArgs<T, COORDS, MODE> A) {
   constexpr bool kComp = MODE == GLV_COMPENSATED;
   constexpr bool kDefer = kComp && sizeof(T) == 4;
   constexpr bool kOwn = dense_owned<MODE, BEST>();
@@ -1538,7 +1539,7 @@ __global__ __launch_bounds__((dense_block<MODE, BEST>()), (MODE == GLV_COMPENSAT
   };
   auto redo_only = [&](int64_t d) { return d <= small_pairs; };
 
-  scan_share<B>(A.off, A.poff, A.ne, kDenseMinPairs, L, &sh, peek, picked, redo_only, [&](int64_t win, int total_listed) {
+  auto work = [&](int64_t win, int total_listed) {
     const int64_t q0 = sh.q0, q1 = sh.q1;
     for (int li = 0; li < total_listed;) {
       // chunk: one lane per event from li on (each wavefront forms it alike)
@@ -1772,7 +1773,8 @@ __global__ __launch_bounds__((dense_block<MODE, BEST>()), (MODE == GLV_COMPENSAT
       }
       li += nc;
     }
-  });
+  };
+  scan_share<B>(A.off, A.poff, A.ne, kDenseMinPairs, L, &sh, peek, picked, redo_only, work);
   if constexpr (kDefer) {
     if (A.fallback) {
 #pragma unroll
@@ -2494,11 +2496,11 @@ hipError_t fwd_typed(int64_t ne, const int64_t* off, const int64_t* poff, const 
   if (!pairs)
     hipLaunchKernelGGL((k_event_totals_big<T, COORDS, MODE>), dim3(big_grid(ne)), dim3(kBigBlock), 0, s, A);
   else if (best)
-    hipLaunchKernelGGL((k_event_dense<T, COORDS, MODE, true>), dim3(dense_grid<MODE, true>()), dim3(dense_block<MODE, true>()), 0, s,
-                       A);
+    hipLaunchKernelGGL((k_event_dense<T, COORDS, MODE, true>), dim3(dense_grid<MODE, true>()),
+                       dim3(dense_block<MODE, true>()), 0, s, A);
   else
-    hipLaunchKernelGGL((k_event_dense<T, COORDS, MODE, false>), dim3(dense_grid<MODE, false>()), dim3(dense_block<MODE, false>()), 0,
-                       s, A);
+    hipLaunchKernelGGL((k_event_dense<T, COORDS, MODE, false>), dim3(dense_grid<MODE, false>()),
+                       dim3(dense_block<MODE, false>()), 0, s, A);
   return hipGetLastError();
 }
 

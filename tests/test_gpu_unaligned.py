@@ -67,3 +67,24 @@ def test_unaligned_outputs_in_place(dtype):
     glv.glv_boost(rows, beta, out=rows)
     assert all(torch.equal(r, w) for r, w in zip(rows, want))
     assert bool((block[:, :2] == -7.0).all()) and bool((block[:, -1] == -7.0).all())
+
+
+@pytest.mark.parametrize("n", [(160 << 20) // 32 - 3, (160 << 20) // 32 + 5])
+def test_cached_and_streamed_loads_agree(n):
+    """A conversion of FP32 columns just under and over the size that streams: the first and last items bitwise
+    those of a small call."""
+    g = torch.Generator(device="cuda").manual_seed(962)
+    x = tuple(torch.rand(n, device="cuda", generator=g) + 0.1 for _ in range(4))
+    y = glv.glv_convert(x, "PtEtaPhiM", "PxPyPzE")
+    for part in (slice(0, 1000), slice(n - 1001, n)):
+        small = glv.glv_convert(tuple(c[part].clone() for c in x), "PtEtaPhiM", "PxPyPzE")
+        assert all(torch.equal(c[part], s) for c, s in zip(y, small))
+
+
+@pytest.mark.parametrize("n", [512, 511 * 512 * 2 + 1, 1024 * 1024 - 2, 1024 * 1024, 4096 * 1024 - 2, 4096 * 1024 + 3])
+def test_fused_histogram_grids(n):
+    """The sizes around which the fused histogram changes its number of workgroups: the counts of the stored masses."""
+    a, b = (gpu(x, torch.float64) for x in synth.pairs_generic(synth.rng(963), n))
+    got = glv.glv_invariant_mass_histogram(a, b, 0.0, 300.0, 1000)
+    want = glv.glv_mass_histogram(glv.glv_invariant_mass(a, b), 0.0, 300.0, 1000)
+    assert torch.equal(got, want) and int(got.sum()) == n
