@@ -112,11 +112,12 @@ typedef enum glv_mode { GLV_PLAIN = 0, GLV_COMPENSATED = 1 } glv_mode;
  *                    (larger events go to the second launch)
  *   pairs_per_round  a multiple of 64 in 64 .. 4096: pairs a wavefront
  *                    evaluates per round, each lane a run of consecutive
- *                    pairs.  FP64 masses pass through LDS in rounds of 64 m
- *                    pairs, m the largest odd number <= pairs_per_round / 64;
- *                    the FP32 plain mode takes a chunk's pairs in one round;
- *                    the compensated mode and glv_event_reduce_best_pair
- *                    take rounds of pairs_per_round
+ *                    pairs.  Plain masses (and the FP64 compensated ones) pass
+ *                    through LDS in rounds of 64 m pairs, m the largest odd
+ *                    number <= pairs_per_round / 64 (FP32 plain: in smaller
+ *                    rounds where LDS would not hold them); the FP32
+ *                    compensated mode and glv_event_reduce_best_pair take
+ *                    rounds of pairs_per_round
  * Backward (glv_event_reduce_bwd): a workgroup takes tiles of
  * events_per_tile consecutive events and stages at most one particle per
  * thread.
@@ -128,10 +129,12 @@ typedef enum glv_mode { GLV_PLAIN = 0, GLV_COMPENSATED = 1 } glv_mode;
  * Fields set to 0 take the library's current choice (the autotuned one if
  * glv_autotune_event_reduce, or glv_autotune_event_reduce_bwd for the
  * backward, ran for this device/dtype/coords/mode, otherwise a built-in
- * default).  A tiling whose workgroup would need more than 64 KiB of LDS is
- * rejected with GLV_EINVAL_TILING: per wavefront the forward keeps 4 values
+ * default).  A call that neither gives a field nor has an autotuned choice is
+ * launched as the library finds best for its type, mode and number of events.
+ * A tiling whose workgroup would need more than 64 KiB of LDS is rejected with
+ * GLV_EINVAL_TILING: per wavefront the forward keeps 4 values
  * per staged particle (12 in the compensated mode), per pair of a round one
- * value in FP64 (none in FP32), 8 more bytes in the compensated mode, one
+ * value in FP64 (none counted in FP32), 8 more bytes in the compensated mode, one
  * value and 4 bytes for glv_event_reduce_best_pair (instead of the FP64
  * value), and 12 bytes per event of the tile; per workgroup the backward
  * keeps 4 values and 2 bytes per staged particle, one value per staged pair
@@ -445,8 +448,9 @@ glv_status glv_autotune_event_reduce(glv_dtype dtype, glv_coords coords, glv_mod
                                      void* const total[4], void* event_m, void* pair_m,
                                      glv_tiling* best, void* stream);
 
-/* The tiling glv_event_reduce would use for these arguments (the current
- * choice or the default), written to *out. */
+/* The tiling whose fields glv_event_reduce would take for these arguments
+ * where a call leaves them 0 (the current choice or the default), written to
+ * *out. */
 glv_status glv_current_tiling(glv_dtype dtype, glv_coords coords, glv_mode mode, glv_tiling* out);
 
 /* The same for glv_event_reduce_bwd, with its arguments (grad_p ends up

@@ -190,6 +190,36 @@ int tile_events(int dflt, int64_t ne) {
   return dflt;
 }
 
+// Sizes of a forward call that evaluates pairs and neither gives a tiling nor
+// has a tuned one; the defaults above are what a tiling's zero fields and the
+// calls of totals alone take.  One wavefront per workgroup, whose LDS is free
+// again as soon as its tile is done; as many staged particles as leave most
+// tiles in one or two full chunks; rounds small enough that staged pairs do not
+// cut the wavefronts per CU, and large for the selection, which stages none.
+// 2^20 Poisson(8) events, defaults above -> these: FP64 182 -> 165 us, FP32 112
+// -> 103, compensated FP64 589 -> 478 and FP32 190 -> 179, best pair FP64 175
+// -> 151 and FP32 131 -> 107; 2^19 events of 14 particles: FP64 188 -> 181, FP32
+// 122 -> 117, compensated FP64 770 -> 600, best pair FP64 206 -> 173.
+glv::Tiling pair_tiling(glv_dtype dt, glv_mode mode, bool best) {
+  const bool f64 = dt == GLV_F64;
+  glv::Tiling t;
+  t.block = 64;
+  if (best) {
+    t.events_per_tile = f64 ? 40 : 64;
+    t.lds_particles = f64 ? 192 : 320;
+    t.pairs_per_round = 3072;
+  } else if (mode == GLV_COMPENSATED) {
+    t.events_per_tile = 32;
+    t.lds_particles = f64 ? 96 : 144;
+    t.pairs_per_round = f64 ? 512 : 768;
+  } else {
+    t.events_per_tile = 32;
+    t.lds_particles = f64 ? 128 : 160;
+    t.pairs_per_round = f64 ? 384 : 768;
+  }
+  return t;
+}
+
 constexpr size_t kMaxLds = 64 * 1024;
 
 bool block_ok(int b) { return (b == 64 || b == 128 || b == 256 || b == 512) && b <= glv::kMaxBlock; }
@@ -205,10 +235,14 @@ bool tiling_valid(glv_dtype dt, glv_mode mode, bool bwd, const glv::Tiling& t, b
 }
 
 // Resolve a user tiling (fields 0 = current choice) for ne events and validate
-// it.
+// it; pairs: a forward call that evaluates pairs.
 glv_status resolve_tiling(glv_dtype dt, glv_coords co, glv_mode mode, const glv_tiling* user, bool bwd, int64_t ne,
-                          glv::Tiling* out, bool best = false) {
-  glv::Tiling base = bwd ? default_tiling_bwd(dt) : best ? default_tiling_best() : default_tiling(dt, mode);
+                          bool pairs, glv::Tiling* out, bool best = false) {
+  const bool given = user && (user->block || user->events_per_tile || user->lds_particles || user->pairs_per_round);
+  glv::Tiling base = bwd               ? default_tiling_bwd(dt)
+                     : pairs && !given ? pair_tiling(dt, mode, best)
+                     : best            ? default_tiling_best()
+                                       : default_tiling(dt, mode);
   base.events_per_tile = tile_events(base.events_per_tile, ne);
   if (!best) {
     int dev = 0;
@@ -711,7 +745,7 @@ glv_status glv_event_reduce(glv_dtype dt, glv_coords co, glv_mode mode, int64_t 
   glv_status st = validate_event_reduce(dt, co, mode, ne, off, poff, p, total, em, pm);
   if (st != GLV_OK) return st;
   glv::Tiling t;
-  st = resolve_tiling(dt, co, mode, tiling, false, ne, &t);
+  st = resolve_tiling(dt, co, mode, tiling, false, ne, pm || (mode == GLV_COMPENSATED && em), &t);
   if (st != GLV_OK) return st;
   if (ne == 0 || (!total && !em && !pm)) return GLV_OK;
   return hip_status(
@@ -736,7 +770,7 @@ glv_status glv_event_reduce_best_pair(glv_dtype dt, glv_coords co, glv_mode mode
       if (a >= r.lo && a < r.hi) return GLV_EINVAL_ALIAS;
   }
   glv::Tiling t;
-  st = resolve_tiling(dt, co, mode, tiling, false, ne, &t, true);
+  st = resolve_tiling(dt, co, mode, tiling, false, ne, true, &t, true);
   if (st != GLV_OK) return st;
   const glv::BestOut b{best_rank, best_m, target};
   return hip_status(glv::launch_event_reduce(dt, co, mode, ne, off, poff, p, nullptr, nullptr, nullptr, fallback, t,
@@ -792,7 +826,7 @@ glv_status glv_event_reduce_bwd(glv_dtype dt, glv_coords co, int64_t ne, const i
   glv_status st = validate_event_reduce_bwd(dt, co, ne, off, poff, p, gt, gem, gpair, gp);
   if (st != GLV_OK || ne == 0) return st;
   glv::Tiling t;
-  st = resolve_tiling(dt, co, GLV_PLAIN, tiling, true, ne, &t);
+  st = resolve_tiling(dt, co, GLV_PLAIN, tiling, true, ne, false, &t);
   if (st != GLV_OK) return st;
   if (ne == 0) return GLV_OK;
   return hip_status(
@@ -810,7 +844,7 @@ glv_status glv_event_reduce_bwd_totals(glv_dtype dt, glv_coords co, int64_t ne, 
     for (int j = 0; j < 4; ++j)
       if (overlap(rng(tot[j], ne, elem(dt)), rng(gp[k], 1, elem(dt)))) return GLV_EINVAL_ALIAS;
   glv::Tiling t;
-  st = resolve_tiling(dt, co, GLV_PLAIN, tiling, true, ne, &t);
+  st = resolve_tiling(dt, co, GLV_PLAIN, tiling, true, ne, false, &t);
   if (st != GLV_OK) return st;
   return hip_status(glv::launch_event_reduce_bwd(dt, co, ne, off, poff, p, gt, gem, gpair, gp, t,
                                                  (hipStream_t)stream, gem ? tot : nullptr));
@@ -823,7 +857,7 @@ glv_status glv_current_tiling(glv_dtype dt, glv_coords co, glv_mode mode, glv_ti
   if (ms != GLV_OK) return ms;
   if (!out) return GLV_EINVAL_NULL;
   glv::Tiling t;
-  glv_status st = resolve_tiling(dt, co, mode, nullptr, false, INT64_MAX, &t);
+  glv_status st = resolve_tiling(dt, co, mode, nullptr, false, INT64_MAX, false, &t);
   if (st != GLV_OK) return st;
   write_tiling(t, out);
   return GLV_OK;
@@ -834,7 +868,7 @@ glv_status glv_current_tiling_bwd(glv_dtype dt, glv_coords co, glv_tiling* out) 
   if (!coords_ok(co)) return GLV_EINVAL_COORDS;
   if (!out) return GLV_EINVAL_NULL;
   glv::Tiling t;
-  glv_status st = resolve_tiling(dt, co, GLV_PLAIN, nullptr, true, INT64_MAX, &t);
+  glv_status st = resolve_tiling(dt, co, GLV_PLAIN, nullptr, true, INT64_MAX, false, &t);
   if (st != GLV_OK) return st;
   write_tiling(t, out);
   return GLV_OK;
@@ -859,6 +893,7 @@ glv_status glv_autotune_event_reduce(glv_dtype dt, glv_coords co, glv_mode mode,
           glv::Tiling t{b, e, c, q};
           if (tiling_valid(dt, mode, false, t)) cands.push_back(t);
         }
+  cands.push_back(pair_tiling(dt, mode, false));  // what an untuned call takes, but for few events
   auto launch = [&](const glv::Tiling& t) {
     return glv::launch_event_reduce(dt, co, mode, ne, off, poff, p, total, em, pm, nullptr, t, s);
   };

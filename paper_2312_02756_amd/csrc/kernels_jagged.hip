@@ -488,18 +488,20 @@ __device__ __forceinline__ int search_le32(const int* a, int lo, int hi, int key
 // (up to kDenseFrom particles) than by waking the second launch, and once most
 // events are large that launch takes all but the smallest (kDenseLow).  The
 // line lies where the two cross for Poisson sizes, by type; 40,000 events,
-// first launch / second launch: FP64 of 22 particles 52.2 / 56.4 us, of 26
-// 70.2 / 63.5, of 32 94.5 / 73.6; FP32 of 18 48.2 / 47.9, of 26 94.3 / 51.2;
-// FP32 compensated of 22 85.2 / 81.4, of 26 114.5 / 91.0; FP64 compensated of
-// 14 101 / 120, of 18 148 / 126; best pair of 22 67.5 / 79.6, of 26 90.8 / 86.8.
+// first launch / second launch: FP64 of 24 particles 58.7 / 58.3 us, of 28
+// 80.5 / 64.4; FP32 of 24 45.7 / 47.6, of 26 57.0 / 51.3; FP32 compensated of
+// 20 76.5 / 81.3, of 24 101 / 87; FP64 compensated of 18 121 / 121, of 20 149 /
+// 127; best pair FP64 of 28 84 / 89, FP32 of 32 86 / 83.  With 300,000 events
+// the first launch stays ahead longer (best pair of 32 particles 417 / 603,
+// FP32 of 28 230 / 255), with 1,000 also (FP32 of 28 19.6 / 23.1).
 constexpr int kDenseFrom = 48;
 constexpr int kDenseLow = 12;
 
 template <typename T, int MODE, bool BEST>
 __device__ __forceinline__ int small_events(const int64_t* poff, int64_t ne, int small) {
-  constexpr int64_t kMean = BEST                      ? 310
-                            : MODE == GLV_COMPENSATED ? (sizeof(T) == 8 ? 140 : 230)
-                                                      : (sizeof(T) == 8 ? 290 : 180);
+  constexpr int64_t kMean = BEST                      ? 480
+                            : MODE == GLV_COMPENSATED ? (sizeof(T) == 8 ? 170 : 250)
+                                                      : 290;
   return poff[ne] >= ne * kMean ? min(small, kDenseLow) : small;
 }
 
@@ -507,7 +509,8 @@ __device__ __forceinline__ int small_events(const int64_t* poff, int64_t ne, int
 //   cart[cap]  (px, py, pz, E)             staged Cartesian records
 //   leg[2 cap] (pt, eta, phi, M), (mT, delta, mT - pt, M^2) per particle,
 //              adjacent (one address for both reads)   compensated mode
-//   pm[qcap]   FP64: pair masses of a round (stored from here, coalesced)
+//   pm[qcap]   pair masses of a round (stored from here, coalesced); not for
+//              FP32 compensated masses
 //   kev[epb+1] K of each of the chunk's events with pairs in a round
 //              (compensated event mass)
 //   bm[epb+1], br[epb+1]  best pair of each of the chunk's events with
@@ -535,7 +538,7 @@ __host__ __device__ __forceinline__ size_t wave_lds_bytes(int cap, int qcap, int
   if (MODE == GLV_COMPENSATED) b += (size_t)cap * 8 * sizeof(T) + (size_t)(epb + 1) * sizeof(double);
   if (BEST)
     b += (size_t)(epb + 1) * (sizeof(T) + sizeof(int));  // each event's best of a round
-  else if (sizeof(T) == 8)
+  else if (sizeof(T) == 8 || MODE == GLV_PLAIN)
     b += (size_t)qcap * sizeof(T);  // staged pair masses
   b += 3 * (size_t)(epb + 1) * sizeof(int);
   return (b + 31) & ~(size_t)31;
@@ -563,7 +566,7 @@ __device__ __forceinline__ WaveLds<T, MODE> carve_wave_lds(unsigned char* p, int
     p += (size_t)(epb + 1) * sizeof(int);
   } else {
     w.br = nullptr;
-    if (sizeof(T) == 8) p += (size_t)qcap * sizeof(T);
+    if (sizeof(T) == 8 || MODE == GLV_PLAIN) p += (size_t)qcap * sizeof(T);
   }
   w.eo = reinterpret_cast<int*>(p);
   w.en = w.eo + (epb + 1);
@@ -678,13 +681,16 @@ constexpr int fwd_waves() {
 //      events with pairs and the square-root decode of its rank, then steps
 //      to the lexicographic successor -- every lane the same number of pairs
 //      whatever the event sizes, and a handful of integer operations per
-//      step.  FP64 masses go to the wave's LDS, in rounds of 64 m pairs with m
-//      odd (which spreads one LDS store instruction's lanes over distinct
-//      banks), and from there to pair_m with coalesced stores; FP32 masses
-//      (two lanes of a store instruction per 64-byte segment at m = 8) are
-//      stored by their lane, in one round (plain mode) or rounds of qcap
-//      (compensated mode and best pair, whose chunks hold at most one round
-//      of pairs unless a single event has more).  In the compensated mode
+//      step.  Masses go to the wave's LDS, in rounds of 64 m pairs with m odd
+//      (which spreads one LDS store instruction's lanes over distinct banks),
+//      and from there to pair_m with coalesced stores; those of the FP32
+//      compensated mode, whose evaluation hides the scattered stores (189 us
+//      against 231 staged on 2^20 Poisson(8) events), are stored by their lane.
+//      FP32 plain masses stored by their lane cost 120 us instead of 103, and
+//      on 2^19 events of 14 particles, whose runs of pairs are longer than a
+//      64-byte segment, 212 instead of 117.  Compensated mode and best pair:
+//      rounds of qcap, a chunk holding at most one round of pairs unless a
+//      single event has more.  In the compensated mode
 //      each lane also sums K = E_i E_j - p_i.p_j of its pairs per event: an
 //      event inside one run takes the lane's sum, an event spanning runs the
 //      scan of their tails (keyed by event over the lanes) plus the head of
@@ -701,7 +707,7 @@ __global__ __launch_bounds__(kMaxBlock, (fwd_waves<T, MODE, BEST>())) void k_eve
   constexpr bool kComp = MODE == GLV_COMPENSATED;
   constexpr bool kDefer = kComp && (sizeof(T) == 4);
   constexpr int kSlots = Prefetch<T>::kSlots;
-  constexpr bool kStageMasses = sizeof(T) == 8 && !BEST;
+  constexpr bool kStageMasses = (sizeof(T) == 8 || !kComp) && !BEST;
   using R4 = typename V4<T>::type;
   const int lane = threadIdx.x & 63;
   const int wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -2457,10 +2463,26 @@ int grid_for(int64_t ne, int epb) {
   return (int)tiles;
 }
 
+// Pairs of one round that a tiling's wavefront stages and the particles beside
+// them.  FP32 plain: the tiling's own limit on LDS leaves the staged pairs out
+// (any pairs_per_round fits), so they get at most a quarter of the 64 KiB of a
+// workgroup, and the particles at most the rest.
+template <typename T, int MODE>
+void fwd_caps(const Tiling& t, bool best, bool pairs, int* cap, int* qcap) {
+  *cap = t.lds_particles;
+  *qcap = t.pairs_per_round;
+  if (sizeof(T) == 8 || MODE != GLV_PLAIN || best) return;
+  const int room = 64 * 1024 / (t.block / 64);
+  *qcap = pairs ? std::min(t.pairs_per_round, room / 4 / (int)sizeof(T)) : 0;
+  if (!pairs) return;
+  const int rest = room - (int)wave_lds_bytes<T, MODE, false>(0, *qcap, t.events_per_tile);
+  *cap = std::min(t.lds_particles, rest / (4 * (int)sizeof(T)));
+}
+
 template <typename T, int COORDS, int MODE>
 hipError_t fwd_typed(int64_t ne, const int64_t* off, const int64_t* poff, const void* const p[4],
                      void* const total[4], void* em, void* pm, const BestOut* best, unsigned long long* fb,
-                     const Tiling& t, size_t lds, hipStream_t s) {
+                     const Tiling& t, hipStream_t s) {
   FwdArgs<T, COORDS, MODE> A;
   A.best_rank = best ? best->rank : nullptr;
   A.best_m = best ? (T*)best->mass : nullptr;
@@ -2476,20 +2498,19 @@ hipError_t fwd_typed(int64_t ne, const int64_t* off, const int64_t* poff, const 
   A.fallback = fb;
   A.ne = ne;
   A.epb = t.events_per_tile;
-  A.cap = t.lds_particles;
   const bool pairs = best || pm || (MODE == GLV_COMPENSATED && em);  // evaluated: pair offsets are given
+  fwd_caps<T, MODE>(t, best != nullptr, pairs, &A.cap, &A.qcap);
   A.small = pairs ? std::min(A.cap, kDenseFrom) : A.cap;
-  A.qcap = t.pairs_per_round;
   const int waves = t.block / 64;
   const int64_t tiles = (ne + t.events_per_tile - 1) / t.events_per_tile;
   if (best) {
-    A.wave_bytes = (int)wave_lds_bytes<T, MODE, true>(t.lds_particles, t.pairs_per_round, t.events_per_tile);
-    hipLaunchKernelGGL((k_event_reduce<T, COORDS, MODE, true>), dim3(grid_for(tiles, waves)), dim3(t.block), lds, s,
-                       A);
+    A.wave_bytes = (int)wave_lds_bytes<T, MODE, true>(A.cap, A.qcap, A.epb);
+    hipLaunchKernelGGL((k_event_reduce<T, COORDS, MODE, true>), dim3(grid_for(tiles, waves)), dim3(t.block),
+                       (size_t)waves * A.wave_bytes, s, A);
   } else {
-    A.wave_bytes = (int)wave_lds_bytes<T, MODE, false>(t.lds_particles, t.pairs_per_round, t.events_per_tile);
-    hipLaunchKernelGGL((k_event_reduce<T, COORDS, MODE, false>), dim3(grid_for(tiles, waves)), dim3(t.block), lds, s,
-                       A);
+    A.wave_bytes = (int)wave_lds_bytes<T, MODE, false>(A.cap, A.qcap, A.epb);
+    hipLaunchKernelGGL((k_event_reduce<T, COORDS, MODE, false>), dim3(grid_for(tiles, waves)), dim3(t.block),
+                       (size_t)waves * A.wave_bytes, s, A);
   }
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;
@@ -2541,18 +2562,18 @@ hipError_t bwd_typed(int64_t ne, const int64_t* off, const int64_t* poff, const 
 template <typename T>
 hipError_t fwd_dt(glv_coords co, glv_mode mode, int64_t ne, const int64_t* off, const int64_t* poff,
                   const void* const p[4], void* const total[4], void* em, void* pm, const BestOut* b,
-                  unsigned long long* fb, const Tiling& t, size_t lds, hipStream_t s) {
+                  unsigned long long* fb, const Tiling& t, hipStream_t s) {
   if (mode == GLV_COMPENSATED)
-    return fwd_typed<T, GLV_PTETAPHIM, GLV_COMPENSATED>(ne, off, poff, p, total, em, pm, b, fb, t, lds, s);
+    return fwd_typed<T, GLV_PTETAPHIM, GLV_COMPENSATED>(ne, off, poff, p, total, em, pm, b, fb, t, s);
   switch (co) {
     case GLV_PXPYPZE:
-      return fwd_typed<T, GLV_PXPYPZE, GLV_PLAIN>(ne, off, poff, p, total, em, pm, b, nullptr, t, lds, s);
+      return fwd_typed<T, GLV_PXPYPZE, GLV_PLAIN>(ne, off, poff, p, total, em, pm, b, nullptr, t, s);
     case GLV_PTETAPHIM:
-      return fwd_typed<T, GLV_PTETAPHIM, GLV_PLAIN>(ne, off, poff, p, total, em, pm, b, nullptr, t, lds, s);
+      return fwd_typed<T, GLV_PTETAPHIM, GLV_PLAIN>(ne, off, poff, p, total, em, pm, b, nullptr, t, s);
     case GLV_PXPYPZM:
-      return fwd_typed<T, GLV_PXPYPZM, GLV_PLAIN>(ne, off, poff, p, total, em, pm, b, nullptr, t, lds, s);
+      return fwd_typed<T, GLV_PXPYPZM, GLV_PLAIN>(ne, off, poff, p, total, em, pm, b, nullptr, t, s);
     default:
-      return fwd_typed<T, GLV_PTETAPHIE, GLV_PLAIN>(ne, off, poff, p, total, em, pm, b, nullptr, t, lds, s);
+      return fwd_typed<T, GLV_PTETAPHIE, GLV_PLAIN>(ne, off, poff, p, total, em, pm, b, nullptr, t, s);
   }
 }
 
@@ -2586,8 +2607,9 @@ size_t fwd_wave_bytes(glv_dtype dt, glv_mode mode, int cap, int qcap, int epb) {
 size_t event_reduce_lds_bytes(glv_dtype dt, glv_mode mode, const Tiling& t, bool best) {
   const size_t waves = (size_t)t.block / 64;
   const int cap = t.lds_particles, qcap = t.pairs_per_round, epb = t.events_per_tile;
-  return waves * (best ? fwd_wave_bytes<true>(dt, mode, cap, qcap, epb)
-                       : fwd_wave_bytes<false>(dt, mode, cap, qcap, epb));
+  if (best) return waves * fwd_wave_bytes<true>(dt, mode, cap, qcap, epb);
+  // staged FP32 plain masses do not count: fwd_caps fits them in
+  return waves * fwd_wave_bytes<false>(dt, mode, cap, dt == GLV_F32 && mode == GLV_PLAIN ? 0 : qcap, epb);
 }
 
 size_t event_reduce_bwd_lds_bytes(glv_dtype dt, const Tiling& t) {
@@ -2621,9 +2643,8 @@ hipError_t launch_event_reduce(glv_dtype dt, glv_coords co, glv_mode mode, int64
                                const int64_t* poff, const void* const p[4], void* const total[4], void* em,
                                void* pm, unsigned long long* fb, const Tiling& t, hipStream_t s,
                                const BestOut* best) {
-  size_t lds = event_reduce_lds_bytes(dt, mode, t, best != nullptr);
-  if (dt == GLV_F64) return fwd_dt<double>(co, mode, ne, off, poff, p, total, em, pm, best, nullptr, t, lds, s);
-  return fwd_dt<float>(co, mode, ne, off, poff, p, total, em, pm, best, fb, t, lds, s);
+  if (dt == GLV_F64) return fwd_dt<double>(co, mode, ne, off, poff, p, total, em, pm, best, nullptr, t, s);
+  return fwd_dt<float>(co, mode, ne, off, poff, p, total, em, pm, best, fb, t, s);
 }
 
 hipError_t launch_event_reduce_bwd(glv_dtype dt, glv_coords co, int64_t ne, const int64_t* off,

@@ -124,3 +124,33 @@ def test_pair_offsets_at_tile_and_launch_edges(ne):
     """Tiles of 2,048 events; one launch up to 65,536 events, three beyond."""
     off = _csr(synth.rng(806 + ne).integers(0, 20, ne))
     assert np.array_equal(host(glv.glv_pair_offsets(_off(off))), oracle.pair_offsets(off))
+
+
+@pytest.mark.parametrize("mode,dtype,n", [("plain", torch.float64, 24), ("plain", torch.float32, 24),
+                                          ("compensated", torch.float64, 18), ("compensated", torch.float32, 22)])
+def test_line_between_the_launches(mode, dtype, n):
+    """Mean pairs just below and above the number from which the second launch
+    takes all but the smallest events."""
+    for size in (n, n + 1):
+        off = _csr([size] * 40 + [1, 0, size - 1])
+        p, _ = synth.pairs_generic(synth.rng(808 + size), int(off[-1]))
+        pg, og = gpu(p, dtype), _off(off)
+        total, em, pm = glv.glv_event_reduce(pg, og, mode=mode)
+        _check_forward(off, p, dtype, "PtEtaPhiM", mode, total, em, pm, f"line {size} {mode} {dtype}")
+
+
+@pytest.mark.parametrize("tiling", [(0, 0, 0, 0), (64, 1, 64, 64), (64, 64, 4000, 4096), (256, 64, 950, 4096),
+                                    (512, 64, 447, 4096), (512, 1, 500, 128), (128, 7, 100, 192)])
+@pytest.mark.parametrize("sizes", [[48, 2, 47, 0, 1, 48] + [0] * 9, [9] * 130, [2] * 300, [30, 3] * 50])
+def test_fp32_rounds_of_any_tiling(tiling, sizes):
+    """FP32 plain masses staged in rounds, up to the tilings whose particles
+    leave the least LDS for them: those of the oracle
+    and bitwise those of another tiling."""
+    off = _csr(sizes, 3)
+    p, _ = synth.pairs_generic(synth.rng(809), int(off[-1]))
+    pg, og = gpu(p, torch.float32), _off(off)
+    total, em, pm = glv.glv_event_reduce(pg, og, tiling=tiling)
+    _check_forward(off, p, torch.float32, "PtEtaPhiM", "plain", total, em, pm, f"rounds {tiling}")
+    ref = glv.glv_event_reduce(pg, og, tiling=(256, 16, 128, 256))
+    assert torch.equal(pm, ref[2]) and torch.equal(em, ref[1])
+    assert all(torch.equal(a, b) for a, b in zip(total, ref[0]))
