@@ -477,13 +477,13 @@ PyObject* py_best_pair(PyObject*, PyObject* const* args, Py_ssize_t na) {
 
 // The tiling of the reverse mode for ne events of n_pairs pairs where none is
 // given or tuned (the library knows the mean size of the events only on the
-// device).  The default, 128 particles and 512 pairs per chunk, suits events
-// of up to about 9 particles; larger ones fill the particles of a chunk only
-// with more pairs.  FP64, 100,000 events of 14 / 24 particles: 104.6 / 303 us
-// at the default, 66.7 / 187 at 256 particles and 2048 pairs, 88.6 / 209 at
-// 4096 (fewer workgroups per CU); 2^19 events of 8: 162.5 / 177 / 231.  FP32:
-// 74.2 / 212 at the default, 46.5 / 96 at 4096; of 8: 104.3 / 101.2.  From
-// about 50 particles on most events are left to the large-event launch.
+// device).  Its own choice suits events of up to about 9 particles (FP64, many
+// events: 13); larger ones fill the particles of a chunk only with more pairs.
+// Library's choice / this one: 60,000 FP64 events of 14 particles 69 / 55 us, of
+// 26 230 / 144; FP32 51 / 41 and 176 / 74; 500,000 events of 14, FP64 336 / 316,
+// FP32 235 / 197, but FP64 of 10 193 / 210; 20,000 FP32 events with a long tail
+// (8 on average) 43 / 31.  From about 50 particles on most events are left to the
+// large-event launch.
 std::optional<glv_tiling> bwd_tiling(glv_dtype dt, glv_coords co, int64_t ne, int64_t n_pairs) {
   constexpr glv_tiling dflt{128, 64, 128, 512};
   glv_tiling cur;
@@ -492,8 +492,9 @@ std::optional<glv_tiling> bwd_tiling(glv_dtype dt, glv_coords co, int64_t ne, in
       cur.lds_particles != dflt.lds_particles || cur.pairs_per_round != dflt.pairs_per_round)
     return std::nullopt;  // tuned
   const double mean = (double)n_pairs / (double)ne;
-  if (mean < 45.0 || mean > 1250.0) return std::nullopt;
-  if (ne <= 32768 && mean < 150.0) return glv_tiling{0, 0, 0, 1024};
+  if (mean < (dt == GLV_F64 && ne > 131072 ? 90.0 : 45.0)) return std::nullopt;
+  if (mean > 1250.0) return glv_tiling{0, 0, 0, 512};
+  if (ne <= 32768 && mean < 150.0) return glv_tiling{0, 0, 0, 1536};
   return glv_tiling{256, 0, 256, dt == GLV_F32 || mean > 350.0 ? 4096 : 2048};
 }
 

@@ -154,3 +154,29 @@ def test_fp32_rounds_of_any_tiling(tiling, sizes):
     ref = glv.glv_event_reduce(pg, og, tiling=(256, 16, 128, 256))
     assert torch.equal(pm, ref[2]) and torch.equal(em, ref[1])
     assert all(torch.equal(a, b) for a, b in zip(total, ref[0]))
+
+
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+@pytest.mark.parametrize("ne,sizes", [(131072, (2, 5)), (131073, (2, 5)), (524288, (1, 3)), (524289, (1, 3)),
+                                      (700, (39, 40, 41, 45, 46, 47)), (700, (54, 55, 56, 57, 4))])
+def test_reverse_mode_chunks_without_a_tiling(ne, sizes, dtype):
+    """Event counts and event sizes around which the chunks of the reverse mode
+    change, through the binding and by the C ABI's own choice: small events
+    bitwise as with a given tiling, larger ones (whose sums follow the launch
+    they are done in) the oracle's gradients."""
+    g = synth.rng(810 + ne)
+    off = _csr(g.choice(sizes, ne))
+    p, _ = synth.pairs_generic(g, int(off[-1]))
+    gpr = g.standard_normal(int(oracle.pair_offsets(off)[-1]))
+    gem, gt = g.standard_normal(ne), synth.upstream(g, ne, 4)
+    pg, og = gpu(p, dtype), _off(off)
+    kw = dict(grad_total=gpu(gt, dtype), grad_event_m=gpu([gem], dtype)[0], grad_pair_m=gpu([gpr], dtype)[0])
+    got = [glv.glv_event_reduce_bwd(pg, og, tiling=t, **kw) for t in (None, (0, 0, 0, 0), (64, 16, 64, 512))]
+    if max(sizes) < 10:
+        assert all(torch.equal(a, b) for o in got[:2] for a, b in zip(o, got[2]))
+        return
+    wp = widened(p, dtype)
+    want = oracle.event_reduce_vjp("PtEtaPhiM", off, wp, widened(gt, dtype), widened([gem], dtype)[0],
+                                   widened([gpr], dtype)[0])
+    for o in got:
+        _check_bwd(off, wp, dtype, "PtEtaPhiM", [host(c).astype(np.float64) for c in o], want, f"chunks {ne} {sizes}")
