@@ -72,11 +72,12 @@ TILING_FIELDS = ("block", "events_per_tile", "lds_particles", "pairs_per_round")
 KERNELS = ["mass_fwd", "mass_bwd", "boost_fwd", "boost_bwd", "mass_fwd32", "mass_bwd32", "boost_fwd32",
            "boost_bwd32", "mass_comp32", "event_reduce", "event_reduce32c", "event_reduce_bwd"]
 KERNEL_SYMBOL = {
-    "mass_fwd": "k_stream<MassPlain<double, 1>, 2>", "mass_bwd": "k_stream<MassBwd<double, 1>, 2>",
-    "boost_fwd": "k_stream<BoostFwd<double, 1>, 2>", "boost_bwd": "k_stream<BoostBwd<double, 1, true>, 2>",
-    "mass_fwd32": "k_stream<MassPlain<float, 1>, 4>", "mass_bwd32": "k_stream<MassBwd<float, 1>, 4>",
-    "boost_fwd32": "k_stream<BoostFwd<float, 1>, 4>", "boost_bwd32": "k_stream<BoostBwd<float, 1, true>, 4>",
-    "mass_comp32": "k_stream<MassComp<float>, 4>",
+    "mass_fwd": "k_stream<MassPlain<double, 1>, 2, true>", "mass_bwd": "k_stream<MassBwd<double, 1>, 2, true>",
+    "boost_fwd": "k_stream<BoostFwd<double, 1>, 2, true>", "boost_bwd": "k_stream<BoostBwd<double, 1, true>, 2, true>",
+    "mass_fwd32": "k_stream<MassPlain<float, 1>, 4, true>", "mass_bwd32": "k_stream<MassBwd<float, 1>, 4, true>",
+    "boost_fwd32": "k_stream<BoostFwd<float, 1>, 4, true>",
+    "boost_bwd32": "k_stream<BoostBwd<float, 1, true>, 4, true>",
+    "mass_comp32": "k_stream<MassComp<float>, 4, true>",
     "event_reduce": "k_event_reduce<double, 1, 0, false>", "event_reduce32c": "k_event_reduce<float, 1, 1, false>",
     "event_reduce_bwd": "k_event_reduce_bwd<double, 1>",
 }
@@ -101,7 +102,7 @@ TRANSFORM_CASES = {
 }
 # The analysis step, measured after the step: kernel symbols.
 ANALYSIS_SYMBOL = {"mass_histogram": "k_hist_lds<double, 2>", "event_best_pair": "k_best_pair<double>",
-                   "mass_comp32_bwd": "k_stream<MassCompBwd<float>, 4>",
+                   "mass_comp32_bwd": "k_stream<MassCompBwd<float>, 4, true>",
                    "mass_histogram_fused": "k_mass_hist<MassPlain<double, 1>, 2, true>",
                    "event_best_pair_fused": "k_event_reduce<double, 1, 0, true>"}
 ALL_SYMBOLS = {**KERNEL_SYMBOL, **{k: v[4] for k, v in CONVERT_CASES.items()},

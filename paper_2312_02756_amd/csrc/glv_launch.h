@@ -78,7 +78,7 @@ struct Tiling {
   int block;
   int events_per_tile;
   int lds_particles;
-  int pairs_per_round;  // forward: pairs a wavefront evaluates per round (the backward ignores it)
+  int pairs_per_round;  // forward: pairs a wavefront evaluates per round (backward: pair upstreams per chunk)
 };
 
 // LDS bytes one workgroup of the forward reduction needs for a tiling (with
