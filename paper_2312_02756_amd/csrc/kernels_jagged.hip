@@ -576,18 +576,21 @@ __device__ __forceinline__ WaveLds<T, MODE> carve_wave_lds(unsigned char* p, int
 
 // Particles of a chunk held in registers between their load and their
 // staging: lane t of the wavefront keeps particles t, t + 64, ...; FP64 keeps
-// one per lane (64 particles), FP32 two (128).  Particles of larger chunks
-// past these are loaded when staged.
-template <typename T>
+// one per lane (64 particles), FP32 two, or three for plain masses, whose
+// chunks hold up to 160 (2^20 Poisson(8) events 105 -> 101 us, 2^19 of 14 119 ->
+// 115; compensated 179 -> 195).  Two in FP64: 190 -> 199.  Particles of larger
+// chunks past these are loaded when staged.
+template <typename T, int MODE, bool BEST>
 struct Prefetch {
-  static constexpr int kSlots = sizeof(T) == 8 ? 1 : 2;
+  static constexpr int kSlots = sizeof(T) == 8 ? 1 : MODE == GLV_PLAIN && !BEST ? 3 : 2;
   T v[kSlots][4];
 };
 
-template <typename T>
-__device__ __forceinline__ void prefetch_chunk(const Cols4<T>& p, int64_t base, int np, int lane, Prefetch<T>* r) {
+template <typename T, int MODE, bool BEST>
+__device__ __forceinline__ void prefetch_chunk(const Cols4<T>& p, int64_t base, int np, int lane,
+                                               Prefetch<T, MODE, BEST>* r) {
 #pragma unroll
-  for (int s = 0; s < Prefetch<T>::kSlots; ++s) {
+  for (int s = 0; s < Prefetch<T, MODE, BEST>::kSlots; ++s) {
     const int t = lane + 64 * s;
     if (t < np) {
 #pragma unroll
@@ -706,7 +709,7 @@ __global__ __launch_bounds__(kMaxBlock, (fwd_waves<T, MODE, BEST>())) void k_eve
   extern __shared__ __align__(32) unsigned char lds[];
   constexpr bool kComp = MODE == GLV_COMPENSATED;
   constexpr bool kDefer = kComp && (sizeof(T) == 4);
-  constexpr int kSlots = Prefetch<T>::kSlots;
+  constexpr int kSlots = Prefetch<T, MODE, BEST>::kSlots;
   constexpr bool kStageMasses = (sizeof(T) == 8 || !kComp) && !BEST;
   using R4 = typename V4<T>::type;
   const int lane = threadIdx.x & 63;
@@ -746,7 +749,7 @@ __global__ __launch_bounds__(kMaxBlock, (fwd_waves<T, MODE, BEST>())) void k_eve
 
   int ca, cb;
   next_chunk(0, nev, valid, mine, olo, ohi, cap, small, plo, phi, pcap, &ca, &cb);
-  Prefetch<T> pre;
+  Prefetch<T, MODE, BEST> pre;
   if (ca < nev) {
     const int64_t b0 = readlane64(olo, ca);
     prefetch_chunk(A.p, b0, (int)(readlane64(ohi, cb - 1) - b0), lane, &pre);
