@@ -27,6 +27,7 @@
 // on collider-sized events it only reads the pair offsets.
 #include "glv_device.h"
 #include "glv_launch.h"
+#include "glv_share.h"
 
 namespace glv {
 namespace {
@@ -1203,16 +1204,11 @@ __device__ __forceinline__ int list_events(EventList<B>& L, bool mine, int64_t l
 // pair offsets both read.  From kShareByEvents events on, hundreds per
 // workgroup, equal numbers of events are equal work enough, and every pair
 // offset is read once (7.0 us against 4.6 on 2^20 small events).
-struct Share {
-  int64_t q0, q1;
-};
 __device__ __forceinline__ int share_index() {  // the grid is a multiple of 8
   return (int)((blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3));
 }
 __device__ __forceinline__ Share my_share(int64_t nq, int64_t min_pairs) {
-  const int64_t grid = gridDim.x, b = share_index();
-  const int64_t per = max((nq + grid - 1) / grid, min_pairs);
-  return {min(b * per, nq), min((b + 1) * per, nq)};
+  return pair_share(nq, min_pairs, gridDim.x, share_index());
 }
 
 constexpr int64_t kShareByEvents = 1 << 18;
@@ -1270,7 +1266,7 @@ __device__ __forceinline__ void scan_share(const int64_t* __restrict__ off, cons
     wins = share_index() * per;
     stop = min(wins + per, ne);
     if (wins >= stop) return;
-    *share = {0, INT64_MAX};
+    *share = whole_share(poff[ne]);
     tries = 0;
   } else {
     // where equal events would put the share, if it is no smaller than the rest
@@ -2447,10 +2443,8 @@ __global__ __launch_bounds__(256, (sizeof(T) == 4 ? 4 : 3)) void k_event_bwd_den
           const int64_t lo = readlane64(L.lo[li], 0), po = readlane64(L.po[li], 0);
           const int n = __builtin_amdgcn_readfirstlane(L.n[li]);
           const int64_t ev = win + (__builtin_amdgcn_readfirstlane(L.e[li]) >> 1);
-          const int64_t nblk = (n + 31) / 32, unit = npairs(n) / nblk;
-          const int64_t k0 = sh.q0 > po ? (sh.q0 - po + unit - 1) / unit : 0;
-          const int64_t k1 = min(nblk, (sh.q1 - po + unit - 1) / unit);
-          for (int64_t k = k0; k < k1; ++k, ++turn)
+          const BlockRange r = share_blocks(sh, po, npairs(n), n);
+          for (int64_t k = r.k0; k < r.k1; ++k, ++turn)
             if (turn % NW == wid) block(ev, lo, n, A.gpair + po, (int)(32 * k));
         }
       });
