@@ -8,8 +8,11 @@
 // Every function returns None where it does not see its way -- an argument of
 // another kind, dtype, layout or device than the plain GPU tensors it knows, a
 // transform or mode of torch that looks inside (functorch, forward mode,
-// dispatch and function modes, tracing), or a status other than GLV_OK: the
-// Python path then runs and does, or refuses, what it always did.
+// dispatch and function modes, tracing), or a refusal by the library (the
+// GLV_EINVAL_* statuses, decided before anything is launched): the Python path
+// then runs and does, or refuses, what it always did.  GLV_EHIP raises here: a
+// kernel may have run by then, and a second call would add to the caller's
+// counters twice.
 #include <Python.h>
 
 #include <ATen/ATen.h>
@@ -194,16 +197,32 @@ PyObject* wrap_tuple(const Cols& c, size_t at, size_t count) {
   return r;
 }
 
-// Runs f without the interpreter lock; false, or an error of torch's (the call
-// has to fail in the Python path too), leaves the call to the Python path.
+// Sets the Python error a failed library call has in the Python path.
+void set_error(const char* fn, glv_status st) {
+  PyObject* const mod = PyImport_ImportModule("paper_2312_02756_amd._lib");
+  PyObject* const r = mod ? PyObject_CallMethod(mod, "check", "si", fn, (int)st) : nullptr;  // raises GlvError
+  Py_XDECREF(r);
+  Py_XDECREF(mod);
+}
+
+// Runs f, which returns the status of library call fn, without the interpreter
+// lock; whether it is done.  If not, the caller returns not_done(): the error
+// of a call that failed on the GPU, or None where the library refused it.
+// Errors of torch's (memory, hooks) are the caller's to raise as they are.
 template <typename F>
-bool unlocked(F f) {
-  NoGil g;
-  try {
-    return f();
-  } catch (const c10::Error&) {
-    return false;
+bool unlocked(const char* fn, F f) {
+  glv_status st;
+  {
+    NoGil g;
+    st = f();
   }
+  if (st == GLV_EHIP) set_error(fn, st);
+  return st == GLV_OK;
+}
+
+PyObject* not_done() {
+  if (PyErr_Occurred()) return nullptr;
+  Py_RETURN_NONE;
 }
 
 // ------------------------------------------------------------ entry points
@@ -221,12 +240,12 @@ PyObject* py_mass(PyObject*, PyObject* const* args, Py_ssize_t na) {
       !counter_arg(args[4], k.device, &fb))
     Py_RETURN_NONE;
   Tensor m;
-  if (!unlocked([&] {
+  if (!unlocked("glv_invariant_mass", [&] {
         m = at::empty({k.n}, k.opts());
         return glv_invariant_mass(k.dt(), co, mo, k.n, Ptrs<4>(c).in(), Ptrs<4>(c, 4).in(), m.data_ptr(),
-                                  counter_ptr(fb), stream_of(k.device)) == GLV_OK;
+                                  counter_ptr(fb), stream_of(k.device));
       }))
-    Py_RETURN_NONE;
+    return not_done();
   return wrap(m);
   END_HANDLE_TH_ERRORS
 }
@@ -254,13 +273,13 @@ PyObject* py_mass_histogram(PyObject*, PyObject* const* args, Py_ssize_t na) {
       Py_RETURN_NONE;
     counts = *t;
   }
-  if (!unlocked([&] {
+  if (!unlocked("glv_invariant_mass_histogram", [&] {
         if (!counts.defined()) counts = at::zeros({bins + 2}, k.opts().dtype(at::kLong));
         return glv_invariant_mass_histogram(k.dt(), co, mo, k.n, Ptrs<4>(c).in(), Ptrs<4>(c, 4).in(), lo, hi, bins,
                                             reinterpret_cast<unsigned long long*>(counts.data_ptr()),
-                                            counter_ptr(fb), stream_of(k.device)) == GLV_OK;
+                                            counter_ptr(fb), stream_of(k.device));
       }))
-    Py_RETURN_NONE;
+    return not_done();
   return wrap(counts);
   END_HANDLE_TH_ERRORS
 }
@@ -277,12 +296,12 @@ PyObject* py_boost(PyObject*, PyObject* const* args, Py_ssize_t na) {
   for (size_t i = 4; i < 7; ++i)
     if (c[i].numel() != (bs ? k.n : 1)) Py_RETURN_NONE;
   Cols y;
-  if (!unlocked([&] {
+  if (!unlocked("glv_boost", [&] {
         y = empties(k, k.n, 4);
         return glv_boost(k.dt(), k.n, Ptrs<4>(c).in(), Ptrs<3>(c, 4).in(), bs, Ptrs<4>(y).out(),
-                         stream_of(k.device)) == GLV_OK;
+                         stream_of(k.device));
       }))
-    Py_RETURN_NONE;
+    return not_done();
   return wrap_tuple(y, 0, 4);
   END_HANDLE_TH_ERRORS
 }
@@ -297,11 +316,11 @@ PyObject* py_convert(PyObject*, PyObject* const* args, Py_ssize_t na) {
       !coords_arg(args[2], &to))
     Py_RETURN_NONE;
   Cols y;
-  if (!unlocked([&] {
+  if (!unlocked("glv_convert", [&] {
         y = empties(k, k.n, 4);
-        return glv_convert(k.dt(), from, to, k.n, Ptrs<4>(c).in(), Ptrs<4>(y).out(), stream_of(k.device)) == GLV_OK;
+        return glv_convert(k.dt(), from, to, k.n, Ptrs<4>(c).in(), Ptrs<4>(y).out(), stream_of(k.device));
       }))
-    Py_RETURN_NONE;
+    return not_done();
   return wrap_tuple(y, 0, 4);
   END_HANDLE_TH_ERRORS
 }
@@ -321,26 +340,24 @@ PyObject* py_transform(PyObject*, PyObject* const* args, Py_ssize_t na) {
   for (const Tensor& t : m)
     if (t.numel() != (stride ? k.n : 1)) Py_RETURN_NONE;
   Cols y;
-  if (!unlocked([&] {
+  if (!unlocked(np == 16 ? "glv_lorentz_transform" : np == 9 ? "glv_rotate" : "glv_rotate_axis_angle", [&] {
         y = empties(k, k.n, 4);
         const Ptrs<4> x(c), o(y);
         void* const s = stream_of(k.device);
-        if (np == 16)
-          return glv_lorentz_transform(k.dt(), k.n, x.in(), Ptrs<16>(m).in(), stride, o.out(), s) == GLV_OK;
-        if (np == 9) return glv_rotate(k.dt(), k.n, x.in(), Ptrs<9>(m).in(), stride, o.out(), s) == GLV_OK;
-        return glv_rotate_axis_angle(k.dt(), k.n, x.in(), Ptrs<4>(m).in(), stride, o.out(), s) == GLV_OK;
+        if (np == 16) return glv_lorentz_transform(k.dt(), k.n, x.in(), Ptrs<16>(m).in(), stride, o.out(), s);
+        if (np == 9) return glv_rotate(k.dt(), k.n, x.in(), Ptrs<9>(m).in(), stride, o.out(), s);
+        return glv_rotate_axis_angle(k.dt(), k.n, x.in(), Ptrs<4>(m).in(), stride, o.out(), s);
       }))
-    Py_RETURN_NONE;
+    return not_done();
   return wrap_tuple(y, 0, 4);
   END_HANDLE_TH_ERRORS
 }
 
-// The pair offsets of `off`, or an undefined tensor.
-Tensor pair_offsets(const Tensor& off) {
-  Tensor po = at::empty({off.numel()}, off.options());
-  const glv_status st = glv_pair_offsets(off.numel() - 1, off.data_ptr<int64_t>(), po.data_ptr<int64_t>(),
-                                         stream_of(off.device()));
-  return st == GLV_OK ? po : Tensor();
+// The pair offsets of `off`.
+glv_status pair_offsets(const Tensor& off, Tensor* po) {
+  *po = at::empty({off.numel()}, off.options());
+  return glv_pair_offsets(off.numel() - 1, off.data_ptr<int64_t>(), po->data_ptr<int64_t>(),
+                          stream_of(off.device()));
 }
 
 // pair_offsets(offsets)
@@ -351,11 +368,7 @@ PyObject* py_pair_offsets(PyObject*, PyObject* const* args, Py_ssize_t na) {
   if (!t || t->scalar_type() != at::kLong || t->dim() != 1 || !t->is_contiguous() || t->numel() < 1) Py_RETURN_NONE;
   const Tensor off = *t;
   Tensor po;
-  if (!unlocked([&] {
-        po = pair_offsets(off);
-        return po.defined();
-      }))
-    Py_RETURN_NONE;
+  if (!unlocked("glv_pair_offsets", [&] { return pair_offsets(off, &po); })) return not_done();
   return wrap(po);
   END_HANDLE_TH_ERRORS
 }
@@ -379,17 +392,14 @@ struct Events {
     }
     return true;
   }
-  bool need_pairs() {
-    if (!po.defined()) po = pair_offsets(off);
-    return po.defined();
-  }
+  glv_status need_pairs() { return po.defined() ? GLV_OK : pair_offsets(off, &po); }
   const int64_t* offs() const { return off.data_ptr<int64_t>(); }
   const int64_t* pos() const { return po.defined() ? po.data_ptr<int64_t>() : nullptr; }
 };
 
 // Totals (4), event masses and pair masses, in this order.
-bool reduce_events(Events& e, glv_coords co, glv_mode mo, bool wt, bool we, bool wp, int64_t n_pairs,
-                   unsigned long long* fb, Cols* out) {
+glv_status reduce_events(Events& e, glv_coords co, glv_mode mo, bool wt, bool we, bool wp, int64_t n_pairs,
+                         unsigned long long* fb, Cols* out) {
   const int64_t ne = e.ne();
   Cols t = empties(e.k, ne, wt ? 4 : 0);
   Tensor em, pm;
@@ -400,14 +410,14 @@ bool reduce_events(Events& e, glv_coords co, glv_mode mo, bool wt, bool we, bool
   }
   std::array<void*, 4> tp{};
   for (size_t i = 0; i < t.size(); ++i) tp[i] = t[i].data_ptr();
-  if (glv_event_reduce(e.k.dt(), co, mo, ne, e.offs(), e.pos(), Ptrs<4>(e.p).in(), wt ? tp.data() : nullptr,
-                       we ? em.data_ptr() : nullptr, wp ? pm.data_ptr() : nullptr, fb, nullptr,
-                       stream_of(e.k.device)) != GLV_OK)
-    return false;
+  const glv_status st = glv_event_reduce(e.k.dt(), co, mo, ne, e.offs(), e.pos(), Ptrs<4>(e.p).in(),
+                                         wt ? tp.data() : nullptr, we ? em.data_ptr() : nullptr,
+                                         wp ? pm.data_ptr() : nullptr, fb, nullptr, stream_of(e.k.device));
+  if (st != GLV_OK) return st;
   *out = std::move(t);
   if (we) out->push_back(em);
   if (wp) out->push_back(pm);
-  return true;
+  return GLV_OK;
 }
 
 bool flag_arg(PyObject* o, bool* b) {
@@ -430,11 +440,14 @@ PyObject* py_event_reduce(PyObject*, PyObject* const* args, Py_ssize_t na) {
       !counter_arg(args[8], e.k.device, &fb) || (args[9] != Py_None && (!int_arg(args[9], &np) || np < 0)))
     Py_RETURN_NONE;
   Cols out;
-  if (!unlocked([&] {
-        if ((wp || (mo == GLV_COMPENSATED && we)) && !e.need_pairs()) return false;
+  if (!unlocked("glv_event_reduce", [&] {
+        if (wp || (mo == GLV_COMPENSATED && we)) {
+          const glv_status st = e.need_pairs();
+          if (st != GLV_OK) return st;
+        }
         return reduce_events(e, co, mo, wt, we, wp, np, counter_ptr(fb), &out);
       }))
-    Py_RETURN_NONE;
+    return not_done();
   PyObject* r = PyTuple_New(3);
   size_t at = 0;
   auto put = [&](Py_ssize_t i, PyObject* o) { PyTuple_SET_ITEM(r, i, o); };
@@ -462,15 +475,16 @@ PyObject* py_best_pair(PyObject*, PyObject* const* args, Py_ssize_t na) {
       !coords_arg(args[4], &co) || !mode_arg(args[5], &mo) || !counter_arg(args[6], e.k.device, &fb))
     Py_RETURN_NONE;
   Cols out(2);
-  if (!unlocked([&] {
-        if (!e.need_pairs()) return false;
+  if (!unlocked("glv_event_reduce_best_pair", [&] {
+        const glv_status st = e.need_pairs();
+        if (st != GLV_OK) return st;
         out[0] = at::empty({e.ne()}, e.off.options());
         out[1] = at::empty({e.ne()}, e.k.opts());
         return glv_event_reduce_best_pair(e.k.dt(), co, mo, e.ne(), e.offs(), e.pos(), Ptrs<4>(e.p).in(), target,
                                           out[0].data_ptr<int64_t>(), out[1].data_ptr(), counter_ptr(fb), nullptr,
-                                          stream_of(e.k.device)) == GLV_OK;
+                                          stream_of(e.k.device));
       }))
-    Py_RETURN_NONE;
+    return not_done();
   return wrap_tuple(out, 0, 2);
   END_HANDLE_TH_ERRORS
 }
@@ -515,8 +529,11 @@ PyObject* py_event_reduce_bwd(PyObject*, PyObject* const* args, Py_ssize_t na) {
     (i == 4 ? gem : gpm) = *t;
   }
   Cols g;
-  if (!unlocked([&] {
-        if (gpm.defined() && !e.need_pairs()) return false;
+  if (!unlocked("glv_event_reduce_bwd", [&] {
+        if (gpm.defined()) {
+          const glv_status st = e.need_pairs();
+          if (st != GLV_OK) return st;
+        }
         g = empties(e.k, e.k.n, 4);
         std::array<void*, 4> tp{};
         for (size_t i = 0; i < gt.size(); ++i) tp[i] = gt[i].data_ptr();
@@ -524,19 +541,25 @@ PyObject* py_event_reduce_bwd(PyObject*, PyObject* const* args, Py_ssize_t na) {
         return glv_event_reduce_bwd(e.k.dt(), co, e.ne(), e.offs(), e.pos(), Ptrs<4>(e.p).in(),
                                     gt.empty() ? nullptr : tp.data(), gem.defined() ? gem.data_ptr() : nullptr,
                                     gpm.defined() ? gpm.data_ptr() : nullptr, Ptrs<4>(g).out(), t ? &*t : nullptr,
-                                    stream_of(e.k.device)) == GLV_OK;
+                                    stream_of(e.k.device));
       }))
-    Py_RETURN_NONE;
+    return not_done();
   return wrap_tuple(g, 0, 4);
   END_HANDLE_TH_ERRORS
 }
 
 // --------------------------------------------------------------- autograd
 
-// The status of a library call inside an autograd node.
+// The status of a library call inside an autograd node, without the
+// interpreter lock: a failure raises what it does in the Python path.
 void check(const char* fn, glv_status st) {
-  TORCH_CHECK(st == GLV_OK, fn, ": ", glv_status_str(st),
-              st == GLV_EHIP ? " (hip error " + std::to_string(glv_last_hip_error()) + ")" : std::string());
+  if (st == GLV_OK) return;
+  python_error e;
+  const PyGILState_STATE gil = PyGILState_Ensure();
+  set_error(fn, st);
+  e.persist();  // the error leaves the thread's state before that may go
+  PyGILState_Release(gil);
+  throw e;
 }
 
 Kind kind_of(const Tensor& t) { return {t.scalar_type(), t.device(), t.numel()}; }
@@ -618,8 +641,7 @@ struct EventReduce : torch::autograd::Function<EventReduce> {
     e.off = off;
     e.po = po;
     Cols out;
-    TORCH_CHECK(reduce_events(e, (glv_coords)co, GLV_PLAIN, true, true, true, -1, nullptr, &out),
-                "glv_event_reduce failed (hip error ", glv_last_hip_error(), ")");
+    check("glv_event_reduce", reduce_events(e, (glv_coords)co, GLV_PLAIN, true, true, true, -1, nullptr, &out));
     ctx->saved_data["coords"] = co;
     variable_list keep{off, po};
     keep.insert(keep.end(), e.p.begin(), e.p.end());
@@ -654,11 +676,11 @@ PyObject* py_autograd_mass(PyObject*, PyObject* const* args, Py_ssize_t na) {
       (mo == GLV_COMPENSATED && co != GLV_PTETAPHIM) || !no_tangents(c))
     Py_RETURN_NONE;
   Tensor m;
-  if (!unlocked([&] {
+  if (!unlocked("glv_invariant_mass", [&] {
         m = InvariantMass::apply((int64_t)co, (int64_t)mo, at::TensorList(c));
-        return true;
+        return GLV_OK;
       }))
-    Py_RETURN_NONE;
+    return not_done();
   return wrap(m);
   END_HANDLE_TH_ERRORS
 }
@@ -675,11 +697,11 @@ PyObject* py_autograd_boost(PyObject*, PyObject* const* args, Py_ssize_t na) {
   for (size_t i = 4; i < 7; ++i)
     if (c[i].numel() != nb) Py_RETURN_NONE;
   Cols y;
-  if (!unlocked([&] {
+  if (!unlocked("glv_boost", [&] {
         y = Boost::apply(at::TensorList(c));
-        return true;
+        return GLV_OK;
       }))
-    Py_RETURN_NONE;
+    return not_done();
   return wrap_tuple(y, 0, 4);
   END_HANDLE_TH_ERRORS
 }
@@ -693,12 +715,12 @@ PyObject* py_autograd_event_reduce(PyObject*, PyObject* const* args, Py_ssize_t 
       !no_tangents(e.p))
     Py_RETURN_NONE;
   Cols out;
-  if (!unlocked([&] {
-        if (!e.need_pairs()) return false;
-        out = EventReduce::apply((int64_t)co, e.off, e.po, at::TensorList(e.p));
-        return true;
+  if (!unlocked("glv_pair_offsets", [&] {
+        const glv_status st = e.need_pairs();
+        if (st == GLV_OK) out = EventReduce::apply((int64_t)co, e.off, e.po, at::TensorList(e.p));
+        return st;
       }))
-    Py_RETURN_NONE;
+    return not_done();
   return wrap_tuple(out, 0, 6);
   END_HANDLE_TH_ERRORS
 }
