@@ -453,6 +453,17 @@ glv_status glv_autotune_event_reduce(glv_dtype dtype, glv_coords coords, glv_mod
  * *out. */
 glv_status glv_current_tiling(glv_dtype dtype, glv_coords coords, glv_mode mode, glv_tiling* out);
 
+/* The sizes for a call of n_events events with n_pairs pairs in all
+ * (pair_offsets[n_events]), written to *out: the tuned choice if there is one,
+ * otherwise what the library finds best.  backward = 0: glv_event_reduce in
+ * `mode`; 1: glv_event_reduce_bwd (mode ignored).  n_pairs: 0 for a call that
+ * evaluates no pairs (without pair upstreams), -1 where it is not known, which
+ * gives the sizes of a call whose tiling is NULL.  A caller of the reverse mode
+ * that knows n_pairs passes *out as the tiling: the call itself learns it only
+ * on the device, too late to choose by it.  Needs no GPU. */
+glv_status glv_call_tiling(glv_dtype dtype, glv_coords coords, glv_mode mode, int32_t backward, int64_t n_events,
+                           int64_t n_pairs, glv_tiling* out);
+
 /* The same for glv_event_reduce_bwd, with its arguments (grad_p ends up
  * holding a valid result); the choice becomes the current backward one for
  * (device, dtype, coords).  Synchronises `stream`. */

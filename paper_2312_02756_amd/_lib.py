@@ -31,7 +31,7 @@ EXPORTS = (
     "glv_lorentz_transform_bwd", "glv_rotate", "glv_rotate_bwd", "glv_rotate_axis_angle",
     "glv_rotate_axis_angle_bwd", "glv_mass_histogram", "glv_event_best_pair", "glv_invariant_mass_comp_bwd",
     "glv_autotune_key", "glv_autotune_lookup", "glv_autotune_forget", "glv_invariant_mass_histogram",
-    "glv_event_reduce_best_pair",
+    "glv_event_reduce_best_pair", "glv_call_tiling",
 )
 
 
@@ -77,6 +77,7 @@ _SIGS = {
                                      _vp],
     "glv_event_reduce_best_pair": [_i, _i, _i, _i64, _vp, _vp, _vp, ctypes.c_double, _vp, _vp, _vp, _vp, _vp],
     "glv_current_tiling_bwd": [_i, _i, _vp],
+    "glv_call_tiling": [_i, _i, _i, ctypes.c_int32, _i64, _i64, _vp],
     "glv_autotune_key": [_i, _i, _i, ctypes.c_int32, _i64, _vp, ctypes.c_char_p, _i64, _vp],
     "glv_autotune_lookup": [_i, _i, _i, ctypes.c_int32, _i64, _vp, _vp, _vp, _vp],
     "glv_autotune_forget": [],

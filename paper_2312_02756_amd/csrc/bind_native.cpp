@@ -489,27 +489,11 @@ PyObject* py_best_pair(PyObject*, PyObject* const* args, Py_ssize_t na) {
   END_HANDLE_TH_ERRORS
 }
 
-// The tiling of the reverse mode for ne events of n_pairs pairs where none is
-// given or tuned (the library knows the mean size of the events only on the
-// device).  Its own choice suits events of up to about 9 particles (FP64, many
-// events: 13); larger ones fill the particles of a chunk only with more pairs.
-// Library's choice / this one: 60,000 FP64 events of 14 particles 69 / 55 us, of
-// 26 230 / 144; FP32 51 / 41 and 176 / 74; 500,000 events of 14, FP64 336 / 316,
-// FP32 235 / 197, but FP64 of 10 193 / 210; 20,000 FP32 events with a long tail
-// (8 on average) 43 / 31.  From about 50 particles on most events are left to the
-// large-event launch.
+// The tiling of the reverse mode of ne events with n_pairs pair upstreams.
 std::optional<glv_tiling> bwd_tiling(glv_dtype dt, glv_coords co, int64_t ne, int64_t n_pairs) {
-  constexpr glv_tiling dflt{128, 64, 128, 512};
-  glv_tiling cur;
-  if (ne < 1 || glv_current_tiling_bwd(dt, co, &cur) != GLV_OK) return std::nullopt;
-  if (cur.block != dflt.block || cur.events_per_tile != dflt.events_per_tile ||
-      cur.lds_particles != dflt.lds_particles || cur.pairs_per_round != dflt.pairs_per_round)
-    return std::nullopt;  // tuned
-  const double mean = (double)n_pairs / (double)ne;
-  if (mean < (dt == GLV_F64 && ne > 131072 ? 90.0 : 45.0)) return std::nullopt;
-  if (mean > 1250.0) return glv_tiling{0, 0, 0, 512};
-  if (ne <= 32768 && mean < 150.0) return glv_tiling{0, 0, 0, 1536};
-  return glv_tiling{256, 0, 256, dt == GLV_F32 || mean > 350.0 ? 4096 : 2048};
+  glv_tiling t;
+  if (glv_call_tiling(dt, co, GLV_PLAIN, 1, ne, n_pairs, &t) != GLV_OK) return std::nullopt;
+  return t;
 }
 
 // event_reduce_bwd(p, offsets, pair_offsets, grad_total, grad_event_m, grad_pair_m, coords)

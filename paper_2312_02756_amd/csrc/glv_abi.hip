@@ -237,6 +237,53 @@ glv::Tiling pair_tiling_bwd(glv_dtype dt, int64_t ne) {
   return t;
 }
 
+// The sizes of a reverse-mode call that neither gives a tiling nor has a tuned
+// one.  n_pairs: its pair upstreams, 0 without them, -1 where their number is
+// not known (the calls themselves know it only on the device).
+//
+// Where it is known, the mean pairs per event decide.  pair_tiling_bwd suits
+// events of up to about 9 particles (FP64, many events: 13); larger ones fill
+// the particles of a chunk only with more pairs.  pair_tiling_bwd / these sizes:
+// 60,000 FP64 events of 14 particles 69 / 55 us, of 26 230 / 144; FP32 51 / 41
+// and 176 / 74; 500,000 events of 14, FP64 336 / 316, FP32 235 / 197, but FP64
+// of 10 193 / 210; 20,000 FP32 events with a long tail (8 on average) 43 / 31.
+// From about 50 particles on most events are left to the large-event launch.
+glv::Tiling untuned_tiling_bwd(glv_dtype dt, int64_t ne, int64_t n_pairs) {
+  glv::Tiling t = n_pairs ? pair_tiling_bwd(dt, ne) : default_tiling_bwd(dt);
+  const double mean = ne > 0 ? (double)n_pairs / (double)ne : 0.0;
+  if (mean >= (dt == GLV_F64 && ne > 131072 ? 90.0 : 45.0)) {
+    t = default_tiling_bwd(dt);
+    if (mean > 1250.0) {
+      t.pairs_per_round = 512;
+    } else if (ne <= 32768 && mean < 150.0) {
+      t.pairs_per_round = 1536;
+    } else {
+      t.block = t.lds_particles = 256;
+      t.pairs_per_round = dt == GLV_F32 || mean > 350.0 ? 4096 : 2048;
+    }
+  }
+  t.events_per_tile = tile_events(t.events_per_tile, ne);
+  return t;
+}
+
+// The same for the forward (n_pairs: 0 where the call evaluates no pairs).
+glv::Tiling untuned_tiling(glv_dtype dt, glv_mode mode, int64_t ne, int64_t n_pairs, bool best) {
+  glv::Tiling t = n_pairs ? pair_tiling(dt, mode, best) : best ? default_tiling_best() : default_tiling(dt, mode);
+  t.events_per_tile = tile_events(t.events_per_tile, ne);
+  return t;
+}
+
+// The tuned choice of this process for these arguments, if there is one.
+bool tuned_tiling(glv_dtype dt, glv_coords co, glv_mode mode, bool bwd, glv::Tiling* out) {
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) dev = 0;
+  std::lock_guard<std::mutex> lk(g_tile_mu);
+  const auto it = g_tiles.find({dev, (int)dt, (int)co, bwd ? kBwdKey : (int)mode});
+  if (it == g_tiles.end()) return false;
+  *out = it->second;
+  return true;
+}
+
 constexpr size_t kMaxLds = 64 * 1024;
 
 bool block_ok(int b) { return (b == 64 || b == 128 || b == 256 || b == 512) && b <= glv::kMaxBlock; }
@@ -256,18 +303,12 @@ bool tiling_valid(glv_dtype dt, glv_mode mode, bool bwd, const glv::Tiling& t, b
 glv_status resolve_tiling(glv_dtype dt, glv_coords co, glv_mode mode, const glv_tiling* user, bool bwd, int64_t ne,
                           bool pairs, glv::Tiling* out, bool best = false) {
   const bool given = user && (user->block || user->events_per_tile || user->lds_particles || user->pairs_per_round);
-  glv::Tiling base = pairs && !given ? (bwd ? pair_tiling_bwd(dt, ne) : pair_tiling(dt, mode, best))
-                     : bwd           ? default_tiling_bwd(dt)
-                     : best          ? default_tiling_best()
-                                     : default_tiling(dt, mode);
-  base.events_per_tile = tile_events(base.events_per_tile, ne);
-  if (!best) {
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess) dev = 0;
-    std::lock_guard<std::mutex> lk(g_tile_mu);
-    auto it = g_tiles.find({dev, (int)dt, (int)co, bwd ? kBwdKey : (int)mode});
-    if (it != g_tiles.end()) base = it->second;
-  }
+  glv::Tiling base;
+  if (!given)
+    base = bwd ? untuned_tiling_bwd(dt, ne, pairs ? -1 : 0) : untuned_tiling(dt, mode, ne, pairs ? -1 : 0, best);
+  else
+    base = bwd ? untuned_tiling_bwd(dt, ne, 0) : untuned_tiling(dt, mode, ne, 0, best);
+  if (!best) tuned_tiling(dt, co, mode, bwd, &base);
   if (user) {
     if (user->block) base.block = user->block;
     if (user->events_per_tile) base.events_per_tile = user->events_per_tile;
@@ -887,6 +928,23 @@ glv_status glv_current_tiling_bwd(glv_dtype dt, glv_coords co, glv_tiling* out) 
   glv::Tiling t;
   glv_status st = resolve_tiling(dt, co, GLV_PLAIN, nullptr, true, INT64_MAX, false, &t);
   if (st != GLV_OK) return st;
+  write_tiling(t, out);
+  return GLV_OK;
+}
+
+glv_status glv_call_tiling(glv_dtype dt, glv_coords co, glv_mode mode, int32_t backward, int64_t ne, int64_t n_pairs,
+                           glv_tiling* out) {
+  if (!dtype_ok(dt)) return GLV_EINVAL_DTYPE;
+  if (!coords_ok(co)) return GLV_EINVAL_COORDS;
+  const bool bwd = backward != 0;
+  if (bwd) mode = GLV_PLAIN;
+  glv_status ms = mode_ok(mode, co);
+  if (ms != GLV_OK) return ms;
+  if (ne < 0 || n_pairs < -1) return GLV_EINVAL_SIZE;
+  if (!out) return GLV_EINVAL_NULL;
+  glv::Tiling t;
+  if (!tuned_tiling(dt, co, mode, bwd, &t))
+    t = bwd ? untuned_tiling_bwd(dt, ne, n_pairs) : untuned_tiling(dt, mode, ne, n_pairs, false);
   write_tiling(t, out);
   return GLV_OK;
 }

@@ -479,6 +479,8 @@ def glv_event_reduce_bwd(p, offsets, pair_offsets=None, grad_total=None, grad_ev
     gem = _cols([grad_event_m], ne, dt, dev, "grad_event_m")[0] if grad_event_m is not None else None
     gpm = _cols([grad_pair_m], None, dt, dev, "grad_pair_m")[0] if grad_pair_m is not None else None
     gp = tuple(torch.empty(n, dtype=dt, device=dev) for _ in range(4))
+    if tiling is None and gpm is not None:
+        tiling = glv_call_tiling(ne, gpm.numel(), dt, coords, backward=True)
     lib = _lib.load()
     gtp = P4(*[t.data_ptr() for t in gt]) if gt else None
     if total is not None:
@@ -556,6 +558,18 @@ def glv_current_tiling_bwd(dtype=torch.float64, coords="PtEtaPhiM"):
     t = glv_tiling()
     check("glv_current_tiling_bwd", _lib.load().glv_current_tiling_bwd(_dtype_code(dtype), _coords_code(coords),
                                                                        ctypes.byref(t)))
+    return _as_tuple(t)
+
+
+def glv_call_tiling(n_events, n_pairs=None, dtype=torch.float64, coords="PtEtaPhiM", mode="plain", backward=False):
+    """The sizes a call of ``n_events`` events is launched with where it is
+    given no tiling (``n_pairs``: their pairs, None if not known, 0 for a call
+    that evaluates none), as (block, events_per_tile, lds_particles,
+    pairs_per_round)."""
+    t = glv_tiling()
+    check("glv_call_tiling",
+          _lib.load().glv_call_tiling(_dtype_code(dtype), _coords_code(coords), _mode_code(mode), int(bool(backward)),
+                                      n_events, -1 if n_pairs is None else n_pairs, ctypes.byref(t)))
     return _as_tuple(t)
 
 

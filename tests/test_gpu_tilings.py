@@ -1,0 +1,73 @@
+"""Which sizes the calls of the Python entry points are launched with."""
+
+import json
+
+import numpy as np
+import pytest
+import torch
+
+import synth
+from gpu_util import gpu
+from test_gpu_jagged import _off
+
+pytestmark = pytest.mark.gpu
+
+glv = pytest.importorskip("paper_2312_02756_amd.glv")
+
+
+@pytest.fixture
+def cache(tmp_path, monkeypatch):
+    path = tmp_path / "tune.json"
+    monkeypatch.setenv("GLV_AUTOTUNE_CACHE", str(path))
+    glv.glv_autotune_forget()
+    yield path
+    glv.glv_autotune_forget()
+
+
+def _tune(path, tiling, off, **kw):
+    """Makes `tiling` the tuned choice of this process for the events of `off`."""
+    key = glv.glv_autotune_key(off, **kw)
+    path.write_text(json.dumps({"format": "glv-autotune-1", "entries": [{"key": key, "tiling": list(tiling)}]}))
+    assert glv.glv_autotune_lookup(off, **kw) == (tiling, True)
+
+
+def _events(counts, seed, dtype):
+    off = np.concatenate([[0], np.cumsum(counts)]).astype(np.int64)
+    g = synth.rng(seed)
+    p, _ = synth.pairs_generic(g, int(off[-1]))
+    n_pairs = int((counts * (counts - 1) // 2).sum())
+    return _off(off), gpu(p, dtype), gpu([g.standard_normal(n_pairs)], dtype)[0]
+
+
+def test_tuned_reverse_mode_is_taken_also_where_it_equals_the_default(cache):
+    """Events of 40 particles: 780 pairs, more than the default stages, so
+    that the launch they are done in, and the order of their sums, tells the
+    sizes apart."""
+    off, p, up = _events(np.full(400, 40), 980, torch.float32)
+    po = glv.glv_pair_offsets(off)
+    run = lambda t: glv.glv_event_reduce_bwd(p, off, po, grad_pair_m=up, tiling=t)  # noqa: E731
+    default = (128, 64, 128, 512)
+    want, untuned = run(default), run(None)
+    assert not all(torch.equal(a, b) for a, b in zip(untuned, want))
+    _tune(cache, default, off, dtype=torch.float32, backward=True)
+    assert all(torch.equal(a, b) for a, b in zip(run(None), want))
+    leaves = tuple(c.clone().requires_grad_(True) for c in p)
+    from paper_2312_02756_amd import autograd as ag
+    pm = ag.event_reduce(leaves, off, po)[2]
+    assert all(torch.equal(a, b) for a, b in zip(torch.autograd.grad(pm, leaves, up), want))
+
+
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+def test_every_route_takes_the_same_sizes(dtype):
+    """The native binding, the Python functions behind it and a C call given
+    glv_call_tiling's sizes: the same gradients, bit for bit."""
+    glv.glv_autotune_forget()
+    for mean in (5, 12, 20, 40, 60):
+        counts = synth.rng(981 + mean).poisson(mean, 3000)
+        off, p, up = _events(counts, 982 + mean, dtype)
+        po = glv.glv_pair_offsets(off)
+        t = glv.glv_call_tiling(3000, up.numel(), dtype, backward=True)
+        want = glv.glv_event_reduce_bwd(p, off, po, grad_pair_m=up, tiling=t)
+        native = glv.glv_event_reduce_bwd(p, off, po, grad_pair_m=up)
+        python = glv.glv_event_reduce_bwd(p, off, po, grad_pair_m=up, coords=1)  # declined by the binding
+        assert all(torch.equal(a, b) and torch.equal(a, c) for a, b, c in zip(want, native, python))

@@ -1,0 +1,83 @@
+"""Tilings on the host (no GPU needed): what a call is launched with, and what
+it refuses, through the C ABI.  Pointers are fake addresses; no call below
+reaches a launch."""
+
+import ctypes
+import json
+
+import pytest
+import torch
+
+from paper_2312_02756_amd import _lib, glv
+
+OK, NULL, SIZE, DTYPE, COORDS, MODE, TILING = 0, 1, 2, 3, 4, 5, 9
+DEFAULT_BWD = (128, 64, 128, 512)
+
+
+@pytest.fixture(scope="module")
+def lib():
+    return _lib.load()
+
+
+@pytest.fixture
+def cache(tmp_path, monkeypatch):
+    path = tmp_path / "tune.json"
+    monkeypatch.setenv("GLV_AUTOTUNE_CACHE", str(path))
+    glv.glv_autotune_forget()
+    yield path
+    glv.glv_autotune_forget()
+
+
+def _tune(path, tiling, **kw):
+    """Makes `tiling` the tuned choice of this process."""
+    key = glv.glv_autotune_key(None, **kw)
+    path.write_text(json.dumps({"format": "glv-autotune-1", "entries": [{"key": key, "tiling": list(tiling)}]}))
+    assert glv.glv_autotune_lookup(None, **kw) == (tiling, True)
+
+
+def test_call_tiling_validation(lib):
+    t = _lib.glv_tiling()
+    f, out = lib.glv_call_tiling, ctypes.byref(t)
+    assert f(3, 1, 0, 0, 10, 10, out) == DTYPE
+    assert f(2, 4, 0, 0, 10, 10, out) == COORDS
+    assert f(2, 0, 1, 0, 10, 10, out) == MODE
+    assert f(2, 0, 1, 1, 10, 10, out) == OK      # the reverse mode has one mode
+    assert f(2, 1, 0, 0, -1, 10, out) == SIZE
+    assert f(2, 1, 0, 0, 10, -2, out) == SIZE
+    assert f(2, 1, 0, 0, 10, 10, None) == NULL
+
+
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+def test_untuned_sizes_are_valid_and_follow_the_events(lib, dtype):
+    """Every choice fits the LDS, and few events get small tiles."""
+    glv.glv_autotune_forget()
+    code, es = (2, 8) if dtype == torch.float64 else (1, 4)
+    for ne in (0, 1, 8192, 8193, 32768, 131072, 131073, 1 << 19, (1 << 19) + 1, 1 << 21):
+        for mean in (None, 0, 1, 10, 44, 46, 89, 91, 149, 151, 349, 351, 1249, 1251, 100000):
+            n_pairs = None if mean is None else mean * ne
+            for mode in ("plain", "compensated"):
+                t = _lib.glv_tiling(*glv.glv_call_tiling(ne, n_pairs, dtype, "PtEtaPhiM", mode))
+                # no events: the tiling is checked and nothing is launched
+                assert lib.glv_event_reduce(code, 1, mode == "compensated", 0, None, None, None, None, None, None, None,
+                                            ctypes.byref(t), None) == OK
+            block, epb, cap, q = glv.glv_call_tiling(ne, n_pairs, dtype, backward=True)
+            assert block in (64, 128, 256, 512) and 1 <= epb <= 64 and 64 <= cap <= block and q % 64 == 0 and q <= 4096
+            assert cap * (4 * es + 2) + (q + 2) * es + epb * (4.5 * es + 32) + 64 <= 65536
+            assert epb <= (4 if ne <= 8192 else 64)
+
+
+def test_pairs_decide_the_reverse_mode_where_they_are_known(cache):
+    assert glv.glv_call_tiling(500000, 500000 * 98, torch.float32, backward=True) == (256, 64, 256, 4096)
+    assert glv.glv_call_tiling(60000, 60000 * 325, torch.float64, backward=True) == (256, 16, 256, 2048)
+    assert glv.glv_call_tiling(500000, 500000 * 32, torch.float32, backward=True) == glv.glv_call_tiling(
+        500000, None, torch.float32, backward=True)
+    assert glv.glv_call_tiling(500000, 0, torch.float32, backward=True) == DEFAULT_BWD  # no pair upstreams
+
+
+@pytest.mark.parametrize("tiling", [DEFAULT_BWD, (64, 16, 64, 256)])
+def test_a_tuned_choice_is_taken_whatever_it_is(cache, tiling):
+    """Also one that equals the built-in default."""
+    _tune(cache, tiling, backward=True)
+    for n_pairs in (None, 60000 * 325):
+        assert glv.glv_call_tiling(60000, n_pairs, backward=True) == tiling
+    assert glv.glv_call_tiling(60000, 60000 * 325, torch.float32, backward=True) != tiling  # another key
