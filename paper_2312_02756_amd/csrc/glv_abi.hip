@@ -222,16 +222,19 @@ glv::Tiling pair_tiling(glv_dtype dt, glv_mode mode, bool best) {
 
 // The same for the reverse mode with pair upstreams: room for 768 of them, so
 // that a chunk of small events is more often ended by its particles than by its
-// pairs, and in FP64 tiles of 32 events.  Default above -> these, 500,000 events,
-// FP64 of 8 particles 157 -> 155 us, of 14 467 -> 336, of 8 on average with a long
-// tail (gamma of shape 2) 315 -> 240; FP32 103 -> 98, 323 -> 235 and 226 -> 171;
-// 60,000 events of 14: FP64 94 -> 69, FP32 72 -> 51.  2^20 FP64 events of 8 take
-// 298 us at the default and 305 at these.  More upstreams would keep larger
-// events in the first launch, also in calls of large events only: at 1,536, 20,000
-// FP32 events of 60 particles take 231 us instead of 191.
-glv::Tiling pair_tiling_bwd(glv_dtype dt, int64_t ne) {
+// pairs, and in FP64 tiles of 32 events, beside which their LDS still leaves
+// twelve workgroups per CU.  Default above -> these, 500,000 events, FP64 of 8
+// particles 157 -> 154 us, of 14 466 -> 338, of 8 on average with a long tail
+// (gamma of shape 2) 313 -> 244; FP32 103 -> 98, 323 -> 235 and 226 -> 171;
+// 60,000 events of 14: FP64 94 -> 69, FP32 72 -> 51.  2^20 FP64 events: of 12
+// 634 -> 501, of 10 443 -> 385, long tail 565 -> 449, of 9 365 -> 349, of 8 299
+// -> 303, of 6 210 -> 222, of 5 170 -> 199.  (64 events and 640 upstreams lose
+// less on small events, 5: 176, and gain less on the others, 12: 577.)  More
+// upstreams would keep larger events in the first launch, also in calls of
+// large events only: at 1,536, 20,000 FP32 events of 60 particles take 231 us
+// instead of 191.
+glv::Tiling pair_tiling_bwd(glv_dtype dt) {
   glv::Tiling t = default_tiling_bwd(dt);
-  if (dt == GLV_F64 && ne > (1 << 19)) return t;
   if (dt == GLV_F64) t.events_per_tile = 32;
   t.pairs_per_round = 768;
   return t;
@@ -248,9 +251,16 @@ glv::Tiling pair_tiling_bwd(glv_dtype dt, int64_t ne) {
 // and 176 / 74; 500,000 events of 14, FP64 336 / 316, FP32 235 / 197, but FP64
 // of 10 193 / 210; 20,000 FP32 events with a long tail (8 on average) 43 / 31.
 // From about 50 particles on most events are left to the large-event launch.
+// Many small FP64 events take the default's tiles of 64: below 36 pairs on
+// average their particles fill its chunks with 512 upstreams, and from about
+// three rounds of such tiles on the GPU (8,192 of them) smaller ones no longer
+// even out the last round.  Default / pair_tiling_bwd, 400,000 events of 8
+// particles 128 / 123 us, of 6 92 / 91; 600,000 184 / 182 and 126 / 129; 2^20 299 /
+// 303 and 210 / 222, but of 9 (40 pairs) 365 / 349.
 glv::Tiling untuned_tiling_bwd(glv_dtype dt, int64_t ne, int64_t n_pairs) {
-  glv::Tiling t = n_pairs ? pair_tiling_bwd(dt, ne) : default_tiling_bwd(dt);
+  glv::Tiling t = n_pairs ? pair_tiling_bwd(dt) : default_tiling_bwd(dt);
   const double mean = ne > 0 ? (double)n_pairs / (double)ne : 0.0;
+  if (dt == GLV_F64 && n_pairs > 0 && mean < 36.0 && ne > 64 * 8192) t = default_tiling_bwd(dt);
   if (mean >= (dt == GLV_F64 && ne > 131072 ? 90.0 : 45.0)) {
     t = default_tiling_bwd(dt);
     if (mean > 1250.0) {

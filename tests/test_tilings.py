@@ -74,6 +74,17 @@ def test_pairs_decide_the_reverse_mode_where_they_are_known(cache):
     assert glv.glv_call_tiling(500000, 0, torch.float32, backward=True) == DEFAULT_BWD  # no pair upstreams
 
 
+def test_reverse_mode_of_many_fp64_events(cache):
+    """The number of events alone does not take the room for pairs away: only
+    small events, which do not need it, have less of it."""
+    for ne in (500000, 600000, 1 << 21):
+        assert glv.glv_call_tiling(ne, None, backward=True) == (128, 32, 128, 768)
+        assert glv.glv_call_tiling(ne, 48 * ne, backward=True) == (128, 32, 128, 768)
+        assert glv.glv_call_tiling(ne, 98 * ne, backward=True) == (256, 64, 256, 2048)
+    assert glv.glv_call_tiling(500000, 32 * 500000, backward=True) == (128, 32, 128, 768)
+    assert glv.glv_call_tiling(600000, 32 * 600000, backward=True) == DEFAULT_BWD
+
+
 @pytest.mark.parametrize("tiling", [DEFAULT_BWD, (64, 16, 64, 256)])
 def test_a_tuned_choice_is_taken_whatever_it_is(cache, tiling):
     """Also one that equals the built-in default."""
