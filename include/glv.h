@@ -489,10 +489,12 @@ glv_status glv_autotune_key(glv_dtype dtype, glv_coords coords, glv_mode mode, i
  * (serving loops): looks the dataset's key up in this process's choices and
  * in the cache file.  Found: *found = 1.  Not found -- no such entry, no
  * GLV_AUTOTUNE_CACHE, a missing or a corrupt file -- *found = 0, the
- * built-in default, a warning on stderr, and still GLV_OK.  Either way the
- * result becomes the current choice (as glv_autotune_event_reduce /
- * glv_autotune_event_reduce_bwd would make it) and is written to *out if not
- * NULL.  Synchronises `stream` when it reads offsets (n_events > 0). */
+ * built-in default, a warning on stderr, and still GLV_OK.  The result is
+ * written to *out if not NULL.  A tiling that was found becomes the current
+ * choice (as glv_autotune_event_reduce / glv_autotune_event_reduce_bwd would
+ * make it); without one there is none any more for these arguments, and calls
+ * are launched as untuned ones (see glv_call_tiling).  Synchronises `stream`
+ * when it reads offsets (n_events > 0). */
 glv_status glv_autotune_lookup(glv_dtype dtype, glv_coords coords, glv_mode mode, int32_t backward,
                                int64_t n_events, const int64_t* offsets, glv_tiling* out, int32_t* found,
                                void* stream);

@@ -92,6 +92,14 @@ void remember_tiling(glv_dtype dt, glv_coords co, int mode_key, const glv::Tilin
   g_tiles[{dev, (int)dt, (int)co, mode_key}] = t;
 }
 
+// Calls with these arguments are untuned from here on.
+void forget_tiling(glv_dtype dt, glv_coords co, int mode_key) {
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) dev = 0;
+  std::lock_guard<std::mutex> lk(g_tile_mu);
+  g_tiles.erase({dev, (int)dt, (int)co, mode_key});
+}
+
 void write_tiling(const glv::Tiling& t, glv_tiling* out) {
   out->block = t.block;
   out->events_per_tile = t.events_per_tile;
@@ -533,8 +541,12 @@ glv_status autotune_common(glv_dtype dt, glv_coords co, glv_mode mode, bool bwd,
     if (!glv::tune::save(path, entries))
       fprintf(stderr, "glv: could not write the autotune cache %s\n", path);
   }
-  if (hit || work) glv::tune::remember_process(key, chosen);
-  remember_tiling(dt, co, bwd ? kBwdKey : (int)mode, chosen);
+  if (hit || work) {
+    glv::tune::remember_process(key, chosen);
+    remember_tiling(dt, co, bwd ? kBwdKey : (int)mode, chosen);
+  } else {  // nothing was timed: no choice
+    forget_tiling(dt, co, bwd ? kBwdKey : (int)mode);
+  }
   if (best) write_tiling(chosen, best);
   return GLV_OK;
 }
@@ -1064,7 +1076,10 @@ glv_status glv_autotune_lookup(glv_dtype dt, glv_coords co, glv_mode mode, int32
     }
     if (hit) glv::tune::remember_process(key, t);
   }
-  remember_tiling(dt, co, bwd ? kBwdKey : (int)mode, t);
+  if (hit)
+    remember_tiling(dt, co, bwd ? kBwdKey : (int)mode, t);
+  else  // the default is no tuned choice: it would stand in the way of the sizes for the call's own events
+    forget_tiling(dt, co, bwd ? kBwdKey : (int)mode);
   if (out) write_tiling(t, out);
   if (found) *found = hit ? 1 : 0;
   return GLV_OK;

@@ -592,9 +592,9 @@ def glv_autotune_key(offsets, dtype=torch.float64, coords="PtEtaPhiM", mode="pla
 
 def glv_autotune_lookup(offsets, dtype=torch.float64, coords="PtEtaPhiM", mode="plain", backward=False):
     """The tuned tiling of this dataset from this process's choices or the
-    GLV_AUTOTUNE_CACHE file, without timing: (tiling, found); not found gives
-    the default tiling (and a warning on stderr).  Either becomes the current
-    choice."""
+    GLV_AUTOTUNE_CACHE file, without timing: (tiling, found).  A tiling that is
+    found becomes the current choice; not found gives the default tiling (and
+    a warning on stderr) and leaves later calls untuned."""
     t = glv_tiling()
     found = ctypes.c_int32(0)
     dt, co, mo, bw, ne, po, st = _key_args(dtype, coords, mode, backward, offsets)

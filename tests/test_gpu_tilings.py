@@ -71,3 +71,15 @@ def test_every_route_takes_the_same_sizes(dtype):
         native = glv.glv_event_reduce_bwd(p, off, po, grad_pair_m=up)
         python = glv.glv_event_reduce_bwd(p, off, po, grad_pair_m=up, coords=1)  # declined by the binding
         assert all(torch.equal(a, b) and torch.equal(a, c) for a, b, c in zip(want, native, python))
+
+
+@pytest.mark.parametrize("backward", [False, True])
+def test_a_miss_drops_the_choice_made_for_other_events(cache, backward):
+    off, _, _ = _events(np.full(400, 40), 983, torch.float64)
+    other, _, _ = _events(np.full(400, 5), 984, torch.float64)
+    untuned = glv.glv_call_tiling(400, 400 * 10, backward=backward)
+    _tune(cache, (64, 16, 64, 256), off, backward=backward)
+    assert glv.glv_call_tiling(400, 400 * 10, backward=backward) == (64, 16, 64, 256)
+    assert glv.glv_autotune_lookup(other, backward=backward)[1] is False
+    assert glv.glv_call_tiling(400, 400 * 10, backward=backward) == untuned
+    assert glv.glv_autotune_lookup(off, backward=backward) == ((64, 16, 64, 256), True)

@@ -92,3 +92,24 @@ def test_a_tuned_choice_is_taken_whatever_it_is(cache, tiling):
     for n_pairs in (None, 60000 * 325):
         assert glv.glv_call_tiling(60000, n_pairs, backward=True) == tiling
     assert glv.glv_call_tiling(60000, 60000 * 325, torch.float32, backward=True) != tiling  # another key
+
+
+@pytest.mark.parametrize("backward", [False, True])
+def test_a_lookup_that_finds_nothing_leaves_the_call_untuned(cache, backward):
+    """It reports the default, as ever, and the call takes what an untuned one
+    does."""
+    kw = dict(dtype=torch.float64, backward=backward)
+    untuned = glv.glv_call_tiling(1000, 98000, **kw)
+    current = glv.glv_current_tiling_bwd if backward else glv.glv_current_tiling
+    default = current(torch.float64)
+    assert untuned != default and untuned[1] == 4
+    assert glv.glv_autotune_lookup(None, **kw) == (default, False)
+    assert glv.glv_call_tiling(1000, 98000, **kw) == untuned
+    _tune(cache, (64, 16, 64, 128), **kw)
+    assert glv.glv_call_tiling(1000, 98000, **kw) == (64, 16, 64, 128)
+    cache.unlink()
+    glv.glv_autotune_forget()
+    _tune(cache, (64, 16, 64, 128), **kw)
+    cache.write_text(json.dumps({"format": "glv-autotune-1", "entries": []}))
+    assert glv.glv_autotune_lookup(None, **dict(kw, dtype=torch.float32)) != ((64, 16, 64, 128), True)
+    assert glv.glv_call_tiling(1000, 98000, **kw) == (64, 16, 64, 128)  # another key's miss changes nothing
