@@ -990,7 +990,8 @@ glv_status glv_autotune_event_reduce(glv_dtype dt, glv_coords co, glv_mode mode,
           glv::Tiling t{b, e, c, q};
           if (tiling_valid(dt, mode, false, t)) cands.push_back(t);
         }
-  cands.push_back(pair_tiling(dt, mode, false));  // what an untuned call takes, but for few events
+  // what an untuned call takes, so that a tuned one is no slower
+  cands.push_back(untuned_tiling(dt, mode, ne, pm || (mode == GLV_COMPENSATED && em) ? -1 : 0, false));
   auto launch = [&](const glv::Tiling& t) {
     return glv::launch_event_reduce(dt, co, mode, ne, off, poff, p, total, em, pm, nullptr, t, s);
   };
@@ -1018,6 +1019,16 @@ glv_status glv_autotune_event_reduce_bwd(glv_dtype dt, glv_coords co, int64_t ne
         glv::Tiling t{b, e, b, std::min(k * b, 4096)};
         if (tiling_valid(dt, GLV_PLAIN, true, t)) cands.push_back(t);
       }
+  // what an untuned call takes with and without its number of pairs known, so
+  // that a tuned one is no slower
+  int64_t n_pairs = 0;
+  if (gpair && ne > 0) {
+    hipError_t err = hipMemcpyAsync(&n_pairs, poff + ne, sizeof n_pairs, hipMemcpyDeviceToHost, s);
+    if (err == hipSuccess) err = hipStreamSynchronize(s);
+    if (err != hipSuccess) return hip_status(err);
+    cands.push_back(untuned_tiling_bwd(dt, ne, -1));
+  }
+  cands.push_back(untuned_tiling_bwd(dt, ne, n_pairs));
   auto launch = [&](const glv::Tiling& t) {
     return glv::launch_event_reduce_bwd(dt, co, ne, off, poff, p, gt, gem, gpair, gp, t, s);
   };

@@ -83,3 +83,16 @@ def test_a_miss_drops_the_choice_made_for_other_events(cache, backward):
     assert glv.glv_autotune_lookup(other, backward=backward)[1] is False
     assert glv.glv_call_tiling(400, 400 * 10, backward=backward) == untuned
     assert glv.glv_autotune_lookup(off, backward=backward) == ((64, 16, 64, 256), True)
+
+
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+def test_autotuning_tries_what_an_untuned_call_takes(cache, dtype):
+    """1,000 events of 22 particles: tiles of four events, which only the
+    untuned choice has, spread them over several times as much of the GPU as
+    the smallest of the other candidates (16)."""
+    cache.unlink(missing_ok=True)
+    off, p, up = _events(np.full(1000, 22), 985, dtype)
+    assert glv.glv_autotune_event_reduce(p, off) == glv.glv_current_tiling(dtype)
+    assert glv.glv_current_tiling(dtype)[1] == 4
+    best = glv.glv_autotune_event_reduce_bwd(p, off, grad_pair_m=up)
+    assert best == glv.glv_current_tiling_bwd(dtype) and best[1] == 4
