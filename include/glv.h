@@ -126,11 +126,13 @@ typedef enum glv_mode { GLV_PLAIN = 0, GLV_COMPENSATED = 1 } glv_mode;
  *   pairs_per_round  pair upstreams staged at once, a multiple of 64 in
  *                    64 .. 4096 (events with more pairs, or more particles
  *                    than the staging capacity, go to the second launch)
- * Fields set to 0 take the library's current choice (the autotuned one if
- * glv_autotune_event_reduce, or glv_autotune_event_reduce_bwd for the
- * backward, ran for this device/dtype/coords/mode, otherwise a built-in
- * default).  A call that neither gives a field nor has an autotuned choice is
- * launched as the library finds best for its type, mode and number of events.
+ * A field set to 0 beside others that are given takes the library's current
+ * choice (the autotuned one if glv_autotune_event_reduce, or
+ * glv_autotune_event_reduce_bwd for the backward, ran for this
+ * device/dtype/coords/mode, otherwise a built-in default), whatever the number
+ * of events.  No tiling, or one of four zeros, takes the autotuned choice or,
+ * without one, the sizes the library finds best for the call's type, mode and
+ * number of events (glv_call_tiling).
  * A tiling whose workgroup would need more than 64 KiB of LDS is rejected with
  * GLV_EINVAL_TILING: per wavefront the forward keeps 4 values
  * per staged particle (12 in the compensated mode), per pair of a round one
@@ -448,9 +450,10 @@ glv_status glv_autotune_event_reduce(glv_dtype dtype, glv_coords coords, glv_mod
                                      void* const total[4], void* event_m, void* pair_m,
                                      glv_tiling* best, void* stream);
 
-/* The tiling whose fields glv_event_reduce would take for these arguments
- * where a call leaves them 0 (the current choice or the default), written to
- * *out. */
+/* The tiling whose fields glv_event_reduce takes for these arguments where a
+ * call gives some and leaves others 0 (the autotuned choice or the built-in
+ * default), written to *out.  glv_call_tiling has the sizes of a call that
+ * gives none. */
 glv_status glv_current_tiling(glv_dtype dtype, glv_coords coords, glv_mode mode, glv_tiling* out);
 
 /* The sizes for a call of n_events events with n_pairs pairs in all
@@ -473,8 +476,8 @@ glv_status glv_autotune_event_reduce_bwd(glv_dtype dtype, glv_coords coords, int
                                          const void* grad_event_m, const void* grad_pair_m,
                                          void* const grad_p[4], glv_tiling* best, void* stream);
 
-/* The tiling glv_event_reduce_bwd would use (the current backward choice or
- * the default), written to *out. */
+/* The same for glv_event_reduce_bwd (the autotuned backward choice or the
+ * built-in default), written to *out. */
 glv_status glv_current_tiling_bwd(glv_dtype dtype, glv_coords coords, glv_tiling* out);
 
 /* The cache key of a dataset (NUL-terminated, into buf of len bytes;

@@ -318,6 +318,9 @@ bool tiling_valid(glv_dtype dt, glv_mode mode, bool bwd, const glv::Tiling& t, b
 
 // Resolve a user tiling (fields 0 = current choice) for ne events and validate
 // it; pairs: the call evaluates pairs (the reverse mode: has pair upstreams).
+// Only a call that gives no field is launched by its number of events and
+// whether it evaluates pairs: a field left 0 beside given ones is the tuned or
+// default one, so that the same tiling is taken or refused whatever the events.
 glv_status resolve_tiling(glv_dtype dt, glv_coords co, glv_mode mode, const glv_tiling* user, bool bwd, int64_t ne,
                           bool pairs, glv::Tiling* out, bool best = false) {
   const bool given = user && (user->block || user->events_per_tile || user->lds_particles || user->pairs_per_round);
@@ -325,7 +328,7 @@ glv_status resolve_tiling(glv_dtype dt, glv_coords co, glv_mode mode, const glv_
   if (!given)
     base = bwd ? untuned_tiling_bwd(dt, ne, pairs ? -1 : 0) : untuned_tiling(dt, mode, ne, pairs ? -1 : 0, best);
   else
-    base = bwd ? untuned_tiling_bwd(dt, ne, 0) : untuned_tiling(dt, mode, ne, 0, best);
+    base = bwd ? default_tiling_bwd(dt) : best ? default_tiling_best() : default_tiling(dt, mode);
   if (!best) tuned_tiling(dt, co, mode, bwd, &base);
   if (user) {
     if (user->block) base.block = user->block;

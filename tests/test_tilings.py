@@ -113,3 +113,25 @@ def test_a_lookup_that_finds_nothing_leaves_the_call_untuned(cache, backward):
     cache.write_text(json.dumps({"format": "glv-autotune-1", "entries": []}))
     assert glv.glv_autotune_lookup(None, **dict(kw, dtype=torch.float32)) != ((64, 16, 64, 128), True)
     assert glv.glv_call_tiling(1000, 98000, **kw) == (64, 16, 64, 128)  # another key's miss changes nothing
+
+
+GiB = 1 << 30
+
+
+def _cols(base):
+    return _lib.P4(*[base + i * GiB for i in range(4)])
+
+
+@pytest.mark.parametrize("ne", [1, 10, 8192, 32768, 131072, 1 << 20])
+def test_partly_given_tilings_are_refused_at_any_number_of_events(lib, ne):
+    """A field left 0 beside given ones is the current choice whatever the
+    number of events, so that a tiling that asks for too much LDS with it is
+    refused for few events as for many."""
+    glv.glv_autotune_forget()
+    off, po, p, t, em, pm = 16 * GiB, 32 * GiB, _cols(100 * GiB), _cols(140 * GiB), 180 * GiB, 190 * GiB
+    for bad in ((512, 0, 140, 448), (512, 0, 128, 512), (256, 0, 300, 896)):
+        b = ctypes.byref(_lib.glv_tiling(*bad))
+        assert lib.glv_event_reduce(2, 1, 0, ne, off, po, p, t, em, pm, None, b, None) == TILING, bad
+    for bad in ((512, 0, 208, 64), (256, 0, 464, 64)):
+        b = ctypes.byref(_lib.glv_tiling(*bad))
+        assert lib.glv_event_reduce_best_pair(2, 1, 0, ne, off, po, p, 91.0, 140 * GiB, em, None, b, None) == TILING, bad
