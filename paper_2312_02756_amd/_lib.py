@@ -7,6 +7,7 @@ fallback: if the library is missing the import of this module fails.
 
 import ctypes
 import os
+import warnings
 
 import torch  # noqa: F401  (load order: torch's HIP runtime first)
 
@@ -112,6 +113,18 @@ def load():
     return _lib
 
 
+class _Declines:
+    """Stands in for a native binding that is not there: leaves every call to
+    the Python path, which makes the same library calls through ctypes."""
+
+    def __getattr__(self, name):
+        return self._decline
+
+    @staticmethod
+    def _decline(*args):
+        return None
+
+
 _native = None
 
 
@@ -124,8 +137,10 @@ def native():
         try:
             from . import _native as mod
         except ImportError as e:
-            raise RuntimeError("the native binding is missing or does not fit this torch: build it with "
-                               "`python -m paper_2312_02756_amd.build`; there is no fallback path") from e
+            warnings.warn(f"the native binding is missing or does not fit this torch ({e}): calls take several times "
+                          "as long on the host; build it with `python -m paper_2312_02756_amd.build`", RuntimeWarning,
+                          stacklevel=3)
+            mod = _Declines()
         _native = mod
     return _native
 
