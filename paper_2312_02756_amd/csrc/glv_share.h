@@ -1,4 +1,4 @@
-// Which pairs and which blocks of events fall to a workgroup of the
+// Which pairs, events and blocks of events fall to a workgroup of the
 // large-event launches.  Plain integer arithmetic without any include but the
 // integer types, so that it runs on the host as well.
 #pragma once
@@ -24,6 +24,22 @@ __host__ __device__ __forceinline__ Share pair_share(int64_t nq, int64_t min_pai
 // pairs there are.  (Not a bound beyond them: the ends of shares are added to
 // below.)
 __host__ __device__ __forceinline__ Share whole_share(int64_t nq) { return {0, nq}; }
+
+// Where the events themselves are dealt out: the first event that thread tid of
+// workgroup `index` of `grid` looks at.  kDealt neighbours (one cache line of
+// their offsets) go to one workgroup, the next kDealt to the next; a workgroup
+// of B threads takes B / kDealt such rows of the grid at a time, at another
+// place in each (B / kDealt is a power of two that divides the grid), so that
+// sizes that repeat with the row do not meet the same workgroup again.  Its next
+// events are B grid further on.
+constexpr int kDealt = 16;
+template <int B>
+__host__ __device__ __forceinline__ int dealt_event(int tid, int index, int grid) {
+  constexpr int kRows = B / kDealt;
+  const int row = tid / kDealt;
+  const int place = index + (row * 5 & (kRows - 1)) * (grid / kRows);  // below 2 grid
+  return (row * grid + (place < grid ? place : place - grid)) * kDealt + tid % kDealt;
+}
 
 // The reverse mode's blocks of 32 particles [k0, k1) of an event of n > 1
 // particles, first pair po and `pairs` pairs that stand in a share: block k

@@ -23,7 +23,8 @@
 // The reverse mode stages one particle per thread of a workgroup (below).
 // Events of many particles, whose pairs are too many for one wavefront or
 // one workgroup's staging, are left to a second launch in either direction,
-// which shares all their pairs out evenly (k_event_dense, k_event_bwd_dense);
+// which shares their pairs, or the events, out evenly (k_event_dense,
+// k_event_bwd_dense);
 // on collider-sized events it only reads the pair offsets.
 #include "glv_device.h"
 #include "glv_launch.h"
@@ -1120,9 +1121,11 @@ __global__ __launch_bounds__(kMaxBlock, (fwd_waves<T, MODE, BEST>())) void k_eve
 //     to as many workgroups as its size asks for;
 //   * K sums (compensated event mass) and the best pair need one result per
 //     event: a workgroup takes every event whose first pair lies in its run.
-// A workgroup finds its first event by a 256-ary search of pair_offsets, reads
-// the sizes of blockDim events at a time and lists the ones that are its
-// business.  It stages runs of listed events (kDenseCap particles) in LDS,
+// (From kShareByEvents events on the events are dealt out instead, and one that
+// is larger than all others together is one workgroup's in any mode.)
+// A workgroup finds its first event by interpolation or a search of
+// pair_offsets, reads the sizes of several thousand events at a time
+// (scan_share) and lists the ones that are its business.  It stages runs of listed events (kDenseCap particles) in LDS,
 // converted once per workgroup, and deals the staged events' pairs to its
 // wavefronts as equal runs of the folded pairs (Folded), 64 per step, so that
 // the masses go out as runs of consecutive addresses straight from registers
@@ -1171,9 +1174,11 @@ struct EventList {
   int cnt[B / 64];
 };
 
-// Lists the threads' events with `mine`, in order; returns their number.
+// Lists the threads' events with `mine`, in order, event `index` of the slice;
+// returns their number.
 template <int B>
-__device__ __forceinline__ int list_events(EventList<B>& L, bool mine, int64_t lo, int n, int64_t po, bool flag) {
+__device__ __forceinline__ int list_events(EventList<B>& L, bool mine, int index, int64_t lo, int n, int64_t po,
+                                           bool flag) {
   const int lane = (int)threadIdx.x & 63, wid = (int)threadIdx.x >> 6;
   const uint64_t mk = __ballot(mine);
   __syncthreads();  // the previous list is no longer read
@@ -1191,7 +1196,7 @@ __device__ __forceinline__ int list_events(EventList<B>& L, bool mine, int64_t l
     L.lo[at] = lo;
     L.n[at] = n;
     L.po[at] = po;
-    L.e[at] = ((int)threadIdx.x << 1) | (flag ? 1 : 0);
+    L.e[at] = (index << 1) | (flag ? 1 : 0);
   }
   __syncthreads();
   return __builtin_amdgcn_readfirstlane(all);
@@ -1201,14 +1206,25 @@ __device__ __forceinline__ int list_events(EventList<B>& L, bool mine, int64_t l
 // all events, whose scan is pair_offsets, cut into one equal run [q0, q1) per
 // workgroup, of at least min_pairs.  Neighbouring runs go to workgroups of the
 // same XCD (dispatched round-robin over the eight), whose L2 then serves the
-// pair offsets both read.  From kShareByEvents events on, hundreds per
-// workgroup, equal numbers of events are equal work enough, and every pair
-// offset is read once (7.0 us against 4.6 on 2^20 small events).
-__device__ __forceinline__ int share_index() {  // the grid is a multiple of 8
-  return (int)((blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3));
+// pair offsets both read.  From kShareByEvents events on the events themselves
+// are dealt out (dealt_event), and every pair offset is read once: 5.0 us
+// against 6.9 on 2^19 small FP64 events, 6.9 against 15.0 on 2^21, where shares of
+// pairs need windows of several times their events.  Large events, also
+// neighbouring ones, then go to many workgroups, but each one whole to its own
+// (2^18 events, 1,000 neighbours of 100 particles among them: forward 112 us, best
+// pair 119, reverse mode 299; 939, 1895 and 3066 where a workgroup took a run of
+// 256 events; 54, 49 and 102 with shares of pairs, one event fewer.  One event of
+// 3,000 particles: 3.0 ms, 83 us with shares).
+// GRID, the number of workgroups, is a constant of each kernel: the divisions by
+// it were a third of the instructions of a launch that finds nothing.
+template <int GRID>
+__device__ __forceinline__ int share_index() {
+  static_assert(GRID % 8 == 0, "one run of shares per XCD");
+  return (int)((blockIdx.x & 7) * (GRID / 8) + (blockIdx.x >> 3));
 }
+template <int GRID>
 __device__ __forceinline__ Share my_share(int64_t nq, int64_t min_pairs) {
-  return pair_share(nq, min_pairs, gridDim.x, share_index());
+  return pair_share(nq, min_pairs, GRID, share_index<GRID>());
 }
 
 constexpr int64_t kShareByEvents = 1 << 18;
@@ -1242,59 +1258,92 @@ __device__ __forceinline__ int64_t search_share(const int64_t* __restrict__ poff
   return lo;
 }
 
+// What a thread sees of its events of a window, one per slice: event e of slice
+// sl is wins + at + sl STEP.
+template <int SLICES, int STEP, typename Seen>
+struct Window {
+  // the low words do where the window holds fewer than 2^32 pairs (half the
+  // registers); the list looks at the whole offsets
+  unsigned po[SLICES], pe[SLICES];
+  Seen seen[SLICES];
+
+  // SKIP: slices past the last event are not read
+  template <bool SKIP, typename Peek>
+  __device__ __forceinline__ void read(const int64_t* __restrict__ poff, int64_t wins, int at, int last, Peek peek) {
+#pragma unroll
+    for (int sl = 0; sl < SLICES; ++sl) {
+      if constexpr (SKIP) {
+        po[sl] = pe[sl] = 0;
+        seen[sl] = {};
+        if (sl > 0 && sl * STEP > last) continue;
+      }
+      const int t = min(sl * STEP + at, last);
+      const unsigned* const low = reinterpret_cast<const unsigned*>(poff + wins);
+      po[sl] = low[2 * t];
+      pe[sl] = low[2 * t + 2];
+      seen[sl] = peek(wins + t);
+    }
+  }
+
+  // Bit sl: the thread's event of slice sl is picked, or has to be looked at whole.
+  template <typename Pick>
+  __device__ __forceinline__ unsigned picked(int64_t at0, int64_t at1, int64_t end, int at, int last, Pick pick) const {
+    const bool wide = at1 - at0 >= ((int64_t)1 << 32);
+    unsigned some = 0;
+#pragma unroll
+    for (int sl = 0; sl < SLICES; ++sl) {
+      const int64_t q = at0 + (unsigned)(po[sl] - (unsigned)at0);
+      if (sl * STEP + at <= last && (wide || (q < end && pick(seen[sl], q, (int64_t)(unsigned)(pe[sl] - po[sl])))))
+        some |= 1u << sl;
+    }
+    return some;
+  }
+};
+
 // Calls body(win, listed) with the whole workgroup for every slice of B events
-// from event win on that has events e with pick(peek(e), po, d) in its share
-// (first pair po, d pairs; peek reads what else tells), listed in L in order
-// with flag(d).  The pair offsets of kSlices slices are read at once, first
-// around the place where the share would begin if all events had the same
-// number of pairs (sizes drawn alike stay within the slack of about 1000
-// events either way for a million events), so that where no event is the
-// workgroup's business, as on small events, the scan costs one memory
+// that has events e with pick(peek(e), po, d) in its share (first pair po, d
+// pairs; peek reads what else tells), listed in L in order with their index
+// from event win on and flag(d).  The pair offsets of kSlices slices are read
+// at once, first around the place where the share would begin if all events
+// had the same number of pairs (sizes drawn alike stay within the slack of
+// about 1000 events either way for a million events), so that where no event
+// is the workgroup's business, as on small events, the scan costs one memory
 // latency; a share that begins outside is searched for.
-template <int B, typename Peek, typename Pick, typename Flag, typename Body>
+template <int B, int GRID, typename Peek, typename Pick, typename Flag, typename Body>
 __device__ __forceinline__ void scan_share(const int64_t* __restrict__ off, const int64_t* __restrict__ poff,
                                            int64_t ne, int64_t min_pairs, EventList<B>& L, Share* share, Peek peek,
                                            Pick pick, Flag flag, Body body) {
   constexpr int kSlices = B == 256 ? 12 : 8;
   constexpr int64_t kWin = (int64_t)kSlices * B;
+  using Seen = decltype(peek((int64_t)0));
   const int tid = (int)threadIdx.x;
-  int64_t wins, stop;  // events still to look at
-  int tries;
+  const bool dealt = ne >= kShareByEvents;
+  int64_t wins = 0;  // the window's first event
+  int tries = 0;
   bool more = true;
-  if (ne >= kShareByEvents) {
-    const int64_t per = (ne + gridDim.x - 1) / (int64_t)gridDim.x;
-    wins = share_index() * per;
-    stop = min(wins + per, ne);
-    if (wins >= stop) return;
-    *share = whole_share(poff[ne]);
-    tries = 0;
-  } else {
+  if (!dealt) {
     // where equal events would put the share, if it is no smaller than the rest
-    wins = (int64_t)((double)ne * share_index() / (double)gridDim.x) - (kWin - ne / (int64_t)gridDim.x) / 2;
+    wins = ne * share_index<GRID>() / GRID - (kWin - ne / GRID) / 2;
     wins = max((int64_t)0, min(wins, ne - kWin));
-    stop = ne;
     tries = 2;
   }
   while (more) {
-    const int64_t wend = min(wins + kWin, stop);
+    const int64_t span = dealt ? kWin * GRID : kWin;  // events the window reaches over
+    const int64_t wend = min(wins + span, ne);
     const int64_t at0 = poff[wins], at1 = poff[wend], nq = poff[ne];
-    unsigned some = 0;  // bit s: this thread's event of slice s
-    {
-      // the low words do where the slices hold fewer than 2^32 pairs (half
-      // the registers); the list below looks at the whole offsets
-      const unsigned* const low = reinterpret_cast<const unsigned*>(poff + wins);
-      const int last = (int)(wend - wins) - 1;
-      unsigned po[kSlices], pe[kSlices];
-      decltype(peek(wins)) seen[kSlices];
-#pragma unroll
-      for (int sl = 0; sl < kSlices; ++sl) {
-        const int t = min(sl * B + tid, last);
-        po[sl] = low[2 * t];
-        pe[sl] = low[2 * t + 2];
-        seen[sl] = peek(wins + t);
-      }
+    const int last = (int)(wend - wins) - 1;
+    unsigned some;
+    if (dealt) {
+      const int at = dealt_event<B>(tid, share_index<GRID>(), GRID);
+      Window<kSlices, B * GRID, Seen> w;
+      w.template read<true>(poff, wins, at, last, peek);
+      *share = whole_share(nq);
+      some = w.picked(at0, at1, nq, at, last, pick);
+    } else {
+      Window<kSlices, B, Seen> w;
+      w.template read<false>(poff, wins, tid, last, peek);
       if (tries) {
-        *share = my_share(nq, min_pairs);
+        *share = my_share<GRID>(nq, min_pairs);
         if (share->q0 >= share->q1) return;
         if (at0 > share->q0 || at1 <= share->q0) {  // begins elsewhere
           if (--tries && share->q1 - share->q0 == min_pairs) {  // few pairs: shares larger than the grid's equal ones
@@ -1308,22 +1357,16 @@ __device__ __forceinline__ void scan_share(const int64_t* __restrict__ off, cons
         }
         tries = 0;
       }
-      more = wend < stop && at1 < share->q1;
-      const bool wide = at1 - at0 >= ((int64_t)1 << 32);
-#pragma unroll
-      for (int sl = 0; sl < kSlices; ++sl) {
-        const int t = sl * B + tid;
-        const int64_t at = at0 + (unsigned)(po[sl] - (unsigned)at0);
-        if (t <= last && (wide || (at < share->q1 && pick(seen[sl], at, (int64_t)(unsigned)(pe[sl] - po[sl])))))
-          some |= 1u << sl;
-      }
+      some = w.picked(at0, at1, share->q1, tid, last, pick);
     }
+    more = wend < ne && at1 < share->q1;
     if (__syncthreads_or(some != 0)) {
 #pragma unroll 1
       for (int sl = 0; sl < kSlices; ++sl) {
         bool mine = (some >> sl) & 1u;
         if (!__syncthreads_or(mine)) continue;
-        const int64_t e = wins + sl * B + tid;
+        const int index = dealt ? dealt_event<B>(tid, share_index<GRID>(), GRID) + sl * (B * GRID) : tid + sl * B;
+        const int64_t e = wins + index;
         int64_t first = 0, n = 0, po = 0, d = 0;
         if (mine) {
           first = off[e];
@@ -1332,11 +1375,11 @@ __device__ __forceinline__ void scan_share(const int64_t* __restrict__ off, cons
           d = npairs(n);
           mine = po < share->q1 && pick(peek(e), po, d);
         }
-        const int listed = list_events<B>(L, mine, first, (int)n, po, mine && flag(d));
-        body(wins + sl * B, listed);
+        const int listed = list_events<B>(L, mine, index, first, (int)n, po, mine && flag(d));
+        body(wins, listed);
       }
     }
-    wins += kWin;
+    wins += span;
   }
 }
 
@@ -1525,12 +1568,12 @@ __global__ __launch_bounds__((dense_block<MODE, BEST>()),
 
   Share sh;
   const int64_t small_pairs = npairs(small_events<T, MODE, BEST>(A.poff, A.ne, A.small));
-  // the event's place for a redo mark (without event masses or best pairs: its first pair mass)
+  // the event's place for a redo mark (without event masses or best pairs: its
+  // first pair mass, looked at by picked(); what is read here is then unused, but
+  // read without a branch, so that all slices' reads are in flight together)
+  const T* const marks = A.event_m ? A.event_m : BEST ? A.best_m : reinterpret_cast<const T*>(A.poff);
   auto peek = [&](int64_t e) -> float {
-    if constexpr (kDefer) {
-      if (A.event_m) return A.event_m[e];
-      if (BEST) return A.best_m[e];
-    }
+    if constexpr (kDefer) return marks[e];
     return 0.0f;
   };
   // whether an event (first pair po, d pairs) is this workgroup's business
@@ -1781,7 +1824,7 @@ __global__ __launch_bounds__((dense_block<MODE, BEST>()),
       li += nc;
     }
   };
-  scan_share<B>(A.off, A.poff, A.ne, kDenseMinPairs, L, &sh, peek, picked, redo_only, work);
+  scan_share<B, dense_grid<MODE, BEST>()>(A.off, A.poff, A.ne, kDenseMinPairs, L, &sh, peek, picked, redo_only, work);
   if constexpr (kDefer) {
     if (A.fallback) {
 #pragma unroll
@@ -2433,7 +2476,7 @@ __global__ __launch_bounds__(256, (sizeof(T) == 4 ? 4 : 3)) void k_event_bwd_den
   Share sh;
   int turn = 0;  // the workgroup's blocks so far: its wavefronts take them in turn
   const int64_t cap_pairs = npairs(A.cap);
-  scan_share<B>(
+  scan_share<B, kBwdGrid>(
       A.off, A.poff, A.ne, kDenseMinPairs, L, &sh,
       [](int64_t) { return 0; },
       [&](int, int64_t po, int64_t d) { return po + d > sh.q0 && (d > A.qcap || d > cap_pairs); },

@@ -27,10 +27,11 @@ def _bwd_into(out, p, off, po, up):
 
 
 @pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
-@pytest.mark.parametrize("ne", [(1 << 18) - 1, 1 << 18, (1 << 18) + 1])
+@pytest.mark.parametrize("ne", [(1 << 18) - 1, 1 << 18, (1 << 18) + 1, (3 << 20) + 77])
 def test_large_events_first_and_last_of_many(ne, dtype):
     """Large events at the start, together in the middle and at the end of
-    calls on either side of 2^18 events: every output of theirs is written, and
+    calls on either side of 2^18 events, and of more events than the threads
+    of a launch look at in one go: every output of theirs is written, and
     bitwise as in a call of their own."""
     g = synth.rng(820)
     large = np.array([96, 41, 300, 130, 64, 97, 60, 1000, 49, 200], dtype=np.int64)

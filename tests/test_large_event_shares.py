@@ -1,7 +1,8 @@
 """The shares of the large-event launches (csrc/glv_share.h), compiled for the
 host with the undefined-behaviour sanitizer: over all workgroups of a launch
 every block of every event is done exactly once, whether the workgroups share
-the pairs or are given whole events."""
+the pairs or are given whole events; events that are dealt out are looked at
+once each, and neighbours go to many workgroups."""
 
 import os
 import shutil
@@ -45,8 +46,43 @@ static int check(const std::vector<int64_t>& n, int64_t limit, int64_t grid, int
   return 0;
 }
 
+// Events by workgroup, as a launch deals them out: window, slice, thread.
+template <int B>
+static int deal(int64_t ne, int grid, int slices) {
+  std::vector<int> owner(ne, -1);
+  const int64_t step = (int64_t)B * grid;
+  for (int b = 0; b < grid; ++b)
+    for (int tid = 0; tid < B; ++tid)
+      for (int64_t win = 0; win < ne; win += slices * step)
+        for (int sl = 0; sl < slices; ++sl) {
+          const int64_t e = win + glv::dealt_event<B>(tid, b, grid) + sl * step;
+          if (e >= ne) continue;
+          if (owner[e] != -1) return 1;
+          owner[e] = b;
+        }
+  for (int o : owner)
+    if (o < 0) return 1;
+  // a run of a thousand events, or the first hundred of every row of the grid
+  for (int64_t from = 0; from + 1000 <= ne; from += 50021) {
+    std::vector<int> mine(grid, 0);
+    for (int64_t e = from; e < from + 1000; ++e)
+      if (++mine[owner[e]] > 2 * glv::kDealt) return 1;
+  }
+  std::vector<int> mine(grid, 0);
+  const int64_t row = (int64_t)grid * glv::kDealt;
+  int64_t rows = 0;
+  for (int64_t r = 0; r + 100 <= ne; r += row, ++rows)
+    for (int64_t e = r; e < r + 100; ++e) ++mine[owner[e]];
+  for (int c : mine)
+    if (c > glv::kDealt * ((rows + 7) / 8 + 1)) return 1;
+  return 0;
+}
+
 int main() {
   int bad = 0;
+  for (int64_t ne : {1 << 18, (1 << 18) + 1, 700001, 1 << 21}) {
+    bad += deal<256>(ne, 1024, 12) + deal<256>(ne, 768, 12) + deal<512>(ne, 512, 8);
+  }
   for (bool by_events : {true, false})
     for (int64_t grid : {8, 1024})
       for (int64_t min_pairs : {64, 2048}) {
