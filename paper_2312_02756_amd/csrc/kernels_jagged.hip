@@ -2276,7 +2276,14 @@ __global__ __launch_bounds__(kBigBlock) void k_event_reduce_bwd_big(BwdArgs<T, C
 // pass over the batch and sums across wavefronts.  Bound by VALU issue: 117
 // us on the events named at k_event_dense (44 ms with one workgroup per event;
 // 202 us with blocks of 64 particles whose partners the workgroup staged).
-constexpr int kBwdGrid = 1024;
+// Workgroups: what the GPU holds at once, as for the forward (four per CU, three
+// with the registers and LDS of FP64; at 1,024 in FP64 the rest started when the
+// first were done: 8.0 -> 5.5 us on 2^19 small events, and 93 -> 70 us on 200 of 300
+// particles).
+template <typename T>
+constexpr int bwd_dense_grid() {
+  return sizeof(T) == 4 ? 1024 : 768;
+}
 template <typename T>
 constexpr int batch_cols() {
   return sizeof(T) == 4 ? 16 : 8;
@@ -2476,7 +2483,7 @@ __global__ __launch_bounds__(256, (sizeof(T) == 4 ? 4 : 3)) void k_event_bwd_den
   Share sh;
   int turn = 0;  // the workgroup's blocks so far: its wavefronts take them in turn
   const int64_t cap_pairs = npairs(A.cap);
-  scan_share<B, kBwdGrid>(
+  scan_share<B, bwd_dense_grid<T>()>(
       A.off, A.poff, A.ne, kDenseMinPairs, L, &sh,
       [](int64_t) { return 0; },
       [&](int, int64_t po, int64_t d) { return po + d > sh.q0 && (d > A.qcap || d > cap_pairs); },
@@ -2596,7 +2603,7 @@ hipError_t bwd_typed(int64_t ne, const int64_t* off, const int64_t* poff, const 
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;
   if (gpair)
-    hipLaunchKernelGGL((k_event_bwd_dense<T, COORDS>), dim3(kBwdGrid), dim3(256), 0, s, A);
+    hipLaunchKernelGGL((k_event_bwd_dense<T, COORDS>), dim3(bwd_dense_grid<T>()), dim3(256), 0, s, A);
   else
     hipLaunchKernelGGL((k_event_reduce_bwd_big<T, COORDS>), dim3(big_grid(ne)), dim3(kBigBlock), 0, s, A);
   return hipGetLastError();
