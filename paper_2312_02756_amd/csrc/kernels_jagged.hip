@@ -863,7 +863,7 @@ __global__ __launch_bounds__(kMaxBlock, (fwd_waves<T, MODE, BEST>())) void k_eve
       // (two records each) or the Cartesian vectors
       constexpr int kStride = kComp ? 2 : 1;
       const R4* const recs = kComp ? W.leg : W.cart;
-      const int rcap = kStageMasses ? 64 * (((qcap >> 6) - 1) | 1) : ((kComp || BEST) ? qcap : 0x3fffffff);
+      const int rcap = kStageMasses ? 64 * (((qcap >> 6) - 1) | 1) : qcap;
       T* const pout = want_pairs ? A.pair_m + q0 : nullptr;
       for (int r0 = 0; r0 < nq; r0 += rcap) {
         const int qn = min(rcap, nq - r0);
@@ -1932,7 +1932,6 @@ struct BwdArgs {
   int epb;         // events per wavefront tile
   int cap;         // particles staged per chunk (per wavefront)
   int qcap;        // pair upstreams staged per chunk (per wavefront)
-  int wave_bytes;  // LDS bytes per wavefront
 };
 
 // An event the tiled backward leaves to the second launch: more than
@@ -2597,7 +2596,6 @@ hipError_t bwd_typed(int64_t ne, const int64_t* off, const int64_t* poff, const 
   A.epb = t.events_per_tile;
   A.cap = bwd_cap(t);
   A.qcap = t.pairs_per_round;
-  A.wave_bytes = 0;
   hipLaunchKernelGGL((k_event_reduce_bwd<T, COORDS>), dim3(grid_for(ne, t.events_per_tile)), dim3(t.block), lds,
                      s, A);
   hipError_t err = hipGetLastError();
