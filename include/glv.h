@@ -94,22 +94,26 @@ typedef enum glv_mode { GLV_PLAIN = 0, GLV_COMPENSATED = 1 } glv_mode;
 
 /* Work decomposition of glv_event_reduce, glv_event_reduce_best_pair and
  * glv_event_reduce_bwd.  It changes
- * speed only: pair masses, totals and gradients of every event that fits the
- * tiling's staging capacity, and plain event masses, are identical for every
- * such tiling; the compensated event mass (a sum of per-pair terms, summed in
+ * speed only: pair masses, totals and gradients of every event that is done in
+ * the same launch, and plain event masses, are identical for every tiling; the compensated event mass (a sum of per-pair terms, summed in
  * an order that follows the tiling) may differ in the last bit between
- * tilings but is reproducible for a given tiling.  An event that does not fit
- * goes to a second launch of the same call: its plain pair masses are the
- * same, its sums take another order, and a compensated pair mass may differ
+ * tilings but is reproducible for a given tiling.  Larger events go to a second
+ * launch of the same call: their plain pair masses are the same bit for bit,
+ * their sums may take another order, and a compensated pair mass may differ
  * in the last bit (that launch fuses the arithmetic differently, which can
  * also move a pair across the FP64-redo threshold); all stay within the
  * stated accuracy.
+ * Which events are larger: where the forward evaluates pairs, those of more
+ * than 48 particles, or of more than 12 where the call's events have many
+ * pairs on average (from 170 to 480 on, by type and mode), so that the last
+ * bits of a compensated mass of an event of 13 to 48 particles can follow the
+ * other events of its call; where it evaluates none, those of more than
+ * lds_particles.  In the backward, see below.
  * Forward (glv_event_reduce): every wavefront (64 threads) of a workgroup
  * works alone on its own tile of consecutive events.
  *   block            threads per workgroup: 64, 128, 256 or 512
  *   events_per_tile  events of one wavefront's tile: 1 .. 64
  *   lds_particles    particles a wavefront stages at once: 64 .. 4096
- *                    (larger events go to the second launch)
  *   pairs_per_round  a multiple of 64 in 64 .. 4096: pairs a wavefront
  *                    evaluates per round, each lane a run of consecutive
  *                    pairs.  Plain masses (and the FP64 compensated ones) pass
@@ -353,10 +357,10 @@ glv_status glv_pair_offsets(int64_t n_events, const int64_t* offsets, int64_t* p
                             void* stream);
 
 /* Per-event reduction of CSR events.  Two launches on `stream`: the main one
- * reduces every event that fits the tiling's staging capacity; a short
- * second one scans the offsets for larger events (and, in the FP32
- * GLV_COMPENSATED mode, for events the first marked for the FP64 redo) and
- * reduces those from global memory.
+ * reduces the events its wavefronts stage (see glv_tiling); the second scans
+ * the offsets for the larger ones (and, in the FP32 GLV_COMPENSATED mode, for
+ * events the first marked for the FP64 redo) and shares those out over the
+ * GPU.
  *   offsets       n_events + 1 int64, offsets[0] = 0, non-decreasing
  *                 (trusted: see glv_validate_offsets)
  *   pair_offsets  from glv_pair_offsets; required when pair_m or a
@@ -365,8 +369,9 @@ glv_status glv_pair_offsets(int64_t n_events, const int64_t* offsets, int64_t* p
  * Outputs (each may be NULL = not wanted):
  *   total[4]  per-event sum of the particles' Cartesian vectors: four sums of
  *             the particles whose index in the event is r mod 4, each in index
- *             order, combined as ((P0 + P1) + (P2 + P3)); events beyond the
- *             staging capacity by a fixed-tree workgroup sum
+ *             order, combined as ((P0 + P1) + (P2 + P3)); by a fixed tree in
+ *             the second launch for events of more than 128 particles, where
+ *             no pairs are evaluated for those of more than lds_particles
  *   event_m   mass of the total: GLV_PLAIN from total; GLV_COMPENSATED as
  *             m^2 = sum_i M_i^2 + 2 sum_{i<j} (E_i E_j - p_i.p_j) with each pair
  *             product from the cancellation-free form

@@ -1125,16 +1125,18 @@ __global__ __launch_bounds__(kMaxBlock, (fwd_waves<T, MODE, BEST>())) void k_eve
 // is larger than all others together is one workgroup's in any mode.)
 // A workgroup finds its first event by interpolation or a search of
 // pair_offsets, reads the sizes of several thousand events at a time
-// (scan_share) and lists the ones that are its business.  It stages runs of listed events (kDenseCap particles) in LDS,
-// converted once per workgroup, and deals the staged events' pairs to its
-// wavefronts as equal runs of the folded pairs (Folded), 64 per step, so that
-// the masses go out as runs of consecutive addresses straight from registers
-// and a step's bookkeeping is the same for every lane.  What bounds it: VALU
-// issue (about 40 instructions per 64 FP32 pairs), then the stores: 61 us on
-// 4,096 FP32 events of 96 particles on average, up to 1,024 (2.8e7 pairs); 27 ms
-// with one workgroup per event, 72 us with unfolded rows and streaming stores.
-// An event that does not fit kDenseCap slots is walked in tiles of
-// kDenseCap / 2 rows by kDenseCap / 2 columns, one row per wavefront.
+// (scan_share) and lists the ones that are its business.  It stages runs of
+// listed events (dense_cap particles) in LDS, converted once per workgroup, and
+// deals the staged events' pairs to its wavefronts as equal runs of the folded
+// pairs (Folded), 64 per step, so that the masses go out as runs of consecutive
+// addresses straight from registers and a step's bookkeeping is the same for
+// every lane.  What bounds it: VALU issue for two thirds of it (54 instructions
+// per 64 FP32 pairs, staging and totals included: 39 us), then waits on the
+// stores and on LDS: 57 us on 4,096 FP32 events of 96 particles on average, up to
+// 1,024 (2.8e7 pairs); 27 ms with one workgroup per event, 72 us with unfolded
+// rows and streaming stores.
+// An event that does not fit dense_cap slots is walked in tiles of half as many
+// rows by half as many columns, one row per wavefront.
 
 // Particles staged per chunk (LDS: 16 KB of records in FP64, 8 KB in FP32, 24 KB
 // with the legs of the compensated mode in either).
@@ -2272,9 +2274,12 @@ __global__ __launch_bounds__(kBigBlock) void k_event_reduce_bwd_big(BwdArgs<T, C
 // The next batch's upstreams and the next partners are in flight while a
 // batch is evaluated.  Every ordered pair's c = g/|m| is evaluated by the lane
 // that needs it: twice per pair, where a shared evaluation would need a second
-// pass over the batch and sums across wavefronts.  Bound by VALU issue: 117
-// us on the events named at k_event_dense (44 ms with one workgroup per event;
-// 202 us with blocks of 64 particles whose partners the workgroup staged).
+// pass over the batch and sums across wavefronts.  Bound by VALU issue for two
+// thirds of it (55 instructions per 64 ordered FP32 pairs: 79 us), then by waits
+// on the upstreams: 111 us on the events named at k_event_dense (44 ms with one
+// workgroup per event; 202 us with blocks of 64 particles whose partners the
+// workgroup staged).
+//
 // Workgroups: what the GPU holds at once, as for the forward (four per CU, three
 // with the registers and LDS of FP64; at 1,024 in FP64 the rest started when the
 // first were done: 8.0 -> 5.5 us on 2^19 small events, and 93 -> 70 us on 200 of 300
