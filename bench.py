@@ -341,10 +341,10 @@ def summarize_sq(csvs):
 
 
 # Sources that define each kernel and its launch configuration.
-KERNEL_SOURCES = {k: ["kernels_jagged.hip", "glv_abi.hip"] for k in ("event_reduce", "event_reduce32c",
+KERNEL_SOURCES = {k: ["kernels_jagged.hip", "glv_share.h", "glv_abi.hip"] for k in ("event_reduce", "event_reduce32c",
                                                                        "event_reduce_bwd")}
 KERNEL_SOURCES.update({k: ["kernels_analysis.hip"] for k in ("mass_histogram", "event_best_pair")})
-KERNEL_SOURCES["event_best_pair_fused"] = ["kernels_jagged.hip", "glv_abi.hip"]
+KERNEL_SOURCES["event_best_pair_fused"] = ["kernels_jagged.hip", "glv_share.h", "glv_abi.hip"]
 SHARED_SOURCES = ["glv_device.h", "glv_math.h", "glv_launch.h"]
 
 

@@ -93,11 +93,11 @@ typedef enum glv_coords { GLV_PXPYPZE = 0, GLV_PTETAPHIM = 1, GLV_PTETAPHIE = 2,
 typedef enum glv_mode { GLV_PLAIN = 0, GLV_COMPENSATED = 1 } glv_mode;
 
 /* Work decomposition of glv_event_reduce, glv_event_reduce_best_pair and
- * glv_event_reduce_bwd.  It changes
- * speed only: pair masses, totals and gradients of every event that is done in
- * the same launch, and plain event masses, are identical for every tiling; the compensated event mass (a sum of per-pair terms, summed in
- * an order that follows the tiling) may differ in the last bit between
- * tilings but is reproducible for a given tiling.  Larger events go to a second
+ * glv_event_reduce_bwd.  It changes speed only: pair masses, totals and
+ * gradients of every event that is done in the same launch, and plain event
+ * masses, are identical for every tiling; the compensated event mass (a sum of
+ * per-pair terms, summed in an order that follows the tiling) may differ in the
+ * last bit between tilings but is reproducible for a given tiling.  Larger events go to a second
  * launch of the same call: their plain pair masses are the same bit for bit,
  * their sums may take another order, and a compensated pair mass may differ
  * in the last bit (that launch fuses the arithmetic differently, which can
