@@ -206,15 +206,18 @@ int tile_events(int dflt, int64_t ne) {
 // cut the wavefronts per CU, and large for the selection, which stages none.
 // 2^20 Poisson(8) events, defaults above -> these: FP64 182 -> 165 us, FP32 112
 // -> 103, compensated FP64 589 -> 478 and FP32 190 -> 179, best pair FP64 175
-// -> 151 and FP32 131 -> 107; 2^19 events of 14 particles: FP64 188 -> 181, FP32
+// -> 151 and FP32 131 -> 107, compensated best pair FP64 470 -> 440 and FP32 206
+// -> 190 (255 at the plain one's sizes); 2^19 events of 14 particles: FP64 188 -> 181, FP32
 // 122 -> 117, compensated FP64 770 -> 600, best pair FP64 206 -> 173.
 glv::Tiling pair_tiling(glv_dtype dt, glv_mode mode, bool best) {
   const bool f64 = dt == GLV_F64;
   glv::Tiling t;
   t.block = 64;
   if (best) {
-    t.events_per_tile = f64 ? 40 : 64;
-    t.lds_particles = f64 ? 192 : 320;
+    // FP32 compensated legs take three times the LDS of plain records: 320 of
+    // them leave 2.5 wavefronts per SIMD
+    t.events_per_tile = f64 ? 40 : mode == GLV_COMPENSATED ? 32 : 64;
+    t.lds_particles = f64 || mode == GLV_COMPENSATED ? 192 : 320;
     t.pairs_per_round = 3072;
   } else if (mode == GLV_COMPENSATED) {
     t.events_per_tile = 32;

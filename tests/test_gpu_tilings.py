@@ -96,3 +96,28 @@ def test_autotuning_tries_what_an_untuned_call_takes(cache, dtype):
     assert glv.glv_current_tiling(dtype)[1] == 4
     best = glv.glv_autotune_event_reduce_bwd(p, off, grad_pair_m=up)
     assert best == glv.glv_current_tiling_bwd(dtype) and best[1] == 4
+
+
+@pytest.mark.parametrize("mode", ["plain", "compensated"])
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+def test_untuned_best_pair_is_no_slower_than_given_sizes(mode, dtype):
+    """2^18 events of 8 particles: the sizes of an untuned call against those
+    calls took before they followed type and mode (a third more time in the
+    FP32 compensated mode at the plain one's sizes), with room for noise."""
+    glv.glv_autotune_forget()
+    off, p, _ = _events(synth.rng(986).poisson(8.0, 1 << 18), 987, dtype)
+    po = glv.glv_pair_offsets(off)
+
+    def us(tiling):
+        ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+        ev[0].record()
+        for _ in range(5):
+            glv.glv_event_reduce_best_pair(p, off, 91.2, po, mode=mode, tiling=tiling)
+        ev[1].record()
+        ev[1].synchronize()
+        return ev[0].elapsed_time(ev[1]) * 200.0
+
+    us((0, 0, 0, 0)), us((64, 64, 128, 1024))
+    turns = [(us((0, 0, 0, 0)), us((64, 64, 128, 1024))) for _ in range(9)]
+    untuned, given = (sorted(t[k] for t in turns)[4] for k in (0, 1))
+    assert untuned < 1.1 * given, (untuned, given)
