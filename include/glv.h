@@ -105,10 +105,10 @@ typedef enum glv_mode { GLV_PLAIN = 0, GLV_COMPENSATED = 1 } glv_mode;
  * stated accuracy.
  * Which events are larger: where the forward evaluates pairs, those of more
  * than 48 particles, or of more than 12 where the call's events have many
- * pairs on average (from 170 to 480 on, by type and mode), so that the last
- * bits of a compensated mass of an event of 13 to 48 particles can follow the
- * other events of its call; where it evaluates none, those of more than
- * lds_particles.  In the backward, see below.
+ * pairs on average (from 170 to 640 on, by type, mode and number of events),
+ * so that the last bits of a compensated mass of an event of 13 to 48
+ * particles can follow the other events of its call; where it evaluates none,
+ * those of more than lds_particles.  In the backward, see below.
  * Forward (glv_event_reduce): every wavefront (64 threads) of a workgroup
  * works alone on its own tile of consecutive events.
  *   block            threads per workgroup: 64, 128, 256 or 512

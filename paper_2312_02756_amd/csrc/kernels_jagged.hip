@@ -489,22 +489,36 @@ __device__ __forceinline__ int search_le32(const int* a, int lo, int hi, int key
 // small events the tail of the sizes is better done beside its neighbours
 // (up to kDenseFrom particles) than by waking the second launch, and once most
 // events are large that launch takes all but the smallest (kDenseLow).  The
-// line lies where the two cross for Poisson sizes, by type; 40,000 events,
-// first launch / second launch: FP64 of 24 particles 58.7 / 58.3 us, of 28
-// 80.5 / 64.4; FP32 of 24 45.7 / 47.6, of 26 57.0 / 51.3; FP32 compensated of
-// 20 76.5 / 81.3, of 24 101 / 87; FP64 compensated of 18 121 / 121, of 20 149 /
-// 127; best pair FP64 of 28 84 / 89, FP32 of 32 86 / 83.  With 300,000 events
-// the first launch stays ahead longer (best pair of 32 particles 417 / 603,
-// FP32 of 28 230 / 255), with 1,000 also (FP32 of 28 19.6 / 23.1).
+// line lies where the two cross for Poisson sizes, by type, mode and number of
+// events: with few events the first launch's small tiles spread them as well as
+// the second's shares do, and with very many its wavefronts fill the GPU with
+// less work per pair.  All but the smallest in the second launch / all in the
+// first, plain FP32 of 26 particles 1.24 at 1,000 events, 0.81 at 10,000, 0.98 at
+// 100,000, 1.16 at 270,000; FP64 1.19, 0.84, 1.02 and 1.00; compensated FP32 of 24
+// 0.97, 0.61, 0.97 and 1.10; compensated FP64 of 20 1.20, 0.87, 0.93 and 0.94;
+// best pair FP64 of 32 0.69, 0.74, 1.22 and (200,000) 1.36; compensated best pair
+// FP32 of 32 0.64, 0.61, 1.16 and (200,000) 1.20, FP64 0.65, 0.64, 0.96 and 1.04.
+// (Best pairs cross at 40 particles from 65,000 events on with the sizes of
+// untuned calls; smaller tilings that are given cross earlier, so the line is at
+// 36: 100,000 events of 40 at (64, 64, 128, 1024) 434 us in the first launch, 221 in
+// the second.)
 constexpr int kDenseFrom = 48;
 constexpr int kDenseLow = 12;
+constexpr int64_t kShareByEvents = 1 << 18;  // see my_share
+
+// That line in pairs per event.
+template <typename T, int MODE, bool BEST>
+__device__ __forceinline__ int64_t dense_line(int64_t ne) {
+  constexpr bool f64 = sizeof(T) == 8, comp = MODE == GLV_COMPENSATED;
+  if (ne <= 4096) return BEST ? 480 : comp ? (f64 ? 270 : 290) : 370;
+  if (ne <= 49152) return BEST ? 480 : comp ? (f64 ? 170 : 250) : 290;
+  if (ne < kShareByEvents) return BEST ? (comp && f64 ? 480 : 640) : comp ? (f64 ? 170 : 290) : 340;
+  return BEST ? 640 : comp ? (f64 ? 200 : 400) : f64 ? 340 : 480;
+}
 
 template <typename T, int MODE, bool BEST>
 __device__ __forceinline__ int small_events(const int64_t* poff, int64_t ne, int small) {
-  constexpr int64_t kMean = BEST                      ? 480
-                            : MODE == GLV_COMPENSATED ? (sizeof(T) == 8 ? 170 : 250)
-                                                      : 290;
-  return poff[ne] >= ne * kMean ? min(small, kDenseLow) : small;
+  return poff[ne] >= ne * dense_line<T, MODE, BEST>(ne) ? min(small, kDenseLow) : small;
 }
 
 // LDS of one wavefront of the forward reduction (cap particles, qcap pairs):
@@ -1228,8 +1242,6 @@ template <int GRID>
 __device__ __forceinline__ Share my_share(int64_t nq, int64_t min_pairs) {
   return pair_share(nq, min_pairs, GRID, share_index<GRID>());
 }
-
-constexpr int64_t kShareByEvents = 1 << 18;
 
 // An event e with poff[e] <= q at most `within` events before the last such
 // one, by probing 1024 evenly spread pair offsets per round.

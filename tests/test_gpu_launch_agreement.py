@@ -15,7 +15,7 @@ pytestmark = pytest.mark.gpu
 
 glv = pytest.importorskip("paper_2312_02756_amd.glv")
 
-N = 20  # particles per event: 190 pairs, below the line to the second launch for a mean of 190 pairs and above it for 290
+N = 20  # particles per event: 190 pairs, for a mean of which the first launch does them; for one of 1,000 the second
 
 
 def _cartesian(scale, g, dtype):
@@ -35,11 +35,11 @@ def _both_launches(cols, ne):
     """Pair masses of the events alone (first launch) and with large events behind them (second launch)."""
     alone = np.arange(ne + 1, dtype=np.int64) * N
     large = 200
-    extra = (ne * 110) // (large * (large - 1) // 2 - 290) + 1  # so that the mean passes 290 pairs
+    extra = (ne * 810) // (large * (large - 1) // 2 - 1000) + 1  # so that the mean passes 1,000 pairs
     counts = np.concatenate([np.full(ne, N), np.full(extra, large)])
     off = np.concatenate([[0], np.cumsum(counts)]).astype(np.int64)
     pairs = counts * (counts - 1) // 2
-    assert pairs[:ne].mean() < 290 <= pairs.mean()
+    assert pairs[:ne].mean() == 190 and pairs.mean() >= 1000
     pad = [torch.ones(extra * large, dtype=c.dtype) * (1.0 if k == 3 else 0.1) for k, c in enumerate(cols)]
     first = glv.glv_event_reduce(tuple(c.cuda() for c in cols), _off(alone), coords="PxPyPzE")
     second = glv.glv_event_reduce(tuple(torch.cat([c, d]).cuda() for c, d in zip(cols, pad)), _off(off),
