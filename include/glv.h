@@ -97,18 +97,20 @@ typedef enum glv_mode { GLV_PLAIN = 0, GLV_COMPENSATED = 1 } glv_mode;
  * gradients of every event that is done in the same launch, and plain event
  * masses, are identical for every tiling; the compensated event mass (a sum of
  * per-pair terms, summed in an order that follows the tiling) may differ in the
- * last bit between tilings but is reproducible for a given tiling.  Larger events go to a second
- * launch of the same call: their plain pair masses are the same bit for bit,
- * their sums may take another order, and a compensated pair mass may differ
- * in the last bit (that launch fuses the arithmetic differently, which can
- * also move a pair across the FP64-redo threshold); all stay within the
- * stated accuracy.
+ * last bit between tilings but is reproducible for a given tiling.
+ * Larger events go to a second launch of the same call: their plain pair
+ * masses are the same bit for bit, their sums may take another order, and a
+ * compensated pair mass may differ in the last bit (that launch fuses the
+ * arithmetic differently, which can also move a pair across the FP64-redo
+ * threshold); all stay within the stated accuracy.
  * Which events are larger: where the forward evaluates pairs, those of more
  * than 48 particles, or of more than 12 where the call's events have many
  * pairs on average (from 170 to 640 on, by type, mode and number of events),
- * so that the last bits of a compensated mass of an event of 13 to 48
+ * so that the last bits of a compensated pair mass of an event of 13 to 48
  * particles can follow the other events of its call; where it evaluates none,
- * those of more than lds_particles.  In the backward, see below.
+ * those of more than lds_particles.  The compensated event mass of an event of
+ * more than 12 particles is summed in an order that follows the events beside
+ * it, and its last bits with them.  In the backward, see below.
  * Forward (glv_event_reduce): every wavefront (64 threads) of a workgroup
  * works alone on its own tile of consecutive events.
  *   block            threads per workgroup: 64, 128, 256 or 512
