@@ -1159,7 +1159,7 @@ constexpr int dense_cap() {
   return (MODE == GLV_COMPENSATED && sizeof(T) == 8) ? 256 : 512;
 }
 constexpr int kDenseEvents = 64;  // events per chunk (one lane each)
-constexpr int kDenseMinPairs = 2048;  // pairs a workgroup takes at least
+constexpr int kDenseMinPairs = 2048;  // pairs a workgroup takes at least, of few events
 
 template <int MODE, bool BEST>
 constexpr bool dense_owned() {  // events stay with one workgroup
@@ -1178,6 +1178,15 @@ constexpr int dense_block() {
 template <int MODE, bool BEST>
 constexpr int dense_grid() {
   return MODE == GLV_COMPENSATED ? 768 : BEST ? 512 : 1024;
+}
+
+// Slices of events a workgroup of those launches reads at once: 4,096 events, or
+// 3,072, or 2,048 in the compensated mode, whose registers have no room for
+// more (twelve slices: 44 bytes of scratch memory, and best pairs of 100,000
+// FP64 events of 8 particles take 66 us instead of 63).
+template <int MODE, bool BEST>
+constexpr int dense_slices() {
+  return MODE == GLV_COMPENSATED || BEST ? 8 : 12;
 }
 
 // The events a workgroup of the large-event launches has to do among B
@@ -1272,6 +1281,8 @@ __device__ __forceinline__ int64_t search_share(const int64_t* __restrict__ poff
   return lo;
 }
 
+struct Nothing {};  // what peek returns where the pair offsets tell all
+
 // What a thread sees of its events of a window, one per slice: event e of slice
 // sl is wins + at + sl STEP.
 template <int SLICES, int STEP, typename Seen>
@@ -1281,21 +1292,24 @@ struct Window {
   unsigned po[SLICES], pe[SLICES];
   Seen seen[SLICES];
 
-  // SKIP: slices past the last event are not read
-  template <bool SKIP, typename Peek>
+  // Slices past the window's last event are not read.
+  template <typename Peek>
   __device__ __forceinline__ void read(const int64_t* __restrict__ poff, int64_t wins, int at, int last, Peek peek) {
 #pragma unroll
     for (int sl = 0; sl < SLICES; ++sl) {
-      if constexpr (SKIP) {
-        po[sl] = pe[sl] = 0;
-        seen[sl] = {};
-        if (sl > 0 && sl * STEP > last) continue;
-      }
+      po[sl] = pe[sl] = 0;
+      seen[sl] = {};
+      if (sl > 0 && sl * STEP > last) continue;
       const int t = min(sl * STEP + at, last);
       const unsigned* const low = reinterpret_cast<const unsigned*>(poff + wins);
       po[sl] = low[2 * t];
       pe[sl] = low[2 * t + 2];
       seen[sl] = peek(wins + t);
+    }
+    // nothing of a slice is looked at, and waited for, before all are on their way
+    if constexpr (!__is_same(Seen, Nothing)) {
+#pragma unroll
+      for (int sl = 0; sl < SLICES; ++sl) asm volatile("" : "+v"(seen[sl]));
     }
   }
 
@@ -1317,32 +1331,43 @@ struct Window {
 // Calls body(win, listed) with the whole workgroup for every slice of B events
 // that has events e with pick(peek(e), po, d) in its share (first pair po, d
 // pairs; peek reads what else tells), listed in L in order with their index
-// from event win on and flag(d).  The pair offsets of kSlices slices are read
-// at once, first around the place where the share would begin if all events
-// had the same number of pairs (sizes drawn alike stay within the slack of
-// about 1000 events either way for a million events), so that where no event
-// is the workgroup's business, as on small events, the scan costs one memory
-// latency; a share that begins outside is searched for.
-template <int B, int GRID, typename Peek, typename Pick, typename Flag, typename Body>
+// from event wins on and flag(d).  The pair offsets of up to kSlices slices are
+// read at once, first around the place where the share would begin if all events
+// had the same number of pairs, so that where no event is the workgroup's
+// business, as on small events, the scan costs one memory latency; a share that
+// begins outside is searched for.  Such a launch takes 5.6 us on 4,096 FP64
+// events and 6.0 on 100,000, FP32 compensated 5.4 and 6.3; with windows of all
+// slices and 2,048 pairs to a share 6.8, 7.8, 11.0 and 10.1.
+template <int B, int GRID, int kSlices, typename Peek, typename Pick, typename Flag, typename Body>
 __device__ __forceinline__ void scan_share(const int64_t* __restrict__ off, const int64_t* __restrict__ poff,
-                                           int64_t ne, int64_t min_pairs, EventList<B>& L, Share* share, Peek peek,
-                                           Pick pick, Flag flag, Body body) {
-  constexpr int kSlices = B == 256 ? 12 : 8;
+                                           int64_t ne, EventList<B>& L, Share* share, Peek peek, Pick pick, Flag flag,
+                                           Body body) {
   constexpr int64_t kWin = (int64_t)kSlices * B;
+  // few pairs fill fewer workgroups, but only where one window holds all events:
+  // the place of such shares is not known before the number of pairs (20,000
+  // events of 8 particles, all outputs, FP32 17.6 -> 14.9 us, FP64 20.0 -> 17.1)
+  const int64_t min_pairs = ne > kWin ? 64 : kDenseMinPairs;
   using Seen = decltype(peek((int64_t)0));
   const int tid = (int)threadIdx.x;
   const bool dealt = ne >= kShareByEvents;
   int64_t wins = 0;  // the window's first event
   int tries = 0;
   bool more = true;
+  int64_t win = kWin;  // events of a window, whole slices
   if (!dealt) {
-    // where equal events would put the share, if it is no smaller than the rest
-    wins = ne * share_index<GRID>() / GRID - (kWin - ne / GRID) / 2;
-    wins = max((int64_t)0, min(wins, ne - kWin));
+    // Where equal events would put the share.  For sizes drawn alike the place is
+    // off by 0.4 sqrt(ne) events (Poisson sizes of 8) to 0.9 (a long tail), one
+    // standard deviation; the window has 2 sqrt(ne) on either side.
+    if (ne > kWin) {
+      const int need = (int)ne / GRID + (int)(4.0f * __builtin_amdgcn_sqrtf((float)ne));
+      win = B * min(kSlices, 1 + need / B);
+    }
+    wins = ne * share_index<GRID>() / GRID - (win - ne / GRID) / 2;
+    wins = max((int64_t)0, min(wins, ne - win));
     tries = 2;
   }
   while (more) {
-    const int64_t span = dealt ? kWin * GRID : kWin;  // events the window reaches over
+    const int64_t span = dealt ? kWin * GRID : win;  // events the window reaches over
     const int64_t wend = min(wins + span, ne);
     const int64_t at0 = poff[wins], at1 = poff[wend], nq = poff[ne];
     const int last = (int)(wend - wins) - 1;
@@ -1350,21 +1375,21 @@ __device__ __forceinline__ void scan_share(const int64_t* __restrict__ off, cons
     if (dealt) {
       const int at = dealt_event<B>(tid, share_index<GRID>(), GRID);
       Window<kSlices, B * GRID, Seen> w;
-      w.template read<true>(poff, wins, at, last, peek);
+      w.read(poff, wins, at, last, peek);
       *share = whole_share(nq);
       some = w.picked(at0, at1, nq, at, last, pick);
     } else {
       Window<kSlices, B, Seen> w;
-      w.template read<false>(poff, wins, tid, last, peek);
+      w.read(poff, wins, tid, last, peek);
       if (tries) {
         *share = my_share<GRID>(nq, min_pairs);
         if (share->q0 >= share->q1) return;
         if (at0 > share->q0 || at1 <= share->q0) {  // begins elsewhere
           if (--tries && share->q1 - share->q0 == min_pairs) {  // few pairs: shares larger than the grid's equal ones
-            wins = (int64_t)((double)ne * (double)share->q0 / (double)nq) - kWin / 2;
-            wins = max((int64_t)0, min(wins, ne - kWin));
+            wins = (int64_t)((double)ne * (double)share->q0 / (double)nq) - win / 2;
+            wins = max((int64_t)0, min(wins, ne - win));
           } else {
-            wins = search_share<B>(poff, ne, share->q0, kWin / 4, L.cnt);
+            wins = search_share<B>(poff, ne, share->q0, win / 4, L.cnt);
             tries = 0;
           }
           continue;
@@ -1586,12 +1611,14 @@ __global__ __launch_bounds__((dense_block<MODE, BEST>()),
   // first pair mass, looked at by picked(); what is read here is then unused, but
   // read without a branch, so that all slices' reads are in flight together)
   const T* const marks = A.event_m ? A.event_m : BEST ? A.best_m : reinterpret_cast<const T*>(A.poff);
-  auto peek = [&](int64_t e) -> float {
-    if constexpr (kDefer) return marks[e];
-    return 0.0f;
+  auto peek = [&](int64_t e) {
+    if constexpr (kDefer)
+      return marks[e];
+    else
+      return Nothing{};
   };
   // whether an event (first pair po, d pairs) is this workgroup's business
-  auto picked = [&](float seen, int64_t po, int64_t d) -> bool {
+  auto picked = [&](auto seen, int64_t po, int64_t d) -> bool {
     if (kOwn ? po < sh.q0 : po + d <= sh.q0) return false;
     if constexpr (kDefer) {
       if (d > 0 && d <= small_pairs) {
@@ -1838,7 +1865,7 @@ __global__ __launch_bounds__((dense_block<MODE, BEST>()),
       li += nc;
     }
   };
-  scan_share<B, dense_grid<MODE, BEST>()>(A.off, A.poff, A.ne, kDenseMinPairs, L, &sh, peek, picked, redo_only, work);
+  scan_share<B, dense_grid<MODE, BEST>(), dense_slices<MODE, BEST>()>(A.off, A.poff, A.ne, L, &sh, peek, picked, redo_only, work);
   if constexpr (kDefer) {
     if (A.fallback) {
 #pragma unroll
@@ -2499,10 +2526,10 @@ __global__ __launch_bounds__(256, (sizeof(T) == 4 ? 4 : 3)) void k_event_bwd_den
   Share sh;
   int turn = 0;  // the workgroup's blocks so far: its wavefronts take them in turn
   const int64_t cap_pairs = npairs(A.cap);
-  scan_share<B, bwd_dense_grid<T>()>(
-      A.off, A.poff, A.ne, kDenseMinPairs, L, &sh,
-      [](int64_t) { return 0; },
-      [&](int, int64_t po, int64_t d) { return po + d > sh.q0 && (d > A.qcap || d > cap_pairs); },
+  scan_share<B, bwd_dense_grid<T>(), 12>(
+      A.off, A.poff, A.ne, L, &sh,
+      [](int64_t) { return Nothing{}; },
+      [&](Nothing, int64_t po, int64_t d) { return po + d > sh.q0 && (d > A.qcap || d > cap_pairs); },
       [](int64_t) { return false; },
       [&](int64_t win, int listed) {
         for (int li = 0; li < listed; ++li) {
