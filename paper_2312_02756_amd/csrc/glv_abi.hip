@@ -190,11 +190,16 @@ glv::Tiling default_tiling_bwd(glv_dtype dt) {
 // few events smaller tiles spread them over more of the GPU.  On Poisson(8)
 // events, FP64, forward / backward: 1,000 events 16.3 / 32.7 us at the default
 // of 32 / 64, 6.2 / 8.3 us at 4; 16,000 events 17.0 / 32.8 us against 9.0 /
-// 13.2 us at 8; 64,000 events 20.5 / 42.6 us against 18.5 / 32.8 us at 16.
-int tile_events(int dflt, int64_t ne) {
+// 13.2 us at 8; 64,000 events 20.5 / 42.6 us against 18.5 / 32.8 us at 16.  The
+// forward's pair masses keep 16 up to `many` = 393,216 events, the more so the
+// larger these are: 200,000 events of 8 / 18 / 24 particles, FP64 49.9 / 135 / 217
+// us at 32, 47.2 / 118 / 189 at 16, FP32 compensated 56 / 193 / 310 and 50 / 161 /
+// 267; 400,000 of 8 73.3 against 74.2 and 83.8 against 80.1, but 2^20 FP64 161
+// against 171.
+int tile_events(int dflt, int64_t ne, int64_t many = 131072) {
   if (ne <= 8192) return std::min(dflt, 4);
   if (ne <= 32768) return std::min(dflt, 8);
-  if (ne <= 131072) return std::min(dflt, 16);
+  if (ne <= many) return std::min(dflt, 16);
   return dflt;
 }
 
@@ -290,7 +295,7 @@ glv::Tiling untuned_tiling_bwd(glv_dtype dt, int64_t ne, int64_t n_pairs) {
 // The same for the forward (n_pairs: 0 where the call evaluates no pairs).
 glv::Tiling untuned_tiling(glv_dtype dt, glv_mode mode, int64_t ne, int64_t n_pairs, bool best) {
   glv::Tiling t = n_pairs ? pair_tiling(dt, mode, best) : best ? default_tiling_best() : default_tiling(dt, mode);
-  t.events_per_tile = tile_events(t.events_per_tile, ne);
+  t.events_per_tile = n_pairs && !best ? tile_events(t.events_per_tile, ne, 3 << 17) : tile_events(t.events_per_tile, ne);
   return t;
 }
 

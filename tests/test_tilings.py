@@ -135,3 +135,15 @@ def test_partly_given_tilings_are_refused_at_any_number_of_events(lib, ne):
     for bad in ((512, 0, 208, 64), (256, 0, 464, 64)):
         b = ctypes.byref(_lib.glv_tiling(*bad))
         assert lib.glv_event_reduce_best_pair(2, 1, 0, ne, off, po, p, 91.0, 140 * GiB, em, None, b, None) == TILING, bad
+
+
+@pytest.mark.parametrize("mode", ["plain", "compensated"])
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+def test_tiles_of_the_forward_stay_small_up_to_393216_events(cache, dtype, mode):
+    """Where pairs are evaluated; without them, and in the reverse mode, up to 131,072."""
+    for n_pairs in (None, 1 << 22):
+        tile = lambda ne: glv.glv_call_tiling(ne, n_pairs, dtype, mode=mode)[1]  # noqa: E731
+        assert tile(32769) == tile(131073) == tile(393216) == 16
+        assert tile(393217) == tile(1 << 22) > 16
+    assert glv.glv_call_tiling(131073, 0, dtype, mode=mode)[1] > 16
+    assert glv.glv_call_tiling(131073, None, dtype, backward=True)[1] > 16
