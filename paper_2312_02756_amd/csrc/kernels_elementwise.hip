@@ -51,7 +51,10 @@ __global__ __launch_bounds__(Op::kBlock) void k_stream(Op op, int64_t n, unsigne
 // boost, 400,000 items: FP32 12.4 -> 9.8 us, FP64 18.9 -> 15.1; of the mass,
 // FP64 20.9 -> 17.4, 1,500,000 items 66.2 -> 60.9; of 5,000,000 (360 MB and
 // more) 190 -> 194 if not streamed.  Stores always stream (cached, they gained
-// nothing beside cached loads and lost up to 8 % on large columns).
+// nothing beside cached loads and lost up to 8 % on large columns).  Inputs that
+// nothing wrote or read lately lose a little: a plain mass alone on new columns
+// of 110 to 160 MB takes 3 to 8 % longer than streamed, against the 8 to 13 % it
+// gains where they are read again.
 constexpr int64_t kCachedBytes = (int64_t)160 << 20;
 
 template <typename T, typename Op>
